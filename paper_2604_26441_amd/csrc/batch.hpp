@@ -30,7 +30,8 @@ struct BSys {               // one system (its hierarchy's operators)
   const double* ke64;
   int nL;
   const int* free_idx;
-  const double* Ainv;
+  const double* Ainv;      // rows ld_inv doubles apart
+  int ld_inv;
 };
 
 struct BItem {              // one (system, load case) solve and its work vectors

@@ -151,16 +151,21 @@ void launch_residual(const double* f, const double* Ax, double* r, int n, RedWs 
                      double* out_rr, hipStream_t s);
 
 // ---- coarsest dense solve (kernels_dense.hip) ------------------------------
-void launch_dense_assemble(const Grid& g, const double* S, const int* free_idx, int nf,
+// Rows of A are ld doubles apart: whole 128-byte lines, so that a tile's rows
+// start and end on them (the inverse reads and writes A once per two pivot
+// blocks).
+inline int dense_ld(int nf) { return (nf + 15) / 16 * 16; }
+void launch_dense_assemble(const Grid& g, const double* S, const int* free_idx, int nf, int ld,
                            double* A, hipStream_t s);
-void launch_dense_add_diag(double* A, int nf, const double* mean_diag_sum, hipStream_t s,
+void launch_dense_add_diag(double* A, int nf, int ld, const double* mean_diag_sum, hipStream_t s,
                            double* eps_out);
-void launch_dense_diag_sum(const double* A, int nf, RedWs ws, double* out, hipStream_t s);
-int dense_spd_inverse(double* A, int nf, double* scratch, int* d_flag, hipStream_t s);
+void launch_dense_diag_sum(const double* A, int nf, int ld, RedWs ws, double* out, hipStream_t s);
+int dense_spd_inverse(double* A, int nf, int ld, double* scratch, int* d_flag, hipStream_t s);
+size_t dense_inverse_scratch(int nf);   // its scratch, in doubles
 // Symmetric coarsest solve from the packed upper-triangle tiles of Ainv:
 // sym_tiles(nf) tiles of 64 x 64 doubles; partials 2 * sym_tiles(nf) * 64 doubles.
 int sym_tiles(int nf);
-void launch_dense_pack(const double* A, int nf, double* P, hipStream_t s);
+void launch_dense_pack(const double* A, int nf, int ld, double* P, hipStream_t s);
 void launch_dense_symv(const double* P, const int* free_idx, int nf, const double* r,
                        double* partials, double* z, hipStream_t s);
 

@@ -152,7 +152,7 @@ __device__ __attribute__((noinline)) void block_vcycle(const BlockCtx<BS>& C, co
     __syncthreads();
     double* xc = I.lx[L - 1][0];
     for (int i = threadIdx.x; i < S.nL; i += BS) {
-      const double* row = S.Ainv + (size_t)i * S.nL;
+      const double* row = S.Ainv + (size_t)i * S.ld_inv;
       double s = 0.0;
       for (int j = 0; j < S.nL; ++j) s += row[j] * I.rc[j];
       xc[S.free_idx[i]] = s;

@@ -334,7 +334,7 @@ __global__ __launch_bounds__(kB) void k_bs_coarse_symv(const BSys* __restrict__ 
   for (int rr = w; rr < kCoarseRows; rr += kB / 64) {
     const int i = sl.lb * kCoarseRows + rr;
     if (i >= S.nL) break;
-    const double* row = S.Ainv + (size_t)i * S.nL;
+    const double* row = S.Ainv + (size_t)i * S.ld_inv;
     double s = 0.0;
     for (int j = lane; j < S.nL; j += 64) s += row[j] * I.rc[j];
     s = wave_sum(s);

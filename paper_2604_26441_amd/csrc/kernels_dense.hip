@@ -5,279 +5,413 @@
 
 namespace sgmg {
 
-constexpr int kNB = 64;       // Gauss-Jordan panel width
+constexpr int kNB = 64;       // pivot block width
 
-__global__ void k_dense_assemble(Grid g, const double* __restrict__ S,
-                                 const int* __restrict__ free_idx, int nf, double* __restrict__ A) {
-  const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (size_t)nf * nf) return;
-  const int i = (int)(t / nf), j = (int)(t % nf);
+// One matrix row per blockIdx.x.  Columns further away than one stencil reach
+// in DOF order are zeros, decided before any index is split.
+__global__ __launch_bounds__(256) void k_dense_assemble(Grid g, const double* __restrict__ S,
+                                                        const int* __restrict__ free_idx, int nf,
+                                                        int ld, double* __restrict__ A) {
+  const int i = blockIdx.x;
+  const int j = blockIdx.y * 256 + threadIdx.x;
+  if (j >= nf) return;
   const int di = free_idx[i], dj = free_idx[j];
-  const int ni = di / 3, nj = dj / 3, d = di % 3, e = dj % 3;
-  const int ix = ni % g.Nx, iy = (ni / g.Nx) % g.Ny, iz = ni / (g.Nx * g.Ny);
-  const int jx = nj % g.Nx, jy = (nj / g.Nx) % g.Ny, jz = nj / (g.Nx * g.Ny);
-  const int ox = jx - ix, oy = jy - iy, oz = jz - iz;
+  const int ni = di / 3, d = di % 3, reach = 1 + g.Nx + g.Nx * g.Ny;
+  const int nj = dj / 3, e = dj - 3 * nj;
   double v = 0.0;
-  if (ox >= -1 && ox <= 1 && oy >= -1 && oy <= 1 && oz >= -1 && oz <= 1) {
-    const int o = (ox + 1) + 3 * (oy + 1) + 9 * (oz + 1);
-    v = S[(size_t)(o * 9 + 3 * d + e) * g.Nn + ni];
+  if (nj - ni <= reach && ni - nj <= reach) {
+    const int ix = ni % g.Nx, iy = (ni / g.Nx) % g.Ny, iz = ni / (g.Nx * g.Ny);
+    const int jx = nj % g.Nx, jy = (nj / g.Nx) % g.Ny, jz = nj / (g.Nx * g.Ny);
+    const int ox = jx - ix, oy = jy - iy, oz = jz - iz;
+    if (ox >= -1 && ox <= 1 && oy >= -1 && oy <= 1 && oz >= -1 && oz <= 1) {
+      const int o = (ox + 1) + 3 * (oy + 1) + 9 * (oz + 1);
+      v = S[(size_t)(o * 9 + 3 * d + e) * g.Nn + ni];
+    }
   }
-  A[t] = v;
+  A[(size_t)i * ld + j] = v;
 }
 
-void launch_dense_assemble(const Grid& g, const double* S, const int* free_idx, int nf, double* A,
+void launch_dense_assemble(const Grid& g, const double* S, const int* free_idx, int nf, int ld, double* A,
                            hipStream_t s) {
-  k_dense_assemble<<<div_up((long)nf * nf, 256), 256, 0, s>>>(g, S, free_idx, nf, A);
+  k_dense_assemble<<<dim3(nf, div_up(nf, 256)), 256, 0, s>>>(g, S, free_idx, nf, ld, A);
 }
 
-__global__ void k_dense_diag_sum(const double* __restrict__ A, int nf, RedWs ws, double* out) {
+__global__ void k_dense_diag_sum(const double* __restrict__ A, int nf, int ld, RedWs ws, double* out) {
   double s = 0.0;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nf; i += gridDim.x * blockDim.x)
-    s += A[(size_t)i * nf + i];
+    s += A[(size_t)i * ld + i];
   const double v[1] = {s};
   grid_sum<1>(v, ws);
 }
 
-void launch_dense_diag_sum(const double* A, int nf, RedWs ws, double* out, hipStream_t s) {
-  k_dense_diag_sum<<<1, 256, 0, s>>>(A, nf, ws, out);
+void launch_dense_diag_sum(const double* A, int nf, int ld, RedWs ws, double* out, hipStream_t s) {
+  k_dense_diag_sum<<<1, 256, 0, s>>>(A, nf, ld, ws, out);
   launch_finalize(ws, 1, 1, out, s);
 }
 
 // eps = max(mean diag * 1e-8, 1e-14) added to the diagonal (Sec. 4.1).
-__global__ void k_dense_add_diag(double* __restrict__ A, int nf, const double* __restrict__ dsum,
+__global__ void k_dense_add_diag(double* __restrict__ A, int nf, int ld, const double* __restrict__ dsum,
                                  double* __restrict__ eps_out) {
   const double eps = fmax(*dsum / nf * 1e-8, 1e-14);
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i == 0 && eps_out) *eps_out = eps;
-  if (i < nf) A[(size_t)i * nf + i] += eps;
+  if (i < nf) A[(size_t)i * ld + i] += eps;
 }
 
-void launch_dense_add_diag(double* A, int nf, const double* mean_diag_sum, hipStream_t s,
+void launch_dense_add_diag(double* A, int nf, int ld, const double* mean_diag_sum, hipStream_t s,
                            double* eps_out) {
-  k_dense_add_diag<<<div_up(nf, 256), 256, 0, s>>>(A, nf, mean_diag_sum, eps_out);
+  k_dense_add_diag<<<div_up(nf, 256), 256, 0, s>>>(A, nf, ld, mean_diag_sum, eps_out);
 }
 
 // --- blocked Gauss-Jordan sweep --------------------------------------------
 // For pivot block K: Q = A_KK^-1; A_KJ <- Q A_KJ (J != K);
 // A_IJ <- A_IJ - A_IK(old) A_KJ(new) (I, J != K); A_IK <- -A_IK(old) Q.
 // After all blocks A holds its inverse.
+//
+// The pivots form one serial chain, so a pivot block's own update and its
+// inversion run in the first block of the launch that updates the rest of
+// the matrix, and two pivot blocks share one pass over it:
+//   panel(K)        : the row and the column of block K, and both rewritten
+//                     in matrix-core operand order (R = A_KJ, C = A_IK old)
+//   update, K alone : row and column K + 1 only; inverts pivot K + 1
+//   panel(K + 1)
+//   update, both    : A_IJ - C_K R_K - C_{K+1} R_{K+1} for everything else,
+//                     one read and one write of A; inverts pivot K + 2
+// Every element sees the same operations in the same order as with one full
+// update per block, so the split changes no bit of the result.
+// Measured per two pivot blocks at n = 3630: panels 10 + 11 us, cross 25 us (the
+// pivot's chain), the pass over A 85 us (2 x 46 us of matrix-core work or 43 us
+// of copy rate; 841 tiles leave a quarter-full last round); whole inverse 7.5
+// -> 3.9 ms. One launch each for column copy, pivot, row panel and update of a
+// single block took 131 us per block. n = 1944: 2.7 -> 1.15 ms, n = 1344: 1.67 ->
+// 0.75 ms, both bound by the chain of pivots (25 us each with its tile).
+//
+// FP64 matrix-core operand layouts (v_mfma_f64_16x16x4_f64): A lane l = (row
+// l % 16, k l / 16), B lane l = (k l / 16, column l % 16), result register i
+// of lane l = (row 4 i + l / 16, column l % 16).  The operands of 16 rows (or
+// columns) for two k-steps of 4 are 64 consecutive pairs of doubles, in lane
+// order, so they are one coalesced 16-byte load and the update needs no LDS
+// (8-byte loads kept the address units busier than the matrix cores): element
+// (16-row group g, k-step t, lane l) of a panel is at
+// ((8 g + t / 2) * 64 + l) * 2 + t % 2.
+typedef double f64x4_gj __attribute__((ext_vector_type(4)));
+constexpr int kLdP = 68;       // LDS pitch (doubles): 8 rows x 4 k of a wave in distinct banks
+constexpr int kUpdThreads = 1024;
 
-__global__ void k_gj_copy_col(const double* __restrict__ A, int n, int k0, int nb,
-                              double* __restrict__ C) {
-  const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (size_t)n * kNB) return;
-  const int i = (int)(t / kNB), c = (int)(t % kNB);
-  C[t] = c < nb ? A[(size_t)i * n + k0 + c] : 0.0;
-}
-
-// Inverse of the nb x nb pivot block by in-place Gauss-Jordan (SPD: no
-// pivoting), four waves: lane r of wave w keeps columns 16w .. 16w + 15 of
-// row r in registers.  The 16 steps whose pivot column a wave owns are
-// unrolled, so every register index is a compile-time constant.  At step p
-// the owner wave publishes column p and lane p of every wave publishes its
-// part of row p in LDS; after a block barrier every lane updates its 16
-// entries:
-//   r == p : a_pc <- a_pc / a_pp (c != p),  a_pp <- 1 / a_pp
-//   r != p : a_rc <- a_rc - (a_rp / a_pp) a_pc (c != p),  a_rp <- -a_rp / a_pp
-// (the same operations, in the same precision, as one lane per row would
-// do).  The block is zero-padded to 64 x 64 with a unit diagonal, so padded
-// rows and columns stay decoupled.
-__global__ __launch_bounds__(256) void k_gj_pivot(double* __restrict__ A, int n, int k0, int nb,
-                                                  double* __restrict__ Q, int* __restrict__ flag) {
-  __shared__ double colp[2][kNB];   // column p (double-buffered over steps)
-  __shared__ double rowp[2][kNB];   // row p
-  const int r = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int c0 = 16 * w;
-  double v[16];
+// The row panel (blocks 0 .. nb - 1, J) and the column panel (blocks nb ..
+// 2 nb - 1, I) of pivot block K.  Q: its inverse, 64 x 64, zero past nbw
+// (the block's width).  CF of row block K and RF of column block K are zeros,
+// so an update with them leaves row and column K as they are.
+__global__ __launch_bounds__(256) void k_gj_panel(double* __restrict__ A, int n, int ld, int nb, int K,
+                                                  const double* __restrict__ Q,
+                                                  double* __restrict__ CF,
+                                                  double* __restrict__ RF) {
+  __shared__ double Qs[kNB][kLdP];
+  __shared__ double Vs[kNB][kLdP];
+  const bool row = (int)blockIdx.x < nb;
+  const int B = row ? blockIdx.x : blockIdx.x - nb;
+  const int k0 = K * kNB, b0 = B * kNB, nbw = min(kNB, n - k0);
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  double* F = (row ? RF : CF) + (size_t)B * kNB * kNB;
+  if (B == K) {
 #pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const int col = c0 + c;
-    v[c] = (r < nb && col < nb) ? A[(size_t)(k0 + r) * n + k0 + col] : (r == col ? 1.0 : 0.0);
-  }
-  bool bad = false;
-  for (int pw = 0; pw < 4; ++pw) {
-#pragma unroll
-    for (int sp = 0; sp < 16; ++sp) {
-      const int p = 16 * pw + sp, buf = sp & 1;
-      if (w == pw) colp[buf][r] = v[sp];
-      if (r == p) {
-#pragma unroll
-        for (int c = 0; c < 16; ++c) rowp[buf][c0 + c] = v[c];
-      }
-      __syncthreads();
-      const double pv = colp[buf][p];
-      bad |= !(pv > 0.0);
-      const double inv = 1.0 / pv;
-      const bool me = r == p;
-      const double g = colp[buf][r] * inv;            // a_rp / a_pp
-#pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        const double rc = rowp[buf][c0 + c];
-        const double upd = me ? rc * inv : __builtin_fma(-g, rc, v[c]);
-        v[c] = (w == pw && c == sp) ? (me ? inv : -g) : upd;
-      }
+    for (int u = 0; u < 16; ++u) {
+      const int e = tid + 256 * u, r = e / kNB, c = e % kNB;
+      F[e] = 0.0;
+      if (row && r < nbw && c < nbw) A[(size_t)(k0 + r) * ld + k0 + c] = Q[e];
     }
+    return;
   }
-  if (bad && threadIdx.x == 0) *flag = 1;
+  double2* F2 = (double2*)F + 512 * w + lane;      // the wave's group of 16 rows or columns
+  const int r0 = row ? k0 : b0, c0 = row ? b0 : k0;
+  double qv[16], vv[16];
 #pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const int col = c0 + c;
-    const bool in = r < nb && col < nb;
-    const double x = in ? v[c] : 0.0;
-    Q[r * kNB + col] = x;
-    if (in) A[(size_t)(k0 + r) * n + k0 + col] = x;
+  for (int u = 0; u < 16; ++u) {
+    const int e = tid + 256 * u, r = e / kNB, c = e % kNB;
+    qv[u] = Q[e];
+    vv[u] = A[(size_t)min(r0 + r, n - 1) * ld + min(c0 + c, n - 1)];
   }
-}
-
-// A_KJ <- Q A_KJ for every column j outside the panel (Q staged in LDS).
-__global__ __launch_bounds__(256) void k_gj_rowpanel(double* __restrict__ A, int n, int k0, int nb,
-                                                     const double* __restrict__ Q) {
-  // 64 columns per block: Q and the block's 64 x 64 piece of the panel rows
-  // are staged in LDS (Q zero-padded past nb), then each thread forms a
-  // 4 x 4 register tile (rows tr + 16 q, columns tc + 16 w) over the 64
-  // products in order
-  __shared__ double Qs[kNB][kNB + 1];
-  __shared__ double Vs[kNB][kNB + 1];
-  const int j0 = blockIdx.x * 64;
-  for (int e = threadIdx.x; e < kNB * kNB; e += 256) {
-    const int r = e / kNB, c = e % kNB, j = j0 + c;
-    Qs[r][c] = (r < nb && c < nb) ? Q[r * kNB + c] : 0.0;
-    Vs[r][c] = (r < nb && j < n) ? A[(size_t)(k0 + r) * n + j] : 0.0;
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int e = tid + 256 * u, r = e / kNB, c = e % kNB;
+    if (row) Qs[c][r] = qv[u];                     // transposed: a thread's rows are adjacent
+    else Qs[r][c] = -qv[u];
+    Vs[r][c] = r0 + r < n && c0 + c < n ? vv[u] : 0.0;
   }
   __syncthreads();
-  const int tr = threadIdx.x / 16, tc = threadIdx.x % 16;
-  double acc[4][4] = {};
-  for (int t = 0; t < kNB; ++t) {
-    double a[4], b[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      a[q] = Qs[tr + 16 * q][t];
-      b[q] = Vs[t][tc + 16 * q];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) acc[q][w] += a[q] * b[w];
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int r = tr + 16 * q;
-    if (r >= nb) continue;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int j = j0 + tc + 16 * w;
-      if (j < n && !(j >= k0 && j < k0 + nb)) A[(size_t)(k0 + r) * n + j] = acc[q][w];
-    }
-  }
-}
-
-// Rank-nb update of all rows outside the panel: A_IJ -= C_I R_J with R_J =
-// A_KJ (new) for columns outside the panel and R_J = -Q for the panel's own
-// columns, which receive -C_I Q (stored, not subtracted).  A 128 x 128
-// output tile per 256-thread block on the FP64 matrix cores
-// (v_mfma_f64_16x16x4_f64): each wave owns a 64 x 64 quarter as 4 x 4 MFMA
-// tiles, K streamed through LDS in chunks of 16 (4 k-steps of 4).  Operand
-// layouts: A lane l = (row l % 16, k l / 16), B lane l = (k l / 16, column
-// l % 16); result register i of lane l = (row 4 i + l / 16, column l % 16).
-constexpr int kUpdTile = 128, kUpdK = 16;
-typedef double f64x4_gj __attribute__((ext_vector_type(4)));
-
-__global__ __launch_bounds__(256) void k_gj_update(double* __restrict__ A, int n, int k0, int nb,
-                                                   const double* __restrict__ C,
-                                                   const double* __restrict__ Q) {
-  __shared__ double Cs[kUpdTile][kUpdK + 1];
-  __shared__ double Rs[kUpdK][kUpdTile + 1];
-  const int i0 = blockIdx.y * kUpdTile, j0 = blockIdx.x * kUpdTile;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int wr = (wv >> 1) * 64, wc = (wv & 1) * 64;
-  const int lr = lane & 15, lk = lane >> 4;
-  f64x4_gj acc[4][4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int w = 0; w < 4; ++w) acc[q][w] = f64x4_gj{0.0, 0.0, 0.0, 0.0};
-  for (int t0 = 0; t0 < nb; t0 += kUpdK) {
-    // staging: every load at a clamped, valid address, all issued before
-    // the first LDS store, the value selected afterwards
-    constexpr int kPer = kUpdTile * kUpdK / 256;
-    double cv[kPer], av[kPer], qv[kPer];
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int e = threadIdx.x + 256 * u;
-      const int r = e / kUpdK, c = e % kUpdK;
-      cv[u] = C[(size_t)min(i0 + r, n - 1) * kNB + min(t0 + c, nb - 1)];
-      const int rr = e / kUpdTile, cc = e % kUpdTile;
-      const int t = min(t0 + rr, nb - 1), j = min(j0 + cc, n - 1);
-      av[u] = A[(size_t)(k0 + t) * n + j];
-      qv[u] = Q[t * kNB + min(max(j - k0, 0), nb - 1)];
-    }
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int e = threadIdx.x + 256 * u;
-      const int r = e / kUpdK, c = e % kUpdK;
-      Cs[r][c] = (i0 + r < n && t0 + c < nb) ? cv[u] : 0.0;
-      const int rr = e / kUpdTile, cc = e % kUpdTile;
-      const int t = t0 + rr, j = j0 + cc;
-      double v = 0.0;
-      if (t < nb && j < n) v = (j >= k0 && j < k0 + nb) ? -qv[u] : av[u];   // -C Q | A_KJ (new)
-      Rs[rr][cc] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < kUpdK; kk += 4) {
+  if (row) {
+    // a 4 x 4 register tile per thread (rows 2 tr + {0, 1, 32, 33}, columns
+    // 2 tc + {0, 1, 32, 33}: 16-byte LDS reads), the 64 products in order
+    const int tr = tid / 16, tc = tid % 16;
+    double acc[4][4] = {};
+#pragma unroll 4
+    for (int t = 0; t < kNB; ++t) {
       double a[4], b[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        a[q] = Cs[wr + 16 * q + lr][kk + lk];
-        b[q] = Rs[kk + lk][wc + 16 * q + lr];
+      for (int h = 0; h < 2; ++h) {
+        const double2 x = *(const double2*)&Qs[t][2 * tr + 32 * h];
+        const double2 y = *(const double2*)&Vs[t][2 * tc + 32 * h];
+        a[2 * h] = x.x; a[2 * h + 1] = x.y;
+        b[2 * h] = y.x; b[2 * h + 1] = y.y;
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int w = 0; w < 4; ++w)
-          acc[q][w] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[w], acc[q][w], 0, 0, 0);
+        for (int p = 0; p < 4; ++p) acc[q][p] = __builtin_fma(a[q], b[p], acc[q][p]);
     }
     __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        *(double2*)&Vs[2 * tr + 32 * (q / 2) + q % 2][2 * tc + 32 * h] =
+            make_double2(acc[q][2 * h], acc[q][2 * h + 1]);
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      F2[64 * t] = make_double2(Vs[8 * t + lk][16 * w + lr], Vs[8 * t + 4 + lk][16 * w + lr]);
+  } else {
+    f64x4_gj acc[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q] = f64x4_gj{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < 16; t += 2) {
+      const double2 a = make_double2(Vs[16 * w + lr][4 * t + lk], Vs[16 * w + lr][4 * t + 4 + lk]);
+      F2[32 * t] = a;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, Qs[4 * t + lk][16 * q + lr], acc[q], 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, Qs[4 * t + 4 + lk][16 * q + lr], acc[q], 0, 0, 0);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) Vs[16 * w + 4 * i + lk][16 * q + lr] = acc[q][i];
+    __syncthreads();
   }
-  // read-modify-write of the tile: all old values are loaded first (at
-  // clamped, valid addresses), then the stores are masked
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    double old[4][4];
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {
-      const int i = min(i0 + wr + 16 * q + 4 * ii + lk, n - 1);
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const int j = min(j0 + wc + 16 * w + lr, n - 1);
-        old[ii][w] = A[(size_t)i * n + j];
-      }
-    }
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {
-      const int i = i0 + wr + 16 * q + 4 * ii + lk;
-      const bool row_ok = i < n && !(i >= k0 && i < k0 + nb);
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const int j = j0 + wc + 16 * w + lr;
-        if (!row_ok || j >= n) continue;
-        const bool panel_col = j >= k0 && j < k0 + nb;
-        A[(size_t)i * n + j] = panel_col ? acc[q][w][ii] : old[ii][w] - acc[q][w][ii];
-      }
-    }
+  for (int u = 0; u < 16; ++u) {
+    const int e = tid + 256 * u, r = e / kNB, c = e % kNB;
+    if (r0 + r < n && c0 + c < n) A[(size_t)(r0 + r) * ld + c0 + c] = Vs[r][c];
   }
 }
 
-int dense_spd_inverse(double* A, int n, double* scratch, int* d_flag, hipStream_t s) {
-  double* C = scratch;                       // n * kNB
-  double* Q = scratch + (size_t)n * kNB;     // kNB * kNB
-  for (int k0 = 0; k0 < n; k0 += kNB) {
-    const int nb = (n - k0) < kNB ? (n - k0) : kNB;
-    k_gj_copy_col<<<div_up((long)n * kNB, 256), 256, 0, s>>>(A, n, k0, nb, C);
-    k_gj_pivot<<<1, 256, 0, s>>>(A, n, k0, nb, Q, d_flag);
-    k_gj_rowpanel<<<div_up(n, 64), 256, 0, s>>>(A, n, k0, nb, Q);
-    dim3 grid(div_up(n, kUpdTile), div_up(n, kUpdTile));
-    k_gj_update<<<grid, 256, 0, s>>>(A, n, k0, nb, C, Q);
+__device__ inline double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+struct PivotLds {
+  double P[kNB][kNB + 1];
+  double g[2][4][kNB];         // 1 / a_pp in lane p, -a_rp / a_pp elsewhere, by parity
+};
+
+// Inverse of the 64 x 64 block S.P by in-place Gauss-Jordan (SPD: no
+// pivoting), sixteen waves: lane r of wave w keeps columns 4 w .. 4 w + 3 of
+// row r.  Pivot p:
+//   r == p : a_pc <- a_pc / a_pp (c != p),  a_pp <- 1 / a_pp
+//   r != p : a_rc <- a_rc - (a_rp / a_pp) a_pc (c != p),  a_rp <- -a_rp / a_pp
+// The wave that owns four pivot columns runs their four steps alone (row p
+// reaches the lanes through scalar registers), publishes the multipliers,
+// and after one barrier the other waves apply the four steps to their own
+// columns in the same order; the next owner goes on with its own steps while
+// the others still apply.  Bound: the owners' chain, a division and the
+// columns of one wave per pivot, which is why each wave has only four.
+// Writes Q, zero past nbw.
+__device__ inline void gj_pivot(PivotLds& S, int nbw, double* __restrict__ Q, int* __restrict__ flag) {
+  const int r = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  __syncthreads();
+  double v[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) v[c] = S.P[r][4 * w + c];
+  bool bad = false;
+  for (int b = 0; b < 16; ++b) {
+    const int buf = b & 1;
+    if (w == b) {
+#pragma unroll
+      for (int sp = 0; sp < 4; ++sp) {
+        const int p = 4 * b + sp;
+        const double pv = lane_value(v[sp], p);
+        bad |= !(pv > 0.0);
+        const double inv = 1.0 / pv;
+        const bool me = r == p;
+        const double g = v[sp] * inv;            // a_rp / a_pp
+        const double f = me ? inv : -g;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          if (c == sp) continue;
+          v[c] = __builtin_fma(f, lane_value(v[c], p), me ? 0.0 : v[c]);
+        }
+        v[sp] = f;
+        S.g[buf][sp][r] = f;
+      }
+    }
+    __syncthreads();
+    if (w != b) {
+#pragma unroll
+      for (int sp = 0; sp < 4; ++sp) {
+        const int p = 4 * b + sp;
+        const bool me = r == p;
+        const double f = S.g[buf][sp][r];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          v[c] = __builtin_fma(f, lane_value(v[c], p), me ? 0.0 : v[c]);
+      }
+    }
+  }
+  if (bad && r == 0) *flag = 1;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) S.P[r][4 * w + c] = v[c];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int e = threadIdx.x + kUpdThreads * u, a = e / kNB, c = e % kNB;
+    Q[e] = a < nbw && c < nbw ? S.P[a][c] : 0.0;
+  }
+}
+
+// acc[NR][NC] = C R over one panel for 16 NR rows and 16 NC columns, the k
+// steps in order.
+template <int NR, int NC>
+__device__ inline void gj_product(const double2* __restrict__ c, const double2* __restrict__ r,
+                                  f64x4_gj (&acc)[NR][NC]) {
+#pragma unroll
+  for (int q = 0; q < NR; ++q)
+#pragma unroll
+    for (int p = 0; p < NC; ++p) acc[q][p] = f64x4_gj{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int t = 0; t < 8; ++t) {
+    double2 a[NR], b[NC];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) a[q] = c[q * 512 + t * 64];
+#pragma unroll
+    for (int p = 0; p < NC; ++p) b[p] = r[p * 512 + t * 64];
+#pragma unroll
+    for (int q = 0; q < NR; ++q)
+#pragma unroll
+      for (int p = 0; p < NC; ++p)
+        acc[q][p] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q].x, b[p].x, acc[q][p], 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < NR; ++q)
+#pragma unroll
+      for (int p = 0; p < NC; ++p)
+        acc[q][p] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q].y, b[p].y, acc[q][p], 0, 0, 0);
+  }
+}
+
+// A wave's tile: rows i0 .., columns j0 .. : old - C_0 R_0 (- C_1 R_1).
+template <int NR, int NC, class Out>
+__device__ inline void gj_tile(const double* __restrict__ A, int n, int ld, int i0, int j0, int panels,
+                               const double* __restrict__ CF, const double* __restrict__ RF,
+                               size_t panel_stride, Out&& out) {
+  const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+  double v[NR][NC][4];
+#pragma unroll
+  for (int q = 0; q < NR; ++q)
+#pragma unroll
+    for (int p = 0; p < NC; ++p)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int a = i0 + 16 * q + 4 * i + lk, b = j0 + 16 * p + lr;
+        v[q][p][i] = A[(size_t)min(a, n - 1) * ld + min(b, n - 1)];
+      }
+  for (int m = 0; m < panels; ++m) {
+    f64x4_gj acc[NR][NC];
+    gj_product<NR, NC>((const double2*)(CF + m * panel_stride + (size_t)(i0 >> 4) * 1024) + lane,
+                       (const double2*)(RF + m * panel_stride + (size_t)(j0 >> 4) * 1024) + lane, acc);
+#pragma unroll
+    for (int q = 0; q < NR; ++q)
+#pragma unroll
+      for (int p = 0; p < NC; ++p)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[q][p][i] -= acc[q][p][i];
+  }
+#pragma unroll
+  for (int q = 0; q < NR; ++q)
+#pragma unroll
+    for (int p = 0; p < NC; ++p)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) out(i0 + 16 * q + 4 * i + lk, j0 + 16 * p + lr, v[q][p][i]);
+}
+
+// Update by the last `panels` panels (K, or K - 1 and K), a 128 x 128 tile per
+// block and 32 x 32 per wave.  cross: only row and column K + 1, blocks 1 ..
+// nj the row's tiles and nj + 1 .. 2 nj the column's; otherwise every tile
+// outside row and column K.  Block 0 forms and inverts pivot block K + 1 (left out of the tiles).
+__global__ __launch_bounds__(kUpdThreads) void k_gj_update(double* __restrict__ A, int n, int ld, int nb,
+                                                           int K, int panels, int cross,
+                                                           const double* __restrict__ CF,
+                                                           const double* __restrict__ RF,
+                                                           size_t panel_stride,
+                                                           double* __restrict__ Q,
+                                                           int* __restrict__ flag) {
+  __shared__ PivotLds S;
+  const int w = threadIdx.x >> 6;
+  if (blockIdx.x == 0) {
+    if (K + 1 >= nb) return;
+    const int k1 = (K + 1) * kNB;
+    gj_tile<1, 1>(A, n, ld, k1 + 16 * (w >> 2), k1 + 16 * (w & 3), panels, CF, RF, panel_stride,
+                  [&](int a, int b, double v) {
+                    S.P[a - k1][b - k1] = a < n && b < n ? v : (a == b ? 1.0 : 0.0);
+                  });
+    gj_pivot(S, min(kNB, n - k1), Q, flag);
+    return;
+  }
+  const int nj = (nb + 1) / 2, t = blockIdx.x - 1, mid = (K + 1) / 2;
+  int Ip, Jp;
+  if (!cross) {
+    // each XCD's share is about one band of four tile rows, column by column:
+    // its L2 keeps the band's C and streams R (all of both is 7.4 MB at n =
+    // 3630, more than the 4 MB an XCD has)
+    const int u = xcd_block(t, nj * nj), band = u / (4 * nj), in = u - band * 4 * nj;
+    const int rows = min(4, nj - 4 * band);
+    Ip = 4 * band + in % rows;
+    Jp = in / rows;
+  } else {
+    Ip = t < nj ? mid : t - nj;
+    Jp = t < nj ? t : mid;
+    if (t >= nj && Ip == mid) return;              // among the row's tiles
+  }
+  const int i0 = 128 * Ip + 32 * (w >> 2), j0 = 128 * Jp + 32 * (w & 3);
+  const int I = i0 / kNB, J = j0 / kNB;
+  if (I >= nb || J >= nb || I == K || J == K || (I == K + 1 && J == K + 1)) return;
+  if (cross && I != K + 1 && J != K + 1) return;
+  gj_tile<2, 2>(A, n, ld, i0, j0, panels, CF, RF, panel_stride,
+                [&](int a, int b, double v) {
+                  if (a < n && b < n) A[(size_t)a * ld + b] = v;
+                });
+}
+
+size_t dense_inverse_scratch(int n) {
+  return (4 * (size_t)div_up(n, kNB) + 1) * kNB * kNB;
+}
+
+int dense_spd_inverse(double* A, int n, int ld, double* scratch, int* d_flag, hipStream_t s) {
+  const int nb = div_up(n, kNB), nj = (nb + 1) / 2;
+  const size_t ps = 2 * (size_t)nb * kNB * kNB;      // two panels, C and R each
+  double* CF = scratch;
+  double* RF = scratch + (size_t)nb * kNB * kNB;
+  double* Q = scratch + 2 * ps;
+  auto panel = [&](int K, int m) {
+    k_gj_panel<<<2 * nb, 256, 0, s>>>(A, n, ld, nb, K, Q, CF + m * ps, RF + m * ps);
+  };
+  auto update = [&](int K, int panels, int cross, int blocks) {
+    k_gj_update<<<1 + blocks, kUpdThreads, 0, s>>>(A, n, ld, nb, K, panels, cross, CF, RF, ps, Q, d_flag);
+  };
+  update(-1, 0, 0, 0);                               // pivot block 0
+  for (int K = 0; K < nb; K += 2) {
+    panel(K, 0);
+    if (K + 1 < nb) {
+      update(K, 1, 1, 2 * nj);
+      panel(K + 1, 1);
+      update(K + 1, 2, 0, nj * nj);
+    } else if (nb > 1) {
+      update(K, 1, 0, nj * nj);
+    }
   }
   return 0;
 }
@@ -318,7 +452,7 @@ __device__ inline void tile_ij(int t, int nb, int& I, int& J) {
   J = i + (t - tile_index(i, i, nb));
 }
 
-__global__ __launch_bounds__(256) void k_dense_pack(const double* __restrict__ A, int nf, int nb,
+__global__ __launch_bounds__(256) void k_dense_pack(const double* __restrict__ A, int nf, int ld, int nb,
                                                    double* __restrict__ P) {
   int I, J;
   tile_ij(blockIdx.x, nb, I, J);
@@ -326,7 +460,7 @@ __global__ __launch_bounds__(256) void k_dense_pack(const double* __restrict__ A
   for (int e = threadIdx.x; e < kTile * kTile; e += 256) {
     const int a = e / kTile, b = e % kTile;
     const int i = I * kTile + a, j = J * kTile + b;
-    T[e] = (i < nf && j < nf) ? A[(size_t)i * nf + j] : 0.0;
+    T[e] = (i < nf && j < nf) ? A[(size_t)i * ld + j] : 0.0;
   }
 }
 
@@ -403,9 +537,9 @@ __global__ __launch_bounds__(256) void k_dense_symv_sum(int nf, int nb,
   }
 }
 
-void launch_dense_pack(const double* A, int nf, double* P, hipStream_t s) {
+void launch_dense_pack(const double* A, int nf, int ld, double* P, hipStream_t s) {
   if (nf <= 0) return;
-  k_dense_pack<<<sym_tiles(nf), 256, 0, s>>>(A, nf, div_up(nf, kTile), P);
+  k_dense_pack<<<sym_tiles(nf), 256, 0, s>>>(A, nf, ld, div_up(nf, kTile), P);
 }
 
 void launch_dense_symv(const double* P, const int* free_idx, int nf, const double* r,

@@ -409,11 +409,12 @@ int assemble_operators(sgmg_hierarchy* h, const double* rho_or_E, hipStream_t s)
   Level& C = h->lev[h->L - 1];
   const int nf = h->nL;
   if (nf > 0 && !h->coarse_iter) {
-    launch_dense_assemble(C.g, C.S64, h->free_idx, nf, h->Ainv, s);
-    launch_dense_diag_sum(h->Ainv, nf, h->ws, h->sc + SC_DSUM, s);
-    launch_dense_add_diag(h->Ainv, nf, h->sc + SC_DSUM, s, h->sc + SC_EPS);
+    const int ld = dense_ld(nf);
+    launch_dense_assemble(C.g, C.S64, h->free_idx, nf, ld, h->Ainv, s);
+    launch_dense_diag_sum(h->Ainv, nf, ld, h->ws, h->sc + SC_DSUM, s);
+    launch_dense_add_diag(h->Ainv, nf, ld, h->sc + SC_DSUM, s, h->sc + SC_EPS);
     SGMG_HIP(hipMemsetAsync(h->d_flag, 0, sizeof(int), s));
-    dense_spd_inverse(h->Ainv, nf, h->gj_scratch, h->d_flag, s);
+    dense_spd_inverse(h->Ainv, nf, ld, h->gj_scratch, h->d_flag, s);
     TRY(check_launch());
     int flag = 0;
     SGMG_HIP(hipMemcpyAsync(&flag, h->d_flag, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -424,7 +425,7 @@ int assemble_operators(sgmg_hierarchy* h, const double* rho_or_E, hipStream_t s)
       set_error("coarsest factorisation met a non-positive pivot");
       return SGMG_EFACTOR;
     }
-    launch_dense_pack(h->Ainv, nf, h->Apack, s);
+    launch_dense_pack(h->Ainv, nf, ld, h->Apack, s);
     TRY(check_launch());
   }
   return 0;
@@ -878,8 +879,8 @@ int sgmg_setup_hierarchy(const sgmg_options* opts, const double* rho_or_E, const
     h->nL = (int)idx.size();
     const size_t nd = h->coarse_iter ? 1 : (size_t)std::max(h->nL, 1);  // dense-solve sizes
     if ((rc = dalloc_t(h, &h->free_idx, std::max<size_t>(idx.size(), 1))) ||
-        (rc = dalloc_t(h, &h->Ainv, nd * nd)) ||
-        (rc = dalloc_t(h, &h->gj_scratch, nd * 64 + 64 * 64)))
+        (rc = dalloc_t(h, &h->Ainv, nd * dense_ld((int)nd))) ||
+        (rc = dalloc_t(h, &h->gj_scratch, dense_inverse_scratch((int)nd))))
       return fail(rc);
     const size_t nt = h->coarse_iter ? 1 : (size_t)std::max(sym_tiles(h->nL), 1);
     if ((rc = dalloc_t(h, &h->Apack, nt * 64 * 64)) ||
@@ -2124,6 +2125,7 @@ BSys make_bsys(const sgmg_hierarchy* h) {
   S.nL = h->nL;
   S.free_idx = h->free_idx;
   S.Ainv = h->Ainv;
+  S.ld_inv = dense_ld(h->nL);
   return S;
 }
 

@@ -1,0 +1,44 @@
+"""Coarsest inverse (blocked Gauss-Jordan, two pivot blocks per pass) at sizes
+around its 64-wide pivot blocks: a two-level V-cycle solves the coarsest level exactly with it, so
+the cycle is compared with the oracle's (whose coarsest solve is a Cholesky
+factorisation of the same regularised matrix)."""
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+# coarsest free DOFs: 54 (one partial block), 81 (a pair), 192 (three whole
+# blocks: a pair and a single), 375 (an odd remainder), 540 (odd axes), 1920
+# (thirty blocks)
+MESHES = [(4, 4, 4), (6, 4, 4), (8, 6, 6), (10, 8, 8), (13, 9, 11), (20, 14, 14)]
+
+
+@pytest.mark.parametrize("dims", MESHES)
+def test_cycle_with_the_inverse_matches_the_oracle(dims):
+    import torch
+    from oracle import mesh, multigrid
+    from paper_2604_26441_amd import simpgmg
+    rho = workloads.grf_rho(dims, 3, corr_len=2.0)
+    fixed = workloads.cantilever_fixed(dims)
+    h = simpgmg.setup_hierarchy(simpgmg.default_options(*dims, n_levels=2, fine_prec="f64"),
+                                torch.tensor(rho, device="cuda:0"))
+    oh = multigrid.build(dims, mesh.simp_modulus(rho, 3), fixed.astype(bool), multigrid.Options(n_levels=2))
+    r = workloads.random_vector(h.n_dof, 5, fixed)
+    z = torch.zeros(h.n_dof, dtype=torch.float64, device="cuda:0")
+    simpgmg.vcycle(h, torch.tensor(r, device="cuda:0"), z)
+    want = multigrid.vcycle(oh, r)
+    # both coarse solves lose up to cond(K_L) (<= 1e6 here) units of FP64
+    # rounding (1.1e-16)
+    assert np.linalg.norm(z.cpu().numpy() - want) <= 2e-10 * np.linalg.norm(want)
+
+
+def test_non_positive_pivot_is_reported():
+    import torch
+    from paper_2604_26441_amd import simpgmg
+    dims = (8, 6, 6)
+    E = torch.full((8 * 6 * 6,), -1.0, dtype=torch.float64, device="cuda:0")
+    with pytest.raises(simpgmg.SimpGmgError, match="-4"):
+        simpgmg.setup_hierarchy(simpgmg.default_options(*dims, n_levels=2, fine_prec="f64",
+                                                        input_is_modulus=1), E)
