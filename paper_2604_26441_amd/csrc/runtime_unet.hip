@@ -13,10 +13,11 @@ using namespace sgmg;
 
 namespace {
 
-constexpr int kNL = 8;
+constexpr int kNL = ParamTable::kLayers;
 const int kCi[kNL] = {5, 16, 32, 64, 128, 64, 32, 16};
 const int kCo[kNL] = {16, 32, 64, 128, 64, 32, 16, 3};
 const int kK[kNL] = {3, 3, 3, 3, 3, 3, 3, 1};
+const int kUp[kNL] = {0, 0, 0, 0, 1, 1, 1, 0};   // the decoder reads upsampled inputs
 
 int pad16(int c) { return (c + 15) / 16 * 16; }
 
@@ -42,6 +43,8 @@ struct sgmg_unet {
   double* sums = nullptr;
   double* partials = nullptr;
   double h_sums[2];
+  float* flat = nullptr;      // parameters or gradients in the order of the C ABI,
+  float* h_flat = nullptr;    // and their pinned copy (allocated on first use)
   // energy-score workspace for eN samples of a mesh with eNn nodes
   int eN = 0, eNn = 0, enel = 0;
   std::vector<void*> emem;
@@ -163,38 +166,47 @@ void upload_layer(const ULayer& L, const std::vector<float>& w_dev_layout, const
 void pack_weights(sgmg_unet* u, hipStream_t s) {
   if (u->packed) return;
   for (int l = 0; l < kNL; ++l)
-    if (u->L[l].k == 3) launch_pack_conv3(u->L[l].wq, u->L[l].ci, u->L[l].co, u->L[l].wp, s);
+    if (u->L[l].k == 3)
+      launch_pack_conv3(u->L[l].wq, kUp[l], u->L[l].ci, u->L[l].co, u->L[l].wp, s);
   u->packed = true;
 }
 
-// up = 1: x holds the layer's input at half resolution and the convolution
-// reads its nearest-neighbour upsampling (3x3x3 layers only)
-void conv(sgmg_unet* u, int l, const float* x, int up, int N, int D, int H, int W, int relu,
-          float* rpre, const float* add, float* y, hipStream_t s) {
+// A decoder layer's x is its input at half resolution; the convolution reads
+// its nearest-neighbour upsampling, which is never stored.
+void conv(sgmg_unet* u, int l, const float* x, int N, int D, int H, int W, int relu, float* rpre,
+          const float* add, float* y, hipStream_t s) {
   const ULayer& L = u->L[l];
   if (L.k == 3)
-    launch_conv3_mfma(x, up, N, L.ci, L.co, D, H, W, L.wp, L.b, relu, rpre, add, y, s);
+    launch_conv3_mfma(x, kUp[l], N, L.ci, L.co, D, H, W, L.wp, L.b, relu, rpre, add, y, s);
   else
     launch_conv_fwd(L.k, x, N, L.ci, L.co, D, H, W, L.wq, L.b, relu, rpre, add, y, s);
 }
 
-void forward(sgmg_unet* u, int N, int D, int H, int W, const float* x, hipStream_t s) {
+// infer: the output goes to `out`, and what only the backward pass reads (the
+// decoder's values before the skips, the last layer's 16 channels) is not
+// stored; the head runs on those channels where they are computed.
+void forward(sgmg_unet* u, int N, int D, int H, int W, const float* x, hipStream_t s,
+             bool infer = false, float* out = nullptr) {
   const int D2 = D / 2, H2 = H / 2, W2 = W / 2, D3 = D / 4, H3 = H / 4, W3 = W / 4, D4 = D / 8,
             H4 = H / 8, W4 = W / 8;
   pack_weights(u, s);
-  conv(u, 0, x, 0, N, D, H, W, 1, nullptr, nullptr, u->r1, s);
+  conv(u, 0, x, N, D, H, W, 1, nullptr, nullptr, u->r1, s);
   launch_pool(u->r1, N * 16, D, H, W, u->p1, s);
-  conv(u, 1, u->p1, 0, N, D2, H2, W2, 1, nullptr, nullptr, u->r2, s);
+  conv(u, 1, u->p1, N, D2, H2, W2, 1, nullptr, nullptr, u->r2, s);
   launch_pool(u->r2, N * 32, D2, H2, W2, u->p2, s);
-  conv(u, 2, u->p2, 0, N, D3, H3, W3, 1, nullptr, nullptr, u->r3, s);
+  conv(u, 2, u->p2, N, D3, H3, W3, 1, nullptr, nullptr, u->r3, s);
   launch_pool(u->r3, N * 64, D3, H3, W3, u->p3, s);
-  conv(u, 3, u->p3, 0, N, D4, H4, W4, 1, nullptr, nullptr, u->r4, s);
-  // the decoder convolutions read the upsampled tensors (up b, up d3, up d2)
-  // through their input staging; those are never stored
-  conv(u, 4, u->r4, 1, N, D3, H3, W3, 1, u->r5, u->r3, u->d3, s);
-  conv(u, 5, u->d3, 1, N, D2, H2, W2, 1, u->r6, u->r2, u->d2, s);
-  conv(u, 6, u->d2, 1, N, D, H, W, 1, u->r7, u->r1, u->d1, s);
-  conv(u, 7, u->d1, 0, N, D, H, W, 0, nullptr, nullptr, u->y, s);
+  conv(u, 3, u->p3, N, D4, H4, W4, 1, nullptr, nullptr, u->r4, s);
+  conv(u, 4, u->r4, N, D3, H3, W3, 1, infer ? nullptr : u->r5, u->r3, u->d3, s);
+  conv(u, 5, u->d3, N, D2, H2, W2, 1, infer ? nullptr : u->r6, u->r2, u->d2, s);
+  if (infer) {
+    const ULayer& L = u->L[6];
+    launch_conv3_mfma(u->d2, 1, N, L.ci, L.co, D, H, W, L.wp, L.b, 1, nullptr, u->r1, nullptr, s,
+                      u->L[7].wq, u->L[7].b, out);
+    return;
+  }
+  conv(u, 6, u->d2, N, D, H, W, 1, u->r7, u->r1, u->d1, s);
+  conv(u, 7, u->d1, N, D, H, W, 0, nullptr, nullptr, u->y, s);
 }
 
 // dx = data gradient of layer l: the convolution with the channels swapped
@@ -204,7 +216,7 @@ void conv_dgrad(sgmg_unet* u, int l, const float* dy, int N, int D, int H, int W
   const ULayer& L = u->L[l];
   launch_weight_transpose(L.wq, L.ci, L.co, L.k, L.wt, s);
   if (L.k == 3) {
-    launch_pack_conv3(L.wt, L.co, L.ci, L.wpt, s);
+    launch_pack_conv3(L.wt, 0, L.co, L.ci, L.wpt, s);
     launch_conv3_mfma(dy, 0, N, L.co, L.ci, D, H, W, L.wpt, nullptr, 0, nullptr, nullptr, dx, s);
   } else {
     launch_conv_fwd(L.k, dy, N, L.co, L.ci, D, H, W, L.wt, nullptr, 0, nullptr, nullptr, dx, s);
@@ -265,6 +277,7 @@ void sgmg_unet_destroy(sgmg_unet* u) {
   free_act(u);
   free_energy(u);
   for (void* p : u->mem) hipFree(p);
+  if (u->h_flat) hipHostFree(u->h_flat);
   delete u;
 }
 
@@ -287,9 +300,9 @@ int sgmg_unet_create(uint64_t seed, sgmg_unet** out) {
     if (!rc) rc = ualloc(u->mem, &L.wt, (size_t)L.co * L.k3 * L.cip);
     if (!rc && L.k == 3) {
       float* a = nullptr;
-      rc = ualloc(u->mem, &a, 4 * conv3_packed_words(L.ci, L.co));
+      rc = ualloc(u->mem, &a, 4 * conv3_packed_words(kUp[l], L.ci, L.co));
       L.wp = (uint4*)a;
-      if (!rc) rc = ualloc(u->mem, &a, 4 * conv3_packed_words(L.co, L.ci));
+      if (!rc) rc = ualloc(u->mem, &a, 4 * conv3_packed_words(0, L.co, L.ci));
       L.wpt = (uint4*)a;
     }
     if (rc) { sgmg_unet_destroy(u); return rc; }
@@ -342,25 +355,34 @@ int sgmg_unet_set_params(sgmg_unet* u, const float* host, void* stream) {
   return check();
 }
 
+// One gather on the device and one copy into pinned memory (the first call
+// allocates both buffers), instead of two copies, a wait and a strided
+// rearrangement on the host per layer.
 static int copy_out(sgmg_unet* u, float* host, bool grads, bool quantized, hipStream_t s) {
-  size_t off = 0;
+  const size_t n = (size_t)sgmg_unet_num_params();
+  if (!u->flat && ualloc(u->mem, &u->flat, n)) return SGMG_ENOMEM;
+  if (!u->h_flat && hipHostMalloc((void**)&u->h_flat, n * sizeof(float), hipHostMallocDefault) != hipSuccess) {
+    u->h_flat = nullptr;
+    set_err("pinned allocation failed");
+    return SGMG_ENOMEM;
+  }
+  ParamTable t;
+  t.off[0] = 0;
   for (int l = 0; l < kNL; ++l) {
     const ULayer& L = u->L[l];
-    std::vector<float> w(L.nw), b(L.co);
-    const float* srcw = grads ? L.gw : (quantized ? L.wq : L.w);
-    const float* srcb = grads ? L.gb : L.b;
-    hipMemcpyAsync(w.data(), srcw, L.nw * sizeof(float), hipMemcpyDeviceToHost, s);
-    hipMemcpyAsync(b.data(), srcb, L.co * sizeof(float), hipMemcpyDeviceToHost, s);
-    if (hipStreamSynchronize(s) != hipSuccess) { set_err("sync failed"); return SGMG_EHIP; }
-    for (int co = 0; co < L.co; ++co)
-      for (int ci = 0; ci < L.ci; ++ci)
-        for (int t = 0; t < L.k3; ++t)
-          host[off + ((size_t)co * L.ci + ci) * L.k3 + t] = w[((size_t)ci * L.k3 + t) * L.cop + co];
-    off += (size_t)L.co * L.ci * L.k3;
-    std::memcpy(host + off, b.data(), L.co * sizeof(float));
-    off += L.co;
+    t.w[l] = grads ? L.gw : (quantized ? L.wq : L.w);
+    t.b[l] = grads ? L.gb : L.b;
+    t.ci[l] = L.ci; t.co[l] = L.co; t.k3[l] = L.k3; t.cop[l] = L.cop;
+    t.off[l + 1] = t.off[l] + L.co * L.ci * L.k3 + L.co;
   }
-  return 0;
+  launch_export_params(t, u->flat, s);
+  if (hipMemcpyAsync(u->h_flat, u->flat, n * sizeof(float), hipMemcpyDeviceToHost, s) != hipSuccess ||
+      hipStreamSynchronize(s) != hipSuccess) {
+    set_err("parameter copy failed");
+    return SGMG_EHIP;
+  }
+  std::memcpy(host, u->h_flat, n * sizeof(float));
+  return check();
 }
 
 int sgmg_unet_get_params(sgmg_unet* u, int quantized, float* host, void* stream) {
@@ -375,8 +397,7 @@ int sgmg_unet_forward(sgmg_unet* u, int N, int D, int H, int W, const float* in,
   if (rc) return rc;
   if ((rc = ensure_act(u, N, D, H, W))) return rc;
   hipStream_t s = (hipStream_t)stream;
-  forward(u, N, D, H, W, in, s);
-  hipMemcpyAsync(out, u->y, (size_t)N * 3 * D * H * W * sizeof(float), hipMemcpyDeviceToDevice, s);
+  forward(u, N, D, H, W, in, s, true, out);
   return check();
 }
 

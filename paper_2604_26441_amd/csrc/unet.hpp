@@ -33,15 +33,30 @@ struct FineView {
 };
 int hierarchy_fine_view(const ::sgmg_hierarchy* h, FineView* v);
 
+// Every layer's parameters (or gradients) on the device; off: first index of
+// each layer in the flat order of the C ABI, then the total.
+struct ParamTable {
+  static constexpr int kLayers = 8;
+  const float* w[kLayers];
+  const float* b[kLayers];
+  int ci[kLayers], co[kLayers], k3[kLayers], cop[kLayers], off[kLayers + 1];
+};
+void launch_export_params(const ParamTable& t, float* out, hipStream_t s);
+
 void launch_conv_fwd(int K, const float* x, int N, int Ci, int Co, int D, int H, int W,
                      const float* w, const float* b, int relu, float* rpre, const float* add,
                      float* y, hipStream_t s);
-size_t conv3_packed_words(int Ci, int Co);   // uint4 words of packed 3x3x3 weights
-void launch_pack_conv3(const float* w, int Ci, int Co, uint4* wp, hipStream_t s);
+// Packed 3x3x3 weights (uint4 words) of a layer that reads its input as stored
+// (up = 0) or upsampled (up = 1).
+size_t conv3_packed_words(int up, int Ci, int Co);
+void launch_pack_conv3(const float* w, int up, int Ci, int Co, uint4* wp, hipStream_t s);
 // up = 1: x is stored at (D/2, H/2, W/2) and read as its nearest x2 upsampling
+// (Ci a multiple of 8); with hw (up = 1, Co = 16) the 1x1x1 head's three
+// channels hw, hb of the result are written to hy, and y may be NULL.
 void launch_conv3_mfma(const float* x, int up, int N, int Ci, int Co, int D, int H, int W,
                        const uint4* wp, const float* b, int relu, float* rpre, const float* add,
-                       float* y, hipStream_t s);
+                       float* y, hipStream_t s, const float* hw = nullptr,
+                       const float* hb = nullptr, float* hy = nullptr);
 void launch_weight_transpose(const float* w, int Ci, int Co, int K, float* wt, hipStream_t s);
 size_t conv_wgrad_part_floats(int N, int Ci, int Co, int D, int H, int W, int K);
 void launch_conv_wgrad(int K, const float* x, int up, const float* dy, int N, int Ci, int Co, int D,
