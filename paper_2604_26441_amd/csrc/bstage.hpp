@@ -48,8 +48,11 @@ void bs_smooth0(const BsArgs& a, const BsTable& t, const int* flags, int post, i
                 int last, hipStream_t s);
 void bs_resid0(const BsArgs& a, const BsTable& t, const int* flags, int cin, hipStream_t s);
 void bs_restrict(const BsArgs& a, const BsTable& t, const int* flags, int l, hipStream_t s);
-void bs_coarse(const BsArgs& a, const BsTable& tg, const BsTable& tm, const int* flags,
-               hipStream_t s);
+// Coarsest solves: the right-hand sides over the items' table tg, the products
+// over a table tm of (group, row block) entries, groups[g] = up to four items
+// of one system (-1 past the last).
+void bs_coarse(const BsArgs& a, const BsTable& tg, const BsTable& tm, const int4* groups,
+               const int* flags, hipStream_t s);
 void bs_prolong(const BsArgs& a, const BsTable& t, const int* flags, int l, int cfine, int ccoarse,
                 hipStream_t s);
 // Level 0 on the BF16X3 MFMA operator: the tile grid of a mesh for launch

@@ -2017,6 +2017,7 @@ struct sgmg_batch {
     bool ready = false;
     void* dmem = nullptr;
     BsTable tv, ts[8], tr[8], tcg, tcm;
+    const int4* groups = nullptr;  // items of one system that share a pass over its inverse
     BsTable tsc[8];                // levels >= 1: row-split stencil blocks
     BsTable tss[8];                // levels >= 1: LDS-staged stencil blocks
     int lform[8] = {};             // per level: 1 = LDS-staged form (timed faster)
@@ -2026,7 +2027,7 @@ struct sgmg_batch {
     int* h_flags = nullptr;        // pinned mirror
     double* h_scal = nullptr;      // pinned mirror
     int Lmax = 0, steps0 = 0, stepsL = 0;
-    hipGraphExec_t g_pro = nullptr, g_it = nullptr;
+    hipGraphExec_t g_pro = nullptr, g_it = nullptr, g_chk = nullptr;
     // level 0 on the BF16X3 MFMA operator: launch shape, (item, block)
     // table and per-item tile grids
     bool mfma0 = false;
@@ -2065,6 +2066,7 @@ void batch_free_staged(sgmg_batch* b) {
   auto& st = b->st;
   if (st.g_pro) hipGraphExecDestroy(st.g_pro);
   if (st.g_it) hipGraphExecDestroy(st.g_it);
+  if (st.g_chk) hipGraphExecDestroy(st.g_chk);
   if (st.g_first) hipGraphExecDestroy(st.g_first);
   if (st.g_more) hipGraphExecDestroy(st.g_more);
   if (st.lmem) hipFree(st.lmem);
@@ -2241,7 +2243,7 @@ void bs_vcycle(const sgmg_batch::Staged& st, const BsArgs& a, const int* flags, 
     bs_restrict(a, st.tr[l], flags, l, s);
     cur &= ~(1u << (l + 1));
   }
-  bs_coarse(a, st.tcg, st.tcm, flags, s);
+  bs_coarse(a, st.tcg, st.tcm, st.groups, flags, s);
   for (int l = st.Lmax - 2; l >= 0; --l) {
     const int steps = l == 0 ? st.steps0 : st.stepsL;
     bs_prolong(a, st.ts[l], flags, l, cb(l), cb(l + 1), s);
@@ -2264,6 +2266,14 @@ void bs_prologue(const sgmg_batch* b, const BsArgs& a, int n, hipStream_t s) {
   bs_vcycle(st, a, fl, s);
   bs_dot_rz(a, st.tv, fl, 1, st.part, s);
   bs_finalize(st.tv, n, 1, st.part, fl, 4, st.scal, s);
+}
+
+// True residual (flags [0, n)): r = f - K u and (f.f, r.r), the start of the
+// prologue by itself.
+void bs_check(const sgmg_batch* b, const BsArgs& a, int n, hipStream_t s) {
+  const auto& st = b->st;
+  bs_fine64_res(a, st.ts[0], st.flags, st.part, s);
+  bs_finalize(st.ts[0], n, 2, st.part, st.flags, 0, st.scal, s);
 }
 
 // One PCG iteration (flags [n, 2n)): q = K p, alpha, x and r, V-cycle, beta, p.
@@ -2510,7 +2520,29 @@ int bs_prepare(sgmg_batch* b, int n, hipStream_t s) {
     hts.push_back(make([&](const BSys& S) { return S.L - 1 > l ? div_up(3 * S.lev[l + 1].g.Nn, TB) : 0; }));
   }
   hts.push_back(make([&](const BSys& S) { return div_up(S.nL, TB); }));               // tcg
-  hts.push_back(make([&](const BSys& S) { return div_up(S.nL, bs_coarse_rows()); }));  // tcm
+  // groups of up to four items of one system, in execution order, and the row
+  // blocks of each group
+  std::vector<int4> groups;
+  {
+    HT t;
+    t.start.assign(n, 0);
+    t.count.assign(n, 0);
+    std::map<int, int> open;                                                           // system -> group
+    for (int i = 0; i < n; ++i) {
+      const int sys = b->h_items[i].sys;
+      auto it = open.find(sys);
+      if (it == open.end() || groups[it->second].w >= 0) {
+        open[sys] = (int)groups.size();
+        groups.push_back(int4{i, -1, -1, -1});
+        const int c = div_up(hsys[sys].nL, bs_coarse_rows());
+        for (int j = 0; j < c; ++j) t.blk.push_back(int2{(int)groups.size() - 1, j});
+      } else {
+        int4& g = groups[it->second];
+        (g.y < 0 ? g.y : g.z < 0 ? g.z : g.w) = i;
+      }
+    }
+    hts.push_back(t);                                                                  // tcm
+  }
   for (int l = 1; l < st.Lmax - 1; ++l) {                                                // tsc, tss
     hts.push_back(make([&](const BSys& S) { return S.L - 1 > l ? bs_stencil_blocks(S.lev[l].g) : 0; }));
     hts.push_back(make([&](const BSys& S) { return S.L - 1 > l ? bs_stencil_s_blocks(S.lev[l].g) : 0; }));
@@ -2543,8 +2575,9 @@ int bs_prepare(sgmg_batch* b, int n, hipStream_t s) {
   const size_t part_b = 2 * maxblk * sizeof(double);
   const size_t scal_b = (size_t)n * kBsScalars * sizeof(double);
   const size_t flag_b = 2 * (size_t)n * sizeof(int);
+  const size_t grp_b = groups.size() * sizeof(int4);
   char* m = nullptr;
-  if (hipMalloc((void**)&m, bytes + part_b + scal_b + flag_b + 512) != hipSuccess) {
+  if (hipMalloc((void**)&m, bytes + part_b + scal_b + flag_b + grp_b + 1024) != hipSuccess) {
     set_error("staged batch allocation failed");
     return SGMG_ENOMEM;
   }
@@ -2572,6 +2605,9 @@ int bs_prepare(sgmg_batch* b, int n, hipStream_t s) {
   st.scal = (double*)(m + at);
   at += (scal_b + 255) & ~(size_t)255;
   st.flags = (int*)(m + at);
+  at += (flag_b + 255) & ~(size_t)255;
+  st.groups = (const int4*)(m + at);
+  SGMG_HIP(hipMemcpyAsync(m + at, groups.data(), grp_b, hipMemcpyHostToDevice, s));
   int k = 0;
   st.tv = dts[k++];
   for (int l = 0; l < st.Lmax - 1; ++l) {
@@ -2649,6 +2685,7 @@ int bs_prepare(sgmg_batch* b, int n, hipStream_t s) {
   }
   TRY(bs_capture(b, bs_prologue, n, &st.g_pro));
   TRY(bs_capture(b, bs_iteration, n, &st.g_it));
+  TRY(bs_capture(b, bs_check, n, &st.g_chk));
   st.ready = true;
   return 0;
 }
@@ -2903,14 +2940,22 @@ int sgmg_pcg_solve_batch_staged(sgmg_batch* b, int nitems, const int* item_sys,
       if (it == maxit) status[i] = SGMG_MAXIT;
     }
     if (ncheck) {
-      // the prologue recomputes r = f - K x in FP64 and restarts the
-      // recurrence from it (beta = 0) for the items that continue
-      TRY(run(st.g_pro));
+      // the true residual alone first: most checked items are done with it,
+      // and a V-cycle of a few items costs as many launches as one of all
+      TRY(run(st.g_chk));
+      int nagain = 0;
       for (int i = 0; i < n; ++i) {
         if (!hf[i]) continue;
         const double rt = std::sqrt(sc(i, kBsRR)) / nf[i];
-        if (rt < rtol) { status[i] = SGMG_CONVERGED; rel_true[i] = rt; continue; }
+        if (rt < rtol) { status[i] = SGMG_CONVERGED; rel_true[i] = rt; hf[i] = 0; continue; }
         rel[i] = rt;
+        ++nagain;
+      }
+      // the prologue restarts the recurrence from it (beta = 0) for the items
+      // that continue
+      if (nagain) TRY(run(st.g_pro));
+      for (int i = 0; i < n; ++i) {
+        if (!hf[i]) continue;
         const double rz = sc(i, kBsRZ);
         if (!std::isfinite(rz)) status[i] = SGMG_NONFINITE;
         else if (rz <= 0.0) status[i] = SGMG_BREAKDOWN;
@@ -2927,7 +2972,7 @@ int sgmg_pcg_solve_batch_staged(sgmg_batch* b, int nitems, const int* item_sys,
     nleft += hf[i];
   }
   if (nleft) {
-    TRY(run(st.g_pro));
+    TRY(run(st.g_chk));
     for (int i = 0; i < n; ++i)
       if (hf[i]) rel_true[i] = std::sqrt(sc(i, kBsRR)) / (nf[i] > 0.0 ? nf[i] : 1.0);
   }
