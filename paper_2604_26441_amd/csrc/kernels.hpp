@@ -204,11 +204,24 @@ void launch_element_energy(const Grid& g, const double* ke, const double* rhohat
 void launch_oc_ratio(int nx, int ny, int nz, double rmin, const double* W, const double* gc,
                      const double* dH, double* ratio, double* dc_out, double* dv_out,
                      hipStream_t s);
-void launch_oc_volume(int nx, int ny, int nz, double rmin, const double* W, const double* rho,
-                      const double* ratio, double lam, double move, double beta, double eta,
-                      RedWs ws, double* vol_out, hipStream_t s);
+// OC volume bisection on the device.
+constexpr int kOcLevels = 6, kOcNodes = (1 << kOcLevels) - 1;   // halvings of a pass, midpoints
+struct OcState {
+  double l1, l2, lmid, vol;    // interval, last midpoint and its volume
+  int halvings, status;        // status 0: bisecting, 1: done, 2: a volume that is not finite
+  double lam[kOcNodes];        // the midpoints of the coming halvings' outcomes
+};
+void launch_filter_adjoint_ones(int nx, int ny, int nz, double rmin, const double* W, double* c,
+                                hipStream_t s);
+size_t oc_partials(int n);
+void launch_oc_init(OcState* st, hipStream_t s);
+void launch_oc_pass(int nx, int ny, int nz, double rmin, const double* W, const double* c,
+                    const double* rho, const double* ratio, double move, double beta, double eta,
+                    double target, double tol, int max_halvings, OcState* st, double* part,
+                    hipStream_t s);
 int oc_apply_blocks(int n);
-void launch_oc_apply(int n, double* rho, const double* ratio, double lam, double move, RedWs ws,
-                     hipStream_t s);
+// Applies the found multiplier (nothing unless the bisection is done).
+void launch_oc_apply(int n, double* rho, const double* ratio, const OcState* st, double move,
+                     RedWs ws, hipStream_t s);
 
 }  // namespace sgmg

@@ -3184,6 +3184,10 @@ struct sgmg_simp {
   double* dH = nullptr;
   double* gc = nullptr;      // dH * dc/drhohat
   double* ratio = nullptr;   // OC ratio max(-dc, 0) / dv
+  double* cvol = nullptr;    // F^T 1: the volume's weights without projection
+  double* oc_part = nullptr;
+  OcState* oc = nullptr;     // the bisection's state on the device, and its pinned copy
+  OcState* h_oc = nullptr;
   RedWs ws{};
   double* sc = nullptr;      // [0] compliance, [1] volume
   double* h_sc = nullptr;
@@ -3222,6 +3226,7 @@ void sgmg_simp_destroy(sgmg_simp* s) {
   if (!s) return;
   for (void* v : s->allocs) hipFree(v);
   if (s->h_sc) hipHostFree(s->h_sc);
+  if (s->h_oc) hipHostFree(s->h_oc);
   delete s;
 }
 
@@ -3245,17 +3250,21 @@ int sgmg_simp_create(const sgmg_simp_params* p, void* stream, sgmg_simp** out) {
   if ((rc = simp_alloc(s, &s->W, n)) || (rc = simp_alloc(s, &s->rhohat, n)) ||
       (rc = simp_alloc(s, &s->dH, n)) || (rc = simp_alloc(s, &s->gc, n)) ||
       (rc = simp_alloc(s, &s->ratio, n)) || (rc = simp_alloc(s, &s->ws.partials, nb)) ||
-      (rc = simp_alloc(s, &s->sc, 4))) {
+      (rc = simp_alloc(s, &s->sc, 4)) || (rc = simp_alloc(s, &s->cvol, n)) ||
+      (rc = simp_alloc(s, &s->oc_part, oc_partials((int)n))) ||
+      (rc = simp_alloc(s, (double**)&s->oc, (sizeof(OcState) + 7) / 8))) {
     sgmg_simp_destroy(s);
     return rc;
   }
-  if (hipHostMalloc((void**)&s->h_sc, 4 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc((void**)&s->h_sc, 4 * sizeof(double), hipHostMallocDefault) != hipSuccess ||
+      hipHostMalloc((void**)&s->h_oc, sizeof(OcState), hipHostMallocDefault) != hipSuccess) {
     sgmg_simp_destroy(s);
     set_error("pinned allocation failed");
     return SGMG_ENOMEM;
   }
   hipStream_t st = as_stream(stream);
   launch_filter_wsum(p->nx, p->ny, p->nz, p->rmin, s->W, st);
+  launch_filter_adjoint_ones(p->nx, p->ny, p->nz, p->rmin, s->W, s->cvol, st);
   if ((rc = check_launch()) || hipStreamSynchronize(st) != hipSuccess) {
     sgmg_simp_destroy(s);
     if (!rc) { set_error("sync failed"); rc = SGMG_EHIP; }
@@ -3306,27 +3315,26 @@ int sgmg_simp_oc_update(sgmg_simp* s, double* rho, double* lambda, double* volum
   const int n = p.nx * p.ny * p.nz;
   const double target = p.volfrac * n;
   hipStream_t st = as_stream(stream);
-  double l1 = 0.0, l2 = 1e9, lmid = 0.5 * (l1 + l2), vol = 0.0;
-  for (int it = 0; it < p.oc_max_halvings; ++it) {
-    lmid = 0.5 * (l1 + l2);
-    launch_oc_volume(p.nx, p.ny, p.nz, p.rmin, s->W, rho, s->ratio, lmid, p.move, p.beta, p.eta,
-                     s->ws, s->sc + 1, st);
-    TRY(check_launch());
-    SGMG_HIP(hipMemcpyAsync(s->h_sc + 1, s->sc + 1, sizeof(double), hipMemcpyDeviceToHost, st));
-    SGMG_HIP(hipStreamSynchronize(st));
-    vol = s->h_sc[1];
-    if (!std::isfinite(vol)) { set_error("OC volume is not finite"); return SGMG_EINVAL; }
-    if (vol > target) l1 = lmid;
-    else l2 = lmid;
-    if (l2 - l1 <= p.oc_tol * (l1 + l2)) break;
-  }
-  launch_oc_apply(n, rho, s->ratio, lmid, p.move, s->ws, st);
-  TRY(check_launch());
-  const int nb = oc_apply_blocks(n);
+  // passes of kOcLevels halvings (one with projection), the update gated on
+  // the bisection's end, then one readback; a bisection that is not done by
+  // then goes on.  1e9 down to a relative width of 1e-9 takes about 60 halvings
+  // plus the multiplier's own magnitude.
+  const int nb = oc_apply_blocks(n), levels = p.beta == 0.0 ? kOcLevels : 1;
   s->h_part.resize(nb);
-  SGMG_HIP(hipMemcpyAsync(s->h_part.data(), s->ws.partials, nb * sizeof(double),
-                          hipMemcpyDeviceToHost, st));
-  SGMG_HIP(hipStreamSynchronize(st));
+  launch_oc_init(s->oc, st);
+  do {
+    for (int k = 0; k < 84; k += levels)
+      launch_oc_pass(p.nx, p.ny, p.nz, p.rmin, s->W, s->cvol, rho, s->ratio, p.move, p.beta, p.eta,
+                     target, p.oc_tol, p.oc_max_halvings, s->oc, s->oc_part, st);
+    launch_oc_apply(n, rho, s->ratio, s->oc, p.move, s->ws, st);
+    TRY(check_launch());
+    SGMG_HIP(hipMemcpyAsync(s->h_oc, s->oc, sizeof(OcState), hipMemcpyDeviceToHost, st));
+    SGMG_HIP(hipMemcpyAsync(s->h_part.data(), s->ws.partials, nb * sizeof(double),
+                            hipMemcpyDeviceToHost, st));
+    SGMG_HIP(hipStreamSynchronize(st));
+  } while (s->h_oc->status == 0);
+  if (s->h_oc->status == 2) { set_error("OC volume is not finite"); return SGMG_EINVAL; }
+  const double lmid = s->h_oc->lmid, vol = s->h_oc->vol;
   double m = 0.0;
   for (double v : s->h_part) m = std::max(m, v);
   if (lambda) *lambda = lmid;
