@@ -58,14 +58,12 @@ void launch_apply_l1_haar(const Grid& coarse, int zchunk, const double* E8, doub
 bool l1_haar_size_ok(const Grid& coarse);
 void launch_scale_E(const double* E, float* Es, int nel, double inv_s, hipStream_t s);
 void build_mfma_atab(const KeTables& kt, uint16_t* out /* 2 * 64 * 8 */);
-
-// ---- stencil levels (kernels_stencil.hip) ----------------------------------
-// Level-1 Galerkin aggregation: S1 = M1 sum_e E_e P_e^T (M_e K_e M_e) P_e M1.
-// gtab: 27 pattern products G_p = P_p^T K_e P_p (24x24 each, pattern index
-// px + 3 py + 9 pz), ke: K_e for the masked-child path.
-void launch_galerkin_l1(const Grid& fine, const Grid& coarse, const double* E,
-                        const double* gtab, const double* ke, const uint8_t* ffix,
-                        const uint8_t* cfix, double* S, hipStream_t s);
+// Coarse nodes next to a fixed fine DOF: flags and a list (its length first).
+void launch_l1_masked_nodes(const Grid& fine, const Grid& coarse, const uint8_t* ffix, uint8_t* flag,
+                            int* list, hipStream_t s);
+void launch_galerkin_l1(const Grid& fine, const Grid& coarse, const double* E, const uint8_t* flag,
+                        const int* list, const double* gtab, const double* ke,
+                        const uint8_t* ffix, const uint8_t* cfix, double* S, hipStream_t s);
 void launch_galerkin_stencil(const Grid& fine, const Grid& coarse, const double* Sf,
                              const uint8_t* cfix, double* Sc, hipStream_t s);
 void launch_stencil_diag(const Grid& g, const double* S, double* d, hipStream_t s);
@@ -100,9 +98,9 @@ void launch_dot(const double* a, const double* b, const double* w, int n, RedWs 
                 double* out, hipStream_t s);
 // y = Dinv * w ; out = ||y||^2
 void launch_scale_dinv_norm(const double* dinv, const double* w, double* y, int n, RedWs ws,
-                            double* out, hipStream_t s);
+                            hipStream_t s);
 // x = y / sqrt(*nrm2)
-void launch_normalize(const double* y, const double* nrm2, double* x, int n, hipStream_t s);
+void launch_normalize(const double* y, const double* part, double* x, int n, hipStream_t s);
 // V-cycle entry on level 0: b = (T) r ; d = c0 * Dinv * b ; x = d
 template <typename T>
 void launch_vcycle_entry(const double* r, T* b, const T* dinv, double c0, T* x, T* d, int n,

@@ -1,5 +1,7 @@
 // Galerkin levels (l >= 1): assembly into a structured 27-point block
 // stencil, its application, and the trilinear transfer kernels.
+#include <algorithm>
+
 #include "batch.hpp"
 #include "bstage.hpp"
 #include "kernels.hpp"
@@ -7,20 +9,50 @@
 
 namespace sgmg {
 
-// 1D local pattern of a fine element inside its coarse element (Sec. 3.3):
-// pattern p = fine index - 2 * coarse index in {0, 1, 2}; entry [dx][cx] is
-// the weight of coarse local node cx at fine local node dx.  Pattern 2 is the
-// last fine element of an odd axis, whose two nodes both map onto the last
-// coarse node (trailing-node weight 1).
-__device__ __constant__ double c_pat[3][2][2] = {
-    {{1.0, 0.0}, {0.5, 0.5}}, {{0.5, 0.5}, {0.0, 1.0}}, {{0.0, 1.0}, {0.0, 1.0}}};
+// Weight of coarse node `end` (0 or 1) of a coarse element at its fine node `t`
+// (0 .. 2 along an axis; 3 exists with an odd fine count only).
+__device__ __forceinline__ double pat_weight(int t, int end) {
+  return t == 1 ? 0.5 : (t == 0) == (end == 0) ? 1.0 : 0.0;
+}
 
-__device__ inline bool elem_has_fixed(const Grid& f, const uint8_t* ffix, int ex, int ey, int ez) {
+// Lists the coarse nodes whose adjacent coarse elements hold a fixed fine DOF,
+// in any order: list[1 ..], their count in list[0]; flag[I] = 1 for them.  The
+// masks never change, so this is made once per hierarchy.  HI: fine nodes
+// above 2 I to look at (3 where an odd axis ends with a third child).
+template <int HI>
+__global__ void k_l1_masked_nodes(Grid f, Grid c, const uint8_t* __restrict__ ffix,
+                                  uint8_t* __restrict__ flag, int* __restrict__ list) {
+  const int I = blockIdx.x * blockDim.x + threadIdx.x;
+  if (I >= c.Nn) return;
+  const int Ix = I % c.Nx, t = I / c.Nx, Iy = t % c.Ny, Iz = t / c.Ny;
+  // clamped to the grid (the clamped node is in the range as well), so that
+  // the loads do not wait for each other
   unsigned any = 0;
+  for (int dz = -2; dz <= HI; ++dz) {
+    const int z = min(max(2 * Iz + dz, 0), f.Nz - 1);
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
-    any |= ffix[(ex + (a & 1)) + f.Nx * ((ey + ((a >> 1) & 1)) + f.Ny * (ez + (a >> 2)))];
-  return any != 0;
+    for (int dy = -2; dy <= HI; ++dy) {
+      const int y = min(max(2 * Iy + dy, 0), f.Ny - 1);
+#pragma unroll
+      for (int dx = -2; dx <= HI; ++dx) {
+        const int x = min(max(2 * Ix + dx, 0), f.Nx - 1);
+        any |= ffix[x + f.Nx * (y + f.Ny * z)];
+      }
+    }
+  }
+  flag[I] = any ? 1 : 0;
+  if (any) list[1 + atomicAdd(list, 1)] = I;
+}
+
+static __global__ void k_zero_count(int* p) { *p = 0; }
+
+void launch_l1_masked_nodes(const Grid& fine, const Grid& coarse, const uint8_t* ffix, uint8_t* flag,
+                            int* list, hipStream_t s) {
+  k_zero_count<<<1, 1, 0, s>>>(list);
+  if ((fine.nx | fine.ny | fine.nz) & 1)
+    k_l1_masked_nodes<3><<<div_up(coarse.Nn, 256), 256, 0, s>>>(fine, coarse, ffix, flag, list);
+  else
+    k_l1_masked_nodes<2><<<div_up(coarse.Nn, 256), 256, 0, s>>>(fine, coarse, ffix, flag, list);
 }
 
 // Level-1 Galerkin aggregation (Eq. galerkin_level1).  Thread (I, o) owns the
@@ -29,79 +61,78 @@ __device__ inline bool elem_has_fixed(const Grid& f, const uint8_t* ffix, int ex
 // where G_p = P_p^T K_e P_p is the precomputed local triple product of the
 // child's pattern.  Children touching a fixed fine DOF use M_e K_e M_e,
 // formed on the fly.  Finally rows/columns of fixed coarse DOFs are zeroed.
+// The loops run over positions that are the same for every lane (element I - 1
+// + s per axis, child p): G and K_e are read through scalar registers, and a
+// lane whose element or child is outside the grid adds zeros.  ODD: an axis
+// with an odd fine count, whose last coarse element has three children.
+// The nodes next to a fixed DOF (listed) have a kernel of their own with a
+// thread per entry: among the others one of them in a wave made the whole wave
+// wait for its long chain of short products (80^3: 554 us; apart 50 + 187 us,
+// 32^3: 205 against 16 + 97 us).  Bound: the 243 stored values per node (134 MB
+// at 80^3, 28 us), and for the listed ones that chain.
+template <bool ODD>
+struct L1Children {
+  static constexpr int NP = ODD ? 3 : 2;
+  static constexpr int N = NP * NP * NP;
+  double E[N];   // the children's moduli, 0 where there is none
+  __device__ __forceinline__ L1Children(const Grid& f, const Grid& c, const double* __restrict__ mod,
+                                        int cx, int cy, int cz) {
+    const bool in = (unsigned)cx < (unsigned)c.nx && (unsigned)cy < (unsigned)c.ny &&
+                    (unsigned)cz < (unsigned)c.nz;
+    const int npx = ODD && cx == c.nx - 1 && (f.nx & 1) ? 3 : 2;
+    const int npy = ODD && cy == c.ny - 1 && (f.ny & 1) ? 3 : 2;
+    const int npz = ODD && cz == c.nz - 1 && (f.nz & 1) ? 3 : 2;
+#pragma unroll
+    for (int p = 0; p < N; ++p) {
+      const int px = p % NP, py = (p / NP) % NP, pz = p / (NP * NP);
+      const bool ok = in && px < npx && py < npy && pz < npz;
+      E[p] = mod[ok ? 2 * cx + px + f.nx * (2 * cy + py + f.ny * (2 * cz + pz)) : 0];
+      if (!ok) E[p] = 0.0;
+    }
+  }
+};
+
+template <bool ODD>
 __global__ __launch_bounds__(256) void k_galerkin_l1(Grid f, Grid c, const double* __restrict__ E,
+                                                     const uint8_t* __restrict__ flag,
                                                      const double* __restrict__ gtab,
-                                                     const double* __restrict__ ke,
-                                                     const uint8_t* __restrict__ ffix,
                                                      const uint8_t* __restrict__ cfix,
                                                      double* __restrict__ S) {
   const int I = blockIdx.x * 256 + threadIdx.x;
+  if (I >= c.Nn || flag[I]) return;
   const int o = blockIdx.y;
-  if (I >= c.Nn) return;
   const int ox = o % 3 - 1, oy = (o / 3) % 3 - 1, oz = o / 9 - 1;
   const int Ix = I % c.Nx, t = I / c.Nx, Iy = t % c.Ny, Iz = t / c.Ny;
   const int Jx = Ix + ox, Jy = Iy + oy, Jz = Iz + oz;
+  using Kids = L1Children<ODD>;
   double acc[9];
 #pragma unroll
   for (int q = 0; q < 9; ++q) acc[q] = 0.0;
+  for (int sz = 0; sz < 2; ++sz) {
+    const int aIz = 1 - sz, aJz = aIz + oz;
+    if ((unsigned)aJz > 1u) continue;
+    for (int sy = 0; sy < 2; ++sy) {
+      const int aIy = 1 - sy, aJy = aIy + oy;
+      if ((unsigned)aJy > 1u) continue;
+      for (int sx = 0; sx < 2; ++sx) {
+        const int aIx = 1 - sx, aJx = aIx + ox;
+        if ((unsigned)aJx > 1u) continue;
+        const int aI = aIx + 2 * aIy + 4 * aIz, aJ = aJx + 2 * aJy + 4 * aJz;
+        const Kids k(f, c, E, Ix - 1 + sx, Iy - 1 + sy, Iz - 1 + sz);
+#pragma unroll
+        for (int q = 0; q < Kids::N; ++q) {
+          const int px = q % Kids::NP, py = (q / Kids::NP) % Kids::NP, pz = q / (Kids::NP * Kids::NP);
+          const double* G = gtab + (size_t)(px + 3 * py + 9 * pz) * 576 + 3 * aI * 24 + 3 * aJ;
+#pragma unroll
+          for (int d = 0; d < 3; ++d)
+#pragma unroll
+            for (int e = 0; e < 3; ++e) acc[3 * d + e] += k.E[q] * G[d * 24 + e];
+        }
+      }
+    }
+  }
   const bool jok = (unsigned)Jx < (unsigned)c.Nx && (unsigned)Jy < (unsigned)c.Ny &&
                    (unsigned)Jz < (unsigned)c.Nz;
-  if (jok) {
-    // coarse elements containing both I and J, per axis
-    const int cx0 = max(max(Ix, Jx) - 1, 0), cx1 = min(min(Ix, Jx), c.nx - 1);
-    const int cy0 = max(max(Iy, Jy) - 1, 0), cy1 = min(min(Iy, Jy), c.ny - 1);
-    const int cz0 = max(max(Iz, Jz) - 1, 0), cz1 = min(min(Iz, Jz), c.nz - 1);
-    for (int cz = cz0; cz <= cz1; ++cz)
-      for (int cy = cy0; cy <= cy1; ++cy)
-        for (int cx = cx0; cx <= cx1; ++cx) {
-          const int aI = (Ix - cx) + 2 * (Iy - cy) + 4 * (Iz - cz);
-          const int aJ = (Jx - cx) + 2 * (Jy - cy) + 4 * (Jz - cz);
-          const int npx = (cx == c.nx - 1 && (f.nx & 1)) ? 3 : 2;
-          const int npy = (cy == c.ny - 1 && (f.ny & 1)) ? 3 : 2;
-          const int npz = (cz == c.nz - 1 && (f.nz & 1)) ? 3 : 2;
-          for (int pz = 0; pz < npz; ++pz)
-            for (int py = 0; py < npy; ++py)
-              for (int px = 0; px < npx; ++px) {
-                const int ex = 2 * cx + px, ey = 2 * cy + py, ez = 2 * cz + pz;
-                const double Ee = E[ex + f.nx * (ey + f.ny * ez)];
-                const int p = px + 3 * py + 9 * pz;
-                if (!elem_has_fixed(f, ffix, ex, ey, ez)) {
-                  const double* G = gtab + (size_t)p * 576;
-#pragma unroll
-                  for (int d = 0; d < 3; ++d)
-#pragma unroll
-                    for (int e = 0; e < 3; ++e)
-                      acc[3 * d + e] += Ee * G[(3 * aI + d) * 24 + 3 * aJ + e];
-                } else {
-                  // masked child: sum_{alpha,beta} W(alpha,aI) W(beta,aJ) m K_e m
-                  for (int al = 0; al < 8; ++al) {
-                    const double wa = c_pat[px][al & 1][aI & 1] *
-                                      c_pat[py][(al >> 1) & 1][(aI >> 1) & 1] *
-                                      c_pat[pz][al >> 2][aI >> 2];
-                    if (wa == 0.0) continue;
-                    const unsigned fa = ffix[(ex + (al & 1)) + f.Nx * ((ey + ((al >> 1) & 1)) +
-                                                                        f.Ny * (ez + (al >> 2)))];
-                    for (int be = 0; be < 8; ++be) {
-                      const double wb = c_pat[px][be & 1][aJ & 1] *
-                                        c_pat[py][(be >> 1) & 1][(aJ >> 1) & 1] *
-                                        c_pat[pz][be >> 2][aJ >> 2];
-                      if (wb == 0.0) continue;
-                      const unsigned fb =
-                          ffix[(ex + (be & 1)) +
-                               f.Nx * ((ey + ((be >> 1) & 1)) + f.Ny * (ez + (be >> 2)))];
-                      for (int d = 0; d < 3; ++d) {
-                        if ((fa >> d) & 1u) continue;
-                        for (int e = 0; e < 3; ++e) {
-                          if ((fb >> e) & 1u) continue;
-                          acc[3 * d + e] += Ee * wa * wb * ke[(3 * al + d) * 24 + 3 * be + e];
-                        }
-                      }
-                    }
-                  }
-                }
-              }
-        }
-  }
   const unsigned fI = cfix[I];
   const unsigned fJ = jok ? cfix[Jx + c.Nx * (Jy + c.Ny * Jz)] : 7u;
 #pragma unroll
@@ -113,108 +144,214 @@ __global__ __launch_bounds__(256) void k_galerkin_l1(Grid f, Grid c, const doubl
     }
 }
 
-void launch_galerkin_l1(const Grid& fine, const Grid& coarse, const double* E, const double* gtab,
-                        const double* ke, const uint8_t* ffix, const uint8_t* cfix, double* S,
-                        hipStream_t s) {
-  dim3 grid(div_up(coarse.Nn, 256), 27);
-  k_galerkin_l1<<<grid, 256, 0, s>>>(fine, coarse, E, gtab, ke, ffix, cfix, S);
+// Entry blockIdx.y of the listed nodes.  The fixed DOFs of a coarse element's
+// fine nodes are held as bits, so that no load waits in the loops.
+template <bool ODD>
+__global__ __launch_bounds__(64) void k_galerkin_l1_masked(
+    Grid f, Grid c, const double* __restrict__ E, const int* __restrict__ list,
+    const double* __restrict__ gtab, const double* __restrict__ ke,
+    const uint8_t* __restrict__ ffix, const uint8_t* __restrict__ cfix, double* __restrict__ S) {
+  const int n = list[0];
+  const int o = blockIdx.y / 9, d = blockIdx.y / 3 % 3, e = blockIdx.y % 3;
+  const int ox = o % 3 - 1, oy = (o / 3) % 3 - 1, oz = o / 9 - 1;
+  using Kids = L1Children<ODD>;
+  constexpr int NP = Kids::NP, NF = NP + 1;   // fine nodes of a coarse element, per axis
+  __shared__ double kde[64];                  // K_e[3 alpha + d, 3 beta + e]
+  kde[threadIdx.x] = ke[(3 * (threadIdx.x >> 3) + d) * 24 + 3 * (threadIdx.x & 7) + e];
+  __syncthreads();
+  for (int it = blockIdx.x * 64 + threadIdx.x; it < n; it += gridDim.x * 64) {
+    const int I = list[1 + it];
+    const int Ix = I % c.Nx, t = I / c.Nx, Iy = t % c.Ny, Iz = t / c.Ny;
+    const int Jx = Ix + ox, Jy = Iy + oy, Jz = Iz + oz;
+    double acc = 0.0;
+    for (int sz = 0; sz < 2; ++sz) {
+      const int aIz = 1 - sz, aJz = aIz + oz;
+      if ((unsigned)aJz > 1u) continue;
+      for (int sy = 0; sy < 2; ++sy) {
+        const int aIy = 1 - sy, aJy = aIy + oy;
+        if ((unsigned)aJy > 1u) continue;
+        for (int sx = 0; sx < 2; ++sx) {
+          const int aIx = 1 - sx, aJx = aIx + ox;
+          if ((unsigned)aJx > 1u) continue;
+          const int aI = aIx + 2 * aIy + 4 * aIz, aJ = aJx + 2 * aJy + 4 * aJz;
+          const int cx = Ix - 1 + sx, cy = Iy - 1 + sy, cz = Iz - 1 + sz;
+          const Kids k(f, c, E, cx, cy, cz);
+          uint64_t any = 0, rows = 0, cols = 0;   // any DOF, DOF d, DOF e fixed
+#pragma unroll
+          for (int q = 0; q < NF * NF * NF; ++q) {
+            // clamped: such a node belongs to no child, and its bit is not looked at
+            const int x = min(max(2 * cx + q % NF, 0), f.Nx - 1);
+            const int y = min(max(2 * cy + q / NF % NF, 0), f.Ny - 1);
+            const int z = min(max(2 * cz + q / (NF * NF), 0), f.Nz - 1);
+            const unsigned m = ffix[x + f.Nx * (y + f.Ny * z)];
+            any |= (uint64_t)(m != 0) << q;
+            rows |= (uint64_t)((m >> d) & 1u) << q;
+            cols |= (uint64_t)((m >> e) & 1u) << q;
+          }
+          constexpr uint64_t corner = 3ull | 3ull << NF | (3ull | 3ull << NF) << (NF * NF);
+#pragma unroll
+          for (int q = 0; q < Kids::N; ++q) {
+            const int px = q % NP, py = (q / NP) % NP, pz = q / (NP * NP);
+            const int b0 = px + NF * (py + NF * pz);
+            if (!(any >> b0 & corner)) {
+              acc += k.E[q] * gtab[(size_t)(px + 3 * py + 9 * pz) * 576 + (3 * aI + d) * 24 + 3 * aJ + e];
+              continue;
+            }
+            // masked child: sum_{alpha,beta} W(alpha,aI) W(beta,aJ) m K_e m
+            double wb[8];
+#pragma unroll
+            for (int be = 0; be < 8; ++be) {
+              const int bit = b0 + (be & 1) + NF * (((be >> 1) & 1) + NF * (be >> 2));
+              wb[be] = (cols >> bit) & 1u
+                           ? 0.0
+                           : pat_weight(px + (be & 1), aJ & 1) *
+                                 pat_weight(py + ((be >> 1) & 1), (aJ >> 1) & 1) *
+                                 pat_weight(pz + (be >> 2), aJ >> 2);
+            }
+#pragma unroll 1
+            for (int al = 0; al < 8; ++al) {
+              const double wa = pat_weight(px + (al & 1), aI & 1) *
+                                pat_weight(py + ((al >> 1) & 1), (aI >> 1) & 1) *
+                                pat_weight(pz + (al >> 2), aI >> 2);
+              if (wa == 0.0) continue;
+              const int bit = b0 + (al & 1) + NF * (((al >> 1) & 1) + NF * (al >> 2));
+              const double Ew = (rows >> bit) & 1u ? 0.0 : k.E[q] * wa;
+#pragma unroll
+              for (int be = 0; be < 8; ++be)   // a weight of zero or a fixed DOF adds zero
+                acc += Ew * wb[be] * kde[8 * al + be];
+            }
+          }
+        }
+      }
+    }
+    const bool jok = (unsigned)Jx < (unsigned)c.Nx && (unsigned)Jy < (unsigned)c.Ny &&
+                     (unsigned)Jz < (unsigned)c.Nz;
+    const unsigned fI = cfix[I];
+    const unsigned fJ = jok ? cfix[Jx + c.Nx * (Jy + c.Ny * Jz)] : 7u;
+    S[(size_t)blockIdx.y * c.Nn + I] = ((fI >> d) & 1u) || ((fJ >> e) & 1u) ? 0.0 : acc;
+  }
+}
+
+void launch_galerkin_l1(const Grid& fine, const Grid& coarse, const double* E, const uint8_t* flag,
+                        const int* list, const double* gtab, const double* ke,
+                        const uint8_t* ffix, const uint8_t* cfix, double* S, hipStream_t s) {
+  const dim3 grid(div_up(coarse.Nn, 256), 27);
+  // the list's length is known on the device: enough blocks for a face of
+  // nodes, more nodes take more rounds
+  const dim3 gm(std::min(div_up(coarse.Nn, 64), 32u), 243);
+  if ((fine.nx | fine.ny | fine.nz) & 1) {
+    k_galerkin_l1<true><<<grid, 256, 0, s>>>(fine, coarse, E, flag, gtab, cfix, S);
+    k_galerkin_l1_masked<true><<<gm, 64, 0, s>>>(fine, coarse, E, list, gtab, ke, ffix, cfix, S);
+  } else {
+    k_galerkin_l1<false><<<grid, 256, 0, s>>>(fine, coarse, E, flag, gtab, cfix, S);
+    k_galerkin_l1_masked<false><<<gm, 64, 0, s>>>(fine, coarse, E, list, gtab, ke, ffix, cfix, S);
+  }
 }
 
 // Deeper Galerkin product K^{l+1} = M P^T K^l P M on stencils (Sec. 3.3).
-// Thread (I, o) sums w(i,I) w(j,J) K^l[i, j] over the fine nodes i that
-// interpolate from I and their stencil neighbours j.  The weights factor over
-// the axes, so each axis contributes a 3 x 3 table of pair weights
-// w1d(i,I) w1d(j,J) for i = 2I + a - 1, j = i + b - 1 (zero where a node is
-// outside the grid or outside the support).  The loops over the z and y pairs
-// skip zero weights before any load.  K^l is stored masked, so only the coarse mask is applied here.
+// Thread (I, o, de) sums w(i,I) w(j,J) K^l[i, j] (entry de of the 3 x 3 block)
+// over the fine nodes i that interpolate from I and their stencil neighbours
+// j.  The weights factor over the axes, so each axis contributes a 3 x 3 table
+// of pair weights w1d(i,I) w1d(j,J) for i = 2I + a - 1, j = i + b - 1 (zero
+// where a node is outside the grid or outside the support).  K^l is stored
+// masked, so only the coarse mask is applied here.
 __device__ inline double axis_pair_weight(int I, int J, int nf, int k) {
   const int i = 2 * I + k / 3 - 1, j = i + k % 3 - 1;
   return ((unsigned)i <= (unsigned)nf && (unsigned)j <= (unsigned)nf) ? w1d(i, I, nf) * w1d(j, J, nf)
                                                                       : 0.0;
 }
 
-// Sum over the pairs of one thread.  Of the nine x pairs, only those with
-// i and j both in the supports of I and J = I + OX can carry weight (the
-// support of a coarse node J is fine nodes 2J-1 .. 2J+1): pairs {0, 1, 3} for
-// OX = -1, {1, .., 7} for OX = 0 and {5, 7, 8} for OX = +1.  Those are loaded
-// without branches so that their loads are in flight together; a pair whose
-// weight is zero at the grid's edge reads an entry inside the grid and adds
-// 0 times it (every stencil entry is written, and finite).
-template <int OX>
-__device__ inline void galerkin_pairs(const Grid& f, const double* __restrict__ Sf, int Ix,
-                                      int Iy, int Iz, int Jy, int Jz, double (&acc)[9]) {
-  constexpr unsigned kMask = OX < 0 ? 0x00Bu : (OX == 0 ? 0x0FEu : 0x1A0u);
-  double wx[9];
+// Of an axis's nine pairs, only those with i and j both in the supports of I
+// and J = I + O can carry weight (the support of a coarse node J is fine nodes
+// 2J-1 .. 2J+1): pairs {0, 1, 3} for O = -1, {1, .., 7} for O = 0 and {5, 7, 8}
+// for O = +1.
+constexpr unsigned axis_pairs(int O) { return O < 0 ? 0x00Bu : (O == 0 ? 0x0FEu : 0x1A0u); }
+
+// Sum over the pairs of one thread: the loads of a z pair (up to 49) are all
+// in flight together; a pair whose weight is zero at the grid's edge reads an
+// entry inside the grid and adds 0 times it (every stencil entry is written,
+// and finite).
+template <int OX, int OY>
+__device__ inline double galerkin_pairs(const Grid& f, const double* __restrict__ Sf, int Ix, int Iy,
+                                        int Iz, int Jz) {
+  double wx[9], wy[9];
+  int ix[9], iy[9];
 #pragma unroll
-  for (int k = 0; k < 9; ++k)
-    wx[k] = (kMask >> k) & 1u ? axis_pair_weight(Ix, Ix + OX, f.nx, k) : 0.0;
-  // fine x index of each pair, clamped into the grid: where the clamp moves
-  // it the pair's weight is zero, and the load only has to stay in bounds
-  int ix[9];
-#pragma unroll
-  for (int k = 0; k < 9; ++k) ix[k] = min(max(2 * Ix + k / 3 - 1, 0), f.nx);
+  for (int k = 0; k < 9; ++k) {
+    wx[k] = (axis_pairs(OX) >> k) & 1u ? axis_pair_weight(Ix, Ix + OX, f.nx, k) : 0.0;
+    wy[k] = (axis_pairs(OY) >> k) & 1u ? axis_pair_weight(Iy, Iy + OY, f.ny, k) : 0.0;
+    // fine index of each pair, clamped into the grid: where the clamp moves
+    // it the pair's weight is zero, and the load only has to stay in bounds
+    ix[k] = min(max(2 * Ix + k / 3 - 1, 0), f.nx);
+    iy[k] = min(max(2 * Iy + k / 3 - 1, 0), f.ny);
+  }
   const size_t blk = (size_t)9 * f.Nn;       // distance between stencil blocks q, q+1
+  double acc = 0.0;
   for (int kz = 0; kz < 9; ++kz) {
     const double wz = axis_pair_weight(Iz, Jz, f.nz, kz);
     if (wz == 0.0) continue;
     const int iz = 2 * Iz + kz / 3 - 1;
+    const double* plane = Sf + (size_t)(9 * (kz % 3)) * blk + (size_t)f.Nx * f.Ny * iz;
+#pragma unroll
     for (int ky = 0; ky < 9; ++ky) {
-      const double wyz = axis_pair_weight(Iy, Jy, f.ny, ky) * wz;
-      if (wyz == 0.0) continue;
-      const int iy = 2 * Iy + ky / 3 - 1;
-      // block of (qx = -1, qy, qz) at fine node (0, iy, iz)
-      const int q0 = 3 * (ky % 3) + 9 * (kz % 3);
-      const double* row = Sf + (size_t)q0 * blk + f.Nx * (iy + f.Ny * iz);
+      if (!((axis_pairs(OY) >> ky) & 1u)) continue;
+      const double wyz = wy[ky] * wz;
+      const double* row = plane + (size_t)(3 * (ky % 3)) * blk + f.Nx * iy[ky];
 #pragma unroll
       for (int kx = 0; kx < 9; ++kx) {
-        if (!((kMask >> kx) & 1u)) continue;
-        const double w = wx[kx] * wyz;
-        const double* src = row + (size_t)(kx % 3) * blk + ix[kx];
-#pragma unroll
-        for (int de = 0; de < 9; ++de) acc[de] += w * src[(size_t)de * f.Nn];
+        if (!((axis_pairs(OX) >> kx) & 1u)) continue;
+        acc += wx[kx] * wyz * row[(size_t)(kx % 3) * blk + ix[kx]];
       }
     }
   }
+  return acc;
 }
 
-// Two waves per SIMD: the register budget lets the scheduler keep a whole
-// y pair's loads in flight (the kernel is bound by their latency).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void
-k_galerkin_stencil(Grid f, Grid c, const double* __restrict__ Sf, const uint8_t* __restrict__ cfix,
-                   double* __restrict__ Sc) {
+// One thread per entry of the 3 x 3 block: nine times the threads of one per
+// block, each with a ninth of the loads per step, so the chain of z pairs (up
+// to seven memory round trips) replaces one of up to 49, and the registers
+// allow more waves.  Blocks of the offsets with the most pairs come first.
+// Bound: the address units (16 cycles per strided load; 183 M loads for level 2
+// of 80^3). 80^3 level 2 / level 3: 400 / 159 us -> 286 us for both; 32^3 level 2: 146 -> 32 us.
+__global__ __launch_bounds__(256) void k_galerkin_stencil(Grid f, Grid c,
+                                                          const double* __restrict__ Sf,
+                                                          const uint8_t* __restrict__ cfix,
+                                                          double* __restrict__ Sc) {
+  // offsets by how many of their axes are 0: the centre, faces, edges, corners
+  constexpr uint8_t order[27] = {13, 4, 10, 12, 14, 16, 22, 1, 3, 5, 7, 9, 11, 15,
+                                 17, 19, 21, 23, 25, 0, 2, 6, 8, 18, 20, 24, 26};
   const int I = blockIdx.x * 256 + threadIdx.x;
-  const int o = blockIdx.y;
+  const int o = order[blockIdx.y / 9], de = blockIdx.y % 9, d = de / 3, e = de % 3;
   if (I >= c.Nn) return;
   const int ox = o % 3 - 1, oy = (o / 3) % 3 - 1, oz = o / 9 - 1;
   const int Ix = I % c.Nx, t = I / c.Nx, Iy = t % c.Ny, Iz = t / c.Ny;
   const int Jx = Ix + ox, Jy = Iy + oy, Jz = Iz + oz;
-  double acc[9];
-#pragma unroll
-  for (int q = 0; q < 9; ++q) acc[q] = 0.0;
   const bool jok = (unsigned)Jx < (unsigned)c.Nx && (unsigned)Jy < (unsigned)c.Ny &&
                    (unsigned)Jz < (unsigned)c.Nz;
+  double acc = 0.0;
+  const double* S0 = Sf + (size_t)de * f.Nn;
   if (jok) {
-    if (ox < 0)
-      galerkin_pairs<-1>(f, Sf, Ix, Iy, Iz, Jy, Jz, acc);
-    else if (ox == 0)
-      galerkin_pairs<0>(f, Sf, Ix, Iy, Iz, Jy, Jz, acc);
-    else
-      galerkin_pairs<1>(f, Sf, Ix, Iy, Iz, Jy, Jz, acc);
+    switch (3 * (oy + 1) + ox + 1) {
+      case 0: acc = galerkin_pairs<-1, -1>(f, S0, Ix, Iy, Iz, Jz); break;
+      case 1: acc = galerkin_pairs<0, -1>(f, S0, Ix, Iy, Iz, Jz); break;
+      case 2: acc = galerkin_pairs<1, -1>(f, S0, Ix, Iy, Iz, Jz); break;
+      case 3: acc = galerkin_pairs<-1, 0>(f, S0, Ix, Iy, Iz, Jz); break;
+      case 4: acc = galerkin_pairs<0, 0>(f, S0, Ix, Iy, Iz, Jz); break;
+      case 5: acc = galerkin_pairs<1, 0>(f, S0, Ix, Iy, Iz, Jz); break;
+      case 6: acc = galerkin_pairs<-1, 1>(f, S0, Ix, Iy, Iz, Jz); break;
+      case 7: acc = galerkin_pairs<0, 1>(f, S0, Ix, Iy, Iz, Jz); break;
+      default: acc = galerkin_pairs<1, 1>(f, S0, Ix, Iy, Iz, Jz); break;
+    }
   }
   const unsigned fI = cfix[I];
   const unsigned fJ = jok ? cfix[Jx + c.Nx * (Jy + c.Ny * Jz)] : 7u;
-#pragma unroll
-  for (int d = 0; d < 3; ++d)
-#pragma unroll
-    for (int e = 0; e < 3; ++e) {
-      const bool z = ((fI >> d) & 1u) || ((fJ >> e) & 1u);
-      Sc[(size_t)(o * 9 + 3 * d + e) * c.Nn + I] = z ? 0.0 : acc[3 * d + e];
-    }
+  const bool z = ((fI >> d) & 1u) || ((fJ >> e) & 1u);
+  Sc[(size_t)(o * 9 + de) * c.Nn + I] = z ? 0.0 : acc;
 }
 
 void launch_galerkin_stencil(const Grid& fine, const Grid& coarse, const double* Sf,
                              const uint8_t* cfix, double* Sc, hipStream_t s) {
-  dim3 grid(div_up(coarse.Nn, 256), 27);
+  dim3 grid(div_up(coarse.Nn, 256), 243);
   k_galerkin_stencil<<<grid, 256, 0, s>>>(fine, coarse, Sf, cfix, Sc);
 }
 

@@ -1,5 +1,7 @@
 // Vector kernels: deterministic dot products, PCG updates, casts, power
 // iteration helpers.
+#include <algorithm>
+
 #include "kernels.hpp"
 
 namespace sgmg {
@@ -71,13 +73,13 @@ int vec_dot_blocks(int n) { return (int)vec_grid(n); }
 void launch_dot(const double* a, const double* b, const double* w, int n, RedWs ws, double* out,
                 hipStream_t s) {
   k_dot<<<vec_grid(n), kVecBlock, 0, s>>>(a, b, w, n, ws, out);
-  launch_finalize(ws, vec_grid(n), 1, out, s);
+  if (out) launch_finalize(ws, vec_grid(n), 1, out, s);
 }
 
 __global__ __launch_bounds__(kVecBlock) void k_scale_dinv_norm(const double* __restrict__ dinv,
                                                                const double* __restrict__ w,
                                                                double* __restrict__ y, int n,
-                                                               RedWs ws, double* out) {
+                                                               RedWs ws) {
   double s = 0.0;
   for (int i = blockIdx.x * kVecBlock + threadIdx.x; i < n; i += gridDim.x * kVecBlock) {
     const double v = dinv[i] * w[i];
@@ -88,22 +90,49 @@ __global__ __launch_bounds__(kVecBlock) void k_scale_dinv_norm(const double* __r
   grid_sum<1>(v, ws);
 }
 
+// y = Dinv w; the block partials of y.y stay in ws.
 void launch_scale_dinv_norm(const double* dinv, const double* w, double* y, int n, RedWs ws,
-                            double* out, hipStream_t s) {
-  k_scale_dinv_norm<<<vec_grid(n), kVecBlock, 0, s>>>(dinv, w, y, n, ws, out);
-  launch_finalize(ws, vec_grid(n), 1, out, s);
+                            hipStream_t s) {
+  k_scale_dinv_norm<<<vec_grid(n), kVecBlock, 0, s>>>(dinv, w, y, n, ws);
 }
 
-__global__ void k_normalize(const double* __restrict__ y, const double* __restrict__ nrm2,
-                            double* __restrict__ x, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double s = *nrm2 > 0.0 ? 1.0 / sqrt(*nrm2) : 0.0;
-  x[i] = y[i] * s;
+// x = y / sqrt(nrm2), nrm2 the sum of np block partials: every block adds them
+// in the order of k_finalize, so no launch of its own is needed for that.
+__global__ __launch_bounds__(kVecBlock) void k_normalize(const double* __restrict__ y,
+                                                         const double* __restrict__ part, int np,
+                                                         double* __restrict__ x, int n) {
+  __shared__ double lds[16];
+  __shared__ double tot;
+  const int i0 = blockIdx.x * kVecBlock + threadIdx.x, stride = gridDim.x * kVecBlock;
+  double yg[kVecUnroll];
+  auto load = [&](int base) {
+#pragma unroll
+    for (int k = 0; k < kVecUnroll; ++k) {
+      const int i = base + k * stride;
+      if (i < n) yg[k] = y[i];
+    }
+  };
+  load(i0);
+  double a = 0.0;
+#pragma unroll 8
+  for (int b = threadIdx.x; b < np; b += kVecBlock) a += part[b];
+  a = block_sum(a, lds);
+  if (threadIdx.x == 0) tot = a;
+  __syncthreads();
+  const double s = tot > 0.0 ? 1.0 / sqrt(tot) : 0.0;
+  for (int base = i0; base < n; base += kVecUnroll * stride) {
+    if (base != i0) load(base);
+#pragma unroll
+    for (int k = 0; k < kVecUnroll; ++k) {
+      const int i = base + k * stride;
+      if (i < n) x[i] = yg[k] * s;
+    }
+  }
 }
 
-void launch_normalize(const double* y, const double* nrm2, double* x, int n, hipStream_t s) {
-  k_normalize<<<div_up(n, 256), 256, 0, s>>>(y, nrm2, x, n);
+// part: the block partials of launch_scale_dinv_norm or launch_dot over n.
+void launch_normalize(const double* y, const double* part, double* x, int n, hipStream_t s) {
+  k_normalize<<<vec_grid(n), kVecBlock, 0, s>>>(y, part, (int)vec_grid(n), x, n);
 }
 
 template <typename T>
@@ -414,7 +443,9 @@ void launch_pcg_update_p_red(double* p, const double* z, const double* rz_part, 
 
 // Largest value of a (non-negative entries, or masked by fixn when given).
 // Max is order independent, so the atomic on the IEEE bit pattern (monotone
-// for non-negative doubles) is deterministic.
+// for non-negative doubles) is deterministic.  One atomic per block of at most
+// 256 (one per wave of 1024 blocks, all on one address, took 30 us at 80^3).
+constexpr int kMaxGrid = 256;
 __global__ void k_max_nonneg(const double* __restrict__ a, const uint8_t* __restrict__ fixn, int n,
                              unsigned long long* __restrict__ out) {
   double m = 0.0;
@@ -422,13 +453,20 @@ __global__ void k_max_nonneg(const double* __restrict__ a, const uint8_t* __rest
     if (fixn && ((fixn[i / 3] >> (i % 3)) & 1u)) continue;
     m = fmax(m, a[i]);
   }
+  __shared__ double lds[kVecBlock / 64];
   for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
-  if ((threadIdx.x & 63) == 0) atomicMax(out, (unsigned long long)__double_as_longlong(m));
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+#pragma unroll
+  for (int w = 1; w < kVecBlock / 64; ++w) m = fmax(m, lds[w]);
+  atomicMax(out, (unsigned long long)__double_as_longlong(m));
 }
 
 void launch_max_nonneg(const double* a, const uint8_t* fixn, int n, double* out, hipStream_t s) {
   hipMemsetAsync(out, 0, sizeof(double), s);
-  k_max_nonneg<<<vec_grid(n), kVecBlock, 0, s>>>(a, fixn, n, (unsigned long long*)out);
+  k_max_nonneg<<<std::min(vec_grid(n), (unsigned)kMaxGrid), kVecBlock, 0, s>>>(
+      a, fixn, n, (unsigned long long*)out);
 }
 
 // Diagonal floor and inverse (Sec. 3.5: floored away from zero): free DOFs

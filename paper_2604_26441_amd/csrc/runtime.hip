@@ -66,6 +66,8 @@ struct sgmg_hierarchy {
   double* ke64 = nullptr;
   float* ke32 = nullptr;
   double* gtab = nullptr;
+  uint8_t* l1_mask = nullptr;  // coarse nodes next to a fixed DOF: flags
+  int* l1_mlist = nullptr;     // and a list, its length first
   double* E64 = nullptr;
   float* E32 = nullptr;
   float* E32s = nullptr;     // E / s for the MFMA kernel
@@ -362,16 +364,26 @@ int power_lambda(sgmg_hierarchy* h, int l, int iters, hipStream_t s, double* out
   double* x = h->p;
   double* w = h->q;
   double* y = h->z;
+  // only the last product's x.w is used; the others are plain products (on
+  // the Galerkin levels by the same stencil form, whose products the dot does
+  // not change)
+  auto product = [&](bool dot) -> int {
+    const Epi<double> ep = dot ? epi_store<double>(w, h->ws, h->sc + SC_XW) : epi_store<double>(w);
+    if (l == 0 || dot) return apply_level<double>(h, l, SGMG_F64, x, ep, s);
+    launch_stencil_apply<double>(L.g, L.S64, x, L.fixn, ep,
+                                 h->o.stencil_form == 3 ? 0 : h->o.stencil_form, s);
+    return check_launch();
+  };
   launch_power_start(x, L.fixn, L.g.Nn, h->o.seed + (uint64_t)l, s);
-  launch_dot(x, nullptr, nullptr, n, h->ws, h->sc + SC_NRM, s);
-  launch_normalize(x, h->sc + SC_NRM, x, n, s);
+  launch_dot(x, nullptr, nullptr, n, h->ws, nullptr, s);
+  launch_normalize(x, h->ws.partials, x, n, s);
   for (int k = 0; k < iters; ++k) {
-    TRY(apply_level<double>(h, l, SGMG_F64, x, epi_store<double>(w, h->ws, h->sc + SC_XW), s));
+    TRY(product(k == iters - 1));
     if (k == iters - 1) {
       launch_dot(x, x, L.d64, n, h->ws, h->sc + SC_XDX, s);
     } else {
-      launch_scale_dinv_norm(L.dinv64, w, y, n, h->ws, h->sc + SC_NRM, s);
-      launch_normalize(y, h->sc + SC_NRM, x, n, s);
+      launch_scale_dinv_norm(L.dinv64, w, y, n, h->ws, s);
+      launch_normalize(y, h->ws.partials, x, n, s);
     }
   }
   TRY(check_launch());
@@ -394,7 +406,7 @@ int assemble_operators(sgmg_hierarchy* h, const double* rho_or_E, hipStream_t s)
     Level& F = h->lev[l - 1];
     Level& C = h->lev[l];
     if (l == 1)
-      launch_galerkin_l1(F.g, C.g, h->E64, h->gtab, h->ke64, F.fixn, C.fixn, C.S64, s);
+      launch_galerkin_l1(F.g, C.g, h->E64, h->l1_mask, h->l1_mlist, h->gtab, h->ke64, F.fixn, C.fixn, C.S64, s);
     else
       launch_galerkin_stencil(F.g, C.g, F.S64, C.fixn, C.S64, s);
     launch_stencil_diag(C.g, C.S64, C.d64, s);
@@ -829,6 +841,8 @@ int sgmg_setup_hierarchy(const sgmg_options* opts, const double* rho_or_E, const
   arena.add(&h->E64, g0.nel);
   arena.add(&h->E32, g0.nel);
   arena.add(&h->E32s, g0.nel);
+  arena.add(&h->l1_mask, grids[1].Nn);
+  arena.add(&h->l1_mlist, (size_t)grids[1].Nn + 1);
   arena.add(&h->atab, 2 * 64 * 8);
   arena.add(&h->atab64, 2 * 6 * 64);
   // reductions, scalars, PCG vectors
@@ -884,6 +898,7 @@ int sgmg_setup_hierarchy(const sgmg_options* opts, const double* rho_or_E, const
   if ((rc = arena.commit(h))) return fail(rc);
   for (int l = 0; l < L; ++l)
     for (void* v : {h->lev[l].x[0], h->lev[l].x[1]}) hipMemsetAsync(v, 0, h->lev[l].g.n * es[l], s);
+  launch_l1_masked_nodes(g0, grids[1], masks[0], h->l1_mask, h->l1_mlist, s);
   hipMemsetAsync(h->ws.counter, 0, sizeof(unsigned), s);
   hipMemsetAsync(h->sc, 0, SC_COUNT * sizeof(double), s);
   std::vector<double> gt, at64(2 * 6 * 64);
