@@ -255,11 +255,12 @@ int sgmg_lanczos(sgmg_hierarchy* h, int precond, int m, const double* g, double 
 /* Autotuner of the fine operators' launch shape: times each candidate
  * (element rows per wave tile: 4, 8; owned node planes per wave: 2, 3, 4,
  * 6, 8, 16, 32) on this hierarchy's mesh for the BF16, BF16X3 and FP64 kernels
- * (the BF16 family in the smoothing epilogue, FP64 as a plain product),
+ * (the BF16 family in the smoothing epilogue and once more, up to 43 planes,
+ * as a plain product, which has a shape of its own; FP64 as a plain product),
  * keeps the fastest in h and in a process-wide cache keyed by (nx, ny, nz,
  * variant) that later setups of the same mesh read.  shape_out (host, 6
- * ints, may be NULL) receives (rows, planes) for BF16, BF16X3, then FP64;
- * for FP64 the vector-ALU node kernel is a candidate too, reported as (0, 0),
+ * ints, may be NULL) receives (rows, planes) for BF16, BF16X3 (smoothing
+ * steps), then FP64; for FP64 the vector-ALU node kernel is a candidate too, reported as (0, 0),
  * and so are the vector-ALU sum-factorised tiles with 2 .. 32 planes,
  * reported as (1, planes) ((1, 4) is the FP64 choice of an untuned mesh).  When
  * the hierarchy holds the level-1 element products (stencil_form 0 or 3,
@@ -274,7 +275,8 @@ int sgmg_lanczos(sgmg_hierarchy* h, int precond, int m, const double* g, double 
  * element sums differently from the matrix-core one). */
 int sgmg_autotune(sgmg_hierarchy* h, int* shape_out, void* stream);
 /* Pins the launch shape of one fine-operator variant (0 BF16, 1 BF16X3, 2
- * FP64) on h, e.g. to reuse a shape tuned earlier: rows 4 or 8, planes >= 1;
+ * FP64) on h, for smoothing steps and plain products alike, e.g. to reuse a
+ * shape tuned earlier: rows 4 or 8, planes >= 1;
  * FP64 also accepts (0, 0), the vector-ALU node kernel, and (1, planes >= 1),
  * the vector-ALU kernel with the element product in sum-factorised form.
  * Variant 3 selects how level 1 is applied on a hierarchy that holds its

@@ -75,6 +75,13 @@ struct sgmg_hierarchy {
   // per wave (tuned per mesh, or the default)
   int mfma_rows[3] = {4, 4, 1};     // [BF16, BF16X3, FP64]; FP64 rows 0: node kernel,
   int mfma_zchunk[3] = {4, 4, 4};   // rows 1: sum/difference-basis tiles
+  // and for plain products y = K u with BF16 and BF16X3: a quarter of a smoothing
+  // step's vector traffic, so longer chunks and taller tiles pay (256^3 BF16X3:
+  // 174 us with the smoothing step's 8 rows x 8 planes, 159 us with 8 x 29;
+  // 220^3: 106 and 94 us, with 8 x 37).  The bound is the LDS: 70 % busy, the
+  // vector ALU 45 %, the matrix cores 30 %
+  int store_rows[2] = {4, 4};
+  int store_zchunk[2] = {4, 4};
   uint16_t* atab = nullptr;  // MFMA A-operand table (BF16 bits)
   double* atab64 = nullptr;  // FP64 MFMA A-operand table
   // level 1 without its stored stencil (FP64 level 1 above the coarsest):
@@ -321,7 +328,9 @@ int apply_level<float>(const sgmg_hierarchy* h, int l, sgmg_prec prec, const flo
         return SGMG_EINVAL;
       }
       const int ns = prec == SGMG_BF16 ? 1 : prec == SGMG_BF16X2 ? 2 : 3;
-      launch_apply_fine_mfma(L.g, ns, h->mfma_rows[ns >= 2], h->mfma_zchunk[ns >= 2], h->E32s,
+      const bool plain = ep.mode == EPI_STORE && !ep.want_dot;
+      launch_apply_fine_mfma(L.g, ns, (plain ? h->store_rows : h->mfma_rows)[ns >= 2],
+                             (plain ? h->store_zchunk : h->mfma_zchunk)[ns >= 2], h->E32s,
                              h->atab, x, L.fixn, ep, s);
     } else {
       set_error("float vectors need F32, BF16 or BF16X3");
@@ -754,6 +763,10 @@ int sgmg_setup_hierarchy(const sgmg_options* opts, const double* rho_or_E, const
                                 q == 2 ? std::make_pair(1, 4) : std::make_pair(4, 4));
     h->mfma_rows[q] = sh.first;
     h->mfma_zchunk[q] = sh.second;
+    if (q == 2) break;
+    const auto st = tuned_shape(opts->nx, opts->ny, opts->nz, q ? 203 : 201, sh);
+    h->store_rows[q] = st.first;
+    h->store_zchunk[q] = st.second;
   }
   // level dims by floor coarsening and masks by injection
   Grid g0 = make_grid(opts->nx, opts->ny, opts->nz);
@@ -1614,6 +1627,10 @@ int sgmg_set_launch_shape(sgmg_hierarchy* h, int variant, int rows, int planes) 
   }
   h->mfma_rows[variant] = rows;
   h->mfma_zchunk[variant] = planes;
+  if (variant < 2) {
+    h->store_rows[variant] = rows;
+    h->store_zchunk[variant] = planes;
+  }
   for (auto& row : h->iter_graph)        // captured graphs hold the old launch shape
     for (auto& g : row)
       if (g) { hipGraphExecDestroy(g); g = nullptr; }
@@ -1747,7 +1764,9 @@ int sgmg_autotune(sgmg_hierarchy* h, int* shape_out, void* stream) {
   hipEventCreate(&e0);
   hipEventCreate(&e1);
   const int rows_c[] = {4, 8};
-  const int z_c[] = {2, 3, 4, 6, 8, 16, 32};
+  const int z_c[] = {2, 3, 4, 6, 8, 16, 32, 12, 20, 24, 29, 37, 43};
+  const int n_z = 7, n_z_store = 13;   // a plain product's chunks are long, and how many of
+                                       // them fill the last wave of blocks matters more
   double* u64 = nullptr;
   double* y64 = nullptr;
   int rc = 0;
@@ -1781,7 +1800,8 @@ int sgmg_autotune(sgmg_hierarchy* h, int* shape_out, void* stream) {
       hipEventElapsedTime(&best_ms, e0, e1);
       best_r = best_z = 0;
       // vector-ALU sum-factorised tiles (rows 1)
-      for (int z : z_c) {
+      for (int iz = 0; iz < n_z; ++iz) {
+        const int z = z_c[iz];
         if (z > L0.g.Nz && z != z_c[0]) continue;
         for (int w = 0; w < 3; ++w)
           launch_apply_fine_sf64(L0.g, z, h->E64, h->kt.lam, h->kt.mu, u64, L0.fixn,
@@ -1803,41 +1823,57 @@ int sgmg_autotune(sgmg_hierarchy* h, int* shape_out, void* stream) {
       }
       if (rc) break;
     }
-    for (int rows : rows_c) {
-      for (int z : z_c) {
-        if (z > L0.g.Nz && z != z_c[0]) continue;
-        auto launch = [&]() {
-          if (q == 2)
-            launch_apply_fine_mfma64(L0.g, rows, z, h->E64, h->atab64, u64, L0.fixn,
-                                     epi_store<double>(y64), s);
-          else   // a Chebyshev smoothing step: the epilogue of most V-cycle applications
-            launch_apply_fine_mfma(L0.g, key, rows, z, h->E32s, h->atab, u, L0.fixn,
-                                   epi_smooth<float>(y, u, (const float*)u64, (float*)y64, 0.5,
-                                                     0.5, 1, nullptr),
-                                   s);
-        };
-        for (int w = 0; w < 3; ++w) launch();
-        hipEventRecord(e0, s);
-        for (int r = 0; r < 30; ++r) launch();
-        hipEventRecord(e1, s);
-        if ((rc = check_launch())) break;
-        if (hipEventSynchronize(e1) != hipSuccess) {
-          rc = SGMG_EHIP;
-          set_error("autotune sync failed");
-          break;
+    // plain: y = K u; otherwise (BF16, BF16X3) a Chebyshev smoothing step, the
+    // epilogue of most V-cycle applications
+    auto tune_tiles = [&](bool plain) {
+      for (int rows : rows_c) {
+        for (int iz = 0; iz < (plain && q < 2 ? n_z_store : n_z); ++iz) {
+          const int z = z_c[iz];
+          if (z > L0.g.Nz && z != z_c[0]) continue;
+          auto launch = [&]() {
+            if (q == 2)
+              launch_apply_fine_mfma64(L0.g, rows, z, h->E64, h->atab64, u64, L0.fixn,
+                                       epi_store<double>(y64), s);
+            else
+              launch_apply_fine_mfma(L0.g, key, rows, z, h->E32s, h->atab, u, L0.fixn,
+                                     plain ? epi_store<float>(y)
+                                           : epi_smooth<float>(y, u, (const float*)u64,
+                                                               (float*)y64, 0.5, 0.5, 1, nullptr),
+                                     s);
+          };
+          for (int w = 0; w < 3; ++w) launch();
+          hipEventRecord(e0, s);
+          for (int r = 0; r < 30; ++r) launch();
+          hipEventRecord(e1, s);
+          if ((rc = check_launch())) return;
+          if (hipEventSynchronize(e1) != hipSuccess) {
+            rc = SGMG_EHIP;
+            set_error("autotune sync failed");
+            return;
+          }
+          float ms = 0.f;
+          hipEventElapsedTime(&ms, e0, e1);
+          if (ms < best_ms) { best_ms = ms; best_r = rows; best_z = z; }
         }
-        float ms = 0.f;
-        hipEventElapsedTime(&ms, e0, e1);
-        if (ms < best_ms) { best_ms = ms; best_r = rows; best_z = z; }
       }
-      if (rc) break;
-    }
+    };
+    auto keep = [&](int as) {
+      std::lock_guard<std::mutex> lk(g_tune_mu);
+      g_tune[std::make_tuple(L0.g.nx, L0.g.ny, L0.g.nz, as)] = std::make_pair(best_r, best_z);
+    };
+    tune_tiles(q == 2);
     if (rc) break;
     h->mfma_rows[q] = best_r;
     h->mfma_zchunk[q] = best_z;
     if (shape_out) { shape_out[2 * q] = best_r; shape_out[2 * q + 1] = best_z; }
-    std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_tune[std::make_tuple(L0.g.nx, L0.g.ny, L0.g.nz, key)] = std::make_pair(best_r, best_z);
+    keep(key);
+    if (q == 2) break;
+    best_ms = 1e30f;
+    tune_tiles(true);
+    if (rc) break;
+    h->store_rows[q] = best_r;
+    h->store_zchunk[q] = best_z;
+    keep(200 + key);
   }
   // level 1: the stored stencil against the element products (1 to 6 and
   // 8 planes); with stencil_form 3 the products stay and only their chunk
