@@ -913,7 +913,7 @@ template void launch_prolong_add<double, float>(const Grid&, const Grid&, const 
 // bit-identical scalars and take the same early-stop decision without any
 // grid-wide synchronisation or host round trip:
 //   prz[k][b]  block partials of r_k . z_k, z_k = D^-1 r_k   (k = 0..iters)
-//   ppq[k][b]  block partials of p_k . K p_k                  (k = 0..iters-1)
+//   ppq[k][b][d]  those of p_k . K p_k, rows d of 64 nodes b  (k = 0..iters-1)
 //   done[k]    1 when an earlier step stopped; later steps change nothing.
 // The apply launch forms p_k = z_k + beta_k p_{k-1} (beta_k = rz_k / rz_{k-1};
 // p_0 = z_0) on the fly for its node and the 26 neighbours, writes p_k into
@@ -922,13 +922,8 @@ template void launch_prolong_add<double, float>(const Grid&, const Grid&, const 
 // their vector and stencil loads before they read the flag and the partials,
 // so the chain of dependent memory round trips per launch stays short.
 
-// Sum of n values in a fixed order: lane-strided partial sums, then the
-// butterfly (every lane of every wave ends with the same bits).
-__device__ inline double wave_total(const double* __restrict__ v, int n) {
-  double t = 0.0;
-  for (int i = threadIdx.x & 63; i < n; i += 64) t += v[i];
-  return wave_sum(t);
-}
+// Nodes of a band of neighbours of 64 consecutive nodes, one z offset.
+__host__ __device__ inline int cpcg_band(const Grid& g) { return 64 + 2 * (g.Nx + 1); }
 
 __global__ __launch_bounds__(256) void k_cpcg_init(int n, const double* __restrict__ b,
                                                    const double* __restrict__ dinv,
@@ -952,13 +947,21 @@ __global__ __launch_bounds__(256) void k_cpcg_init(int n, const double* __restri
   }
 }
 
-// 576 threads: 64 nodes x 3 rows x 3 groups of 9 stencil offsets.  Offsets
+// Block (b, d): row d of 64 nodes; wave pz sums 9 stencil offsets.  Offsets
 // outside the grid read the node itself (a valid address) and add nothing.
 // K p_k is accumulated as K z_k + beta_k (K p_{k-1}) (the same product up
 // to rounding), so the stencil and vector loads need no beta and are all in
 // flight before the partials that give beta arrive.  Step 0 passes pold = z
 // and beta = 0: fma(0, z, z) = z exactly.
-__global__ __launch_bounds__(576) void k_cpcg_apply(Grid g, const double* __restrict__ S,
+// A coarsest grid has few nodes, so the stencil is fetched through few compute
+// units and their share of the bandwidth is the bound: a block per row instead
+// of one for all three rows of 64 nodes uses three times as many.  STAGED: the
+// neighbours of 64 consecutive nodes are three contiguous bands of z and pold,
+// loaded coalesced into LDS once instead of 54 strided loads per thread.  26 x
+// 13 x 7 nodes: 8.8 us with neither, 7.9 us staged, now 6.5 us (an empty launch
+// takes about 2 us).
+template <bool STAGED>
+__global__ __launch_bounds__(192) void k_cpcg_apply(Grid g, const double* __restrict__ S,
                                                     const uint8_t* __restrict__ fixn,
                                                     const double* __restrict__ z,
                                                     const double* __restrict__ pold,
@@ -966,16 +969,38 @@ __global__ __launch_bounds__(576) void k_cpcg_apply(Grid g, const double* __rest
                                                     const double* __restrict__ prz,
                                                     double* __restrict__ ppq,
                                                     const int* __restrict__ done, int k, int nbu) {
-  __shared__ double part[2][3][3][64];
-  __shared__ double lds[16];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int d = w % 3, pz = w / 3;
+  __shared__ double part[2][3][64];
+  extern __shared__ double band[];               // [z, pold][oz][3 * cpcg_band]
+  const int lane = threadIdx.x & 63, pz = threadIdx.x >> 6;
+  const int d = blockIdx.y;
   const int node0 = blockIdx.x * 64 + lane;
   const bool in = node0 < g.Nn;
   const int node = in ? node0 : g.Nn - 1;
   const int i = node % g.Nx, t = node / g.Nx, j = t % g.Ny, kk = t / g.Ny;
   const size_t Nn = g.Nn;
-  double az = 0.0, ap = 0.0;
+  const bool stop = done[k] != 0;
+  // this lane's share of the partials of r_k . z_k and r_{k-1} . z_{k-1}
+  const double* const rz1 = prz + (size_t)k * nbu;
+  const double* const rz0 = prz + (size_t)max(k - 1, 0) * nbu;
+  double t1 = 0.0, t0 = 0.0;
+  if (lane < nbu) {
+    t1 += rz1[lane];
+    t0 += rz0[lane];
+  }
+  const int wb = 3 * cpcg_band(g);               // doubles per band
+  if (STAGED) {
+    const int first = 3 * ((int)blockIdx.x * 64 - g.Nx - 1);
+#pragma unroll 4
+    for (int e = threadIdx.x; e < 3 * wb; e += 192) {
+      const int oz = e / wb;
+      const int at = min(max(first + (e - oz * wb) + 3 * (oz - 1) * g.Nx * g.Ny, 0), g.n - 1);
+      band[e] = z[at];
+      band[3 * wb + e] = pold[at];
+    }
+  }
+  double cf[27];
+  int at[9];
+  unsigned okm = 0;
 #pragma unroll
   for (int qq = 0; qq < 9; ++qq) {
     const int o = 9 * pz + qq;
@@ -983,44 +1008,55 @@ __global__ __launch_bounds__(576) void k_cpcg_apply(Grid g, const double* __rest
     const bool ok = (unsigned)(i + ox) < (unsigned)g.Nx && (unsigned)(j + oy) < (unsigned)g.Ny &&
                     (unsigned)(kk + oz) < (unsigned)g.Nz;
     const int nb = ok ? node + ox + g.Nx * (oy + g.Ny * oz) : node;
-    const size_t b3 = 3 * (size_t)nb;
     // upper blocks from the node, lower blocks mirrored from the neighbour
     const double* Sb = o >= 13 ? S + ((size_t)o * 9 + 3 * d) * Nn + node
                                : S + ((size_t)(26 - o) * 9 + d) * Nn + nb;
     const size_t st = o >= 13 ? Nn : 3 * Nn;
-    double vz = 0.0, vp = 0.0;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const double cf = Sb[c * st];
-      vz += cf * z[b3 + c];
-      vp += cf * pold[b3 + c];
-    }
-    az += ok ? vz : 0.0;
-    ap += ok ? vp : 0.0;
+    for (int c = 0; c < 3; ++c) cf[3 * qq + c] = Sb[c * st];
+    okm |= (unsigned)ok << qq;
+    at[qq] = STAGED ? pz * wb + 3 * (lane + g.Nx + 1 + ox + g.Nx * oy) : 3 * nb;
   }
-  part[0][pz][d][lane] = az;
-  part[1][pz][d][lane] = ap;
   const size_t dof = 3 * (size_t)node + d;
   const double zown = z[dof], pold_own = pold[dof];
   const unsigned fx = fixn[node];
-  const bool stop = done[k] != 0;
-  const double beta = k > 0 ? wave_total(prz + (size_t)k * nbu, nbu) /
-                                  wave_total(prz + (size_t)(k - 1) * nbu, nbu)
-                            : 0.0;
+  if (STAGED) __syncthreads();
+  const double* const vzs = STAGED ? band : z;
+  const double* const vps = STAGED ? band + 3 * wb : pold;
+  double az = 0.0, ap = 0.0;
+#pragma unroll
+  for (int qq = 0; qq < 9; ++qq) {
+    double vz = 0.0, vp = 0.0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      vz += cf[3 * qq + c] * vzs[at[qq] + c];
+      vp += cf[3 * qq + c] * vps[at[qq] + c];
+    }
+    az += (okm >> qq) & 1u ? vz : 0.0;
+    ap += (okm >> qq) & 1u ? vp : 0.0;
+  }
+  part[0][pz][lane] = az;
+  part[1][pz][lane] = ap;
+  for (int b = lane + 64; b < nbu; b += 64) {
+    t1 += rz1[b];
+    t0 += rz0[b];
+  }
+  const double beta = k > 0 ? wave_sum(t1) / wave_sum(t0) : 0.0;
   if (stop) return;                                   // uniform over the grid
   __syncthreads();
+  if (pz != 1) return;
   double dot = 0.0;
-  if (in && pz == 1) {
-    const double kz = (part[0][0][d][lane] + part[0][1][d][lane]) + part[0][2][d][lane];
-    const double kp = (part[1][0][d][lane] + part[1][1][d][lane]) + part[1][2][d][lane];
+  if (in) {
+    const double kz = (part[0][0][lane] + part[0][1][lane]) + part[0][2][lane];
+    const double kp = (part[1][0][lane] + part[1][1][lane]) + part[1][2][lane];
     const double pown = __builtin_fma(beta, pold_own, zown);
     const double y = (fx >> d) & 1u ? 0.0 : __builtin_fma(beta, kp, kz);
     pnew[dof] = pown;
     q[dof] = y;
     dot = pown * y;
   }
-  const double tot = block_sum(dot, lds);
-  if (threadIdx.x == 0) ppq[(size_t)k * gridDim.x + blockIdx.x] = tot;
+  const double tot = wave_sum(dot);
+  if (lane == 0) ppq[3 * ((size_t)k * gridDim.x + blockIdx.x) + d] = tot;
 }
 
 __global__ __launch_bounds__(256) void k_cpcg_update(int n, const double* __restrict__ dinv,
@@ -1038,8 +1074,13 @@ __global__ __launch_bounds__(256) void k_cpcg_update(int n, const double* __rest
   const int i = in ? i0 : n - 1;
   const double xi = x[i], pi = p[i], qi = q[i], ri = r[i], di = dinv[i];
   const bool was_done = done[k] != 0;
-  const double pq = wave_total(ppq + (size_t)k * nba, nba);
-  const double rz = wave_total(prz + (size_t)k * gridDim.x, gridDim.x);
+  double tq = 0.0, tr = 0.0;               // fixed order: lane-strided, then the butterfly
+  for (int b = threadIdx.x & 63; b < nba; b += 64) {
+    const double* const v = ppq + 3 * ((size_t)k * nba + b);   // the rows of 64 nodes
+    tq += (v[0] + v[1]) + v[2];
+  }
+  for (int b = threadIdx.x & 63; b < (int)gridDim.x; b += 64) tr += prz[(size_t)k * gridDim.x + b];
+  const double pq = wave_sum(tq), rz = wave_sum(tr);
   if (was_done || !(pq > 0.0) || rz == 0.0) {         // uniform over the grid
     if (lead) done[k + 1] = 1;
     return;
@@ -1060,7 +1101,7 @@ __global__ __launch_bounds__(256) void k_cpcg_update(int n, const double* __rest
 
 size_t coarse_pcg_scratch(const Grid& g, int iters) {
   const size_t nbu = div_up(g.n, 256), nba = div_up(g.Nn, 64);
-  return (size_t)(iters + 1) * nbu + (size_t)iters * nba;
+  return (size_t)(iters + 1) * nbu + (size_t)iters * nba * 3;
 }
 
 void launch_coarse_pcg(const Grid& g, const double* S, const double* dinv, const uint8_t* fixn,
@@ -1071,9 +1112,18 @@ void launch_coarse_pcg(const Grid& g, const double* S, const double* dinv, const
   double* ppq = scratch + (size_t)(iters + 1) * nbu;
   k_cpcg_init<<<nbu, 256, 0, s>>>(g.n, b, dinv, x, r, z, prz, done);
   double* pp[2] = {p0, p1};
+  // the bands of both vectors: up to 48 KB, Nx <= 137 (a
+  // coarsest grid that long is rare; it keeps the strided loads)
+  const size_t bands = 2 * 9 * (size_t)cpcg_band(g) * sizeof(double);
+  const bool staged = bands <= 48 * 1024;
   for (int k = 0; k < iters; ++k) {
     const double* pold = k == 0 ? z : pp[(k + 1) & 1];
-    k_cpcg_apply<<<nba, 576, 0, s>>>(g, S, fixn, z, pold, pp[k & 1], q, prz, ppq, done, k, nbu);
+    if (staged)
+      k_cpcg_apply<true><<<dim3(nba, 3), 192, bands, s>>>(g, S, fixn, z, pold, pp[k & 1], q, prz,
+                                                          ppq, done, k, nbu);
+    else
+      k_cpcg_apply<false><<<dim3(nba, 3), 192, 0, s>>>(g, S, fixn, z, pold, pp[k & 1], q, prz, ppq,
+                                                       done, k, nbu);
     k_cpcg_update<<<nbu, 256, 0, s>>>(g.n, dinv, x, r, z, pp[k & 1], q, prz, ppq, done, k, nba);
   }
 }

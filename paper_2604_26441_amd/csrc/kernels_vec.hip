@@ -49,18 +49,18 @@ __global__ __launch_bounds__(kVecBlock) void k_dot(const double* __restrict__ a,
 // Second phase of every reduction: one block adds the block partials of
 // each of the nv sums in index order (fixed order: bitwise deterministic).
 __global__ __launch_bounds__(256) void k_finalize(const double* __restrict__ partials, int nblocks,
-                                                  int nv, double* __restrict__ out) {
+                                                  double* __restrict__ out) {
   __shared__ double lds[16];
-  for (int k = 0; k < nv; ++k) {
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nblocks; b += 256) s += partials[(size_t)k * nblocks + b];
-    s = block_sum(s, lds);
-    if (threadIdx.x == 0) out[k] = s;
-  }
+  const int k = blockIdx.x;                      // one block per value
+  double s = 0.0;
+#pragma unroll 4
+  for (int b = threadIdx.x; b < nblocks; b += 256) s += partials[(size_t)k * nblocks + b];
+  s = block_sum(s, lds);
+  if (threadIdx.x == 0) out[k] = s;
 }
 
 void launch_finalize(RedWs ws, int nblocks, int nv, double* out, hipStream_t s) {
-  k_finalize<<<1, 256, 0, s>>>(ws.partials, nblocks, nv, out);
+  k_finalize<<<nv, 256, 0, s>>>(ws.partials, nblocks, out);
 }
 
 static unsigned vec_grid(int n) {
