@@ -165,9 +165,83 @@ __global__ __launch_bounds__(256) void k_apply_fine_node(Grid g, const T* __rest
   }
 }
 
+// The same for meshes that leave most of the chip idle, where the launch lasts
+// as long as one thread's chain of 81 loads and 576 multiply-adds: 64 nodes per
+// block, wave q applies the element at their corner q (24 loads, 72
+// multiply-adds), then three waves add the eight products per DOF in the order
+// of the kernel above.  Same bits.  FP32: 9 x 9 x 17 nodes 3.3 us against 7.0,
+// 33^3 nodes 4.5 against 7.4, 65^3 nodes 13.9 against 17.3; FP64: 3.8 against
+// 8.5, 6.3 against 9.0.
+// Larger meshes fill the chip either way and the 27-node gather needs fewer
+// loads: the lines lie where the two meet (FP32 81^3 nodes 25.8 and 26.4 us,
+// 101^3 46.5 and 45.1; FP64 41^3 nodes 8.8 and 10.0, 51^3 13.4 and 12.0).
+template <typename T>
+constexpr int kSplitNodes = sizeof(T) == 4 ? 400000 : 100000;
+
+template <typename T>
+__global__ __launch_bounds__(512) void k_apply_fine_node8(Grid g, const T* __restrict__ E,
+                                                          const T* __restrict__ ke,
+                                                          const T* __restrict__ u,
+                                                          const uint8_t* __restrict__ fixn,
+                                                          Epi<T> ep) {
+  __shared__ T prod[8][3][64];
+  __shared__ T mod[8][64];
+  const int lane = threadIdx.x & 63;
+  const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int node = min((int)(blockIdx.x * 64 + lane), g.Nn - 1);
+  const int i = node % g.Nx, t = node / g.Nx, j = t % g.Ny, k = t / g.Ny;
+  const int ex = i - 1 + (q & 1), ey = j - 1 + ((q >> 1) & 1), ez = k - 1 + (q >> 2);
+  const bool ok = (unsigned)ex < (unsigned)g.nx && (unsigned)ey < (unsigned)g.ny &&
+                  (unsigned)ez < (unsigned)g.nz;
+  // an element outside the grid reads one inside and counts as zero
+  const int cx = min(max(ex, 0), g.nx - 1), cy = min(max(ey, 0), g.ny - 1);
+  const int cz = min(max(ez, 0), g.nz - 1);
+  T uv[8][3];
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const T* un = u + 3 * (size_t)(cx + (b & 1) + g.Nx * (cy + ((b >> 1) & 1) + g.Ny * (cz + (b >> 2))));
+#pragma unroll
+    for (int c = 0; c < 3; ++c) uv[b][c] = un[c];
+  }
+  const T Ee = E[cx + g.nx * (cy + g.ny * cz)];
+  const size_t dof = 3 * (size_t)node + q;               // waves 0 .. 2
+  Epi1In<T> ein{};
+  T xo = (T)0;
+  unsigned fx = 0;
+  if (q < 3) {
+    ein = epilogue1_load(ep, dof);
+    xo = u[dof];
+    fx = fixn[node];
+  }
+  const T* const kr = ke + (7 - q) * 72;                 // rows of the node's local index
+  T s0 = (T)0, s1 = (T)0, s2 = (T)0;
+#pragma unroll
+  for (int b = 0; b < 8; ++b)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      s0 += kr[3 * b + c] * uv[b][c];
+      s1 += kr[24 + 3 * b + c] * uv[b][c];
+      s2 += kr[48 + 3 * b + c] * uv[b][c];
+    }
+  mod[q][lane] = ok ? Ee : (T)0;
+  prod[q][0][lane] = ok ? s0 : (T)0;
+  prod[q][1][lane] = ok ? s1 : (T)0;
+  prod[q][2][lane] = ok ? s2 : (T)0;
+  __syncthreads();
+  if (q >= 3 || (int)(blockIdx.x * 64 + lane) >= g.Nn) return;
+  T acc = (T)0;
+#pragma unroll
+  for (int p = 0; p < 8; ++p) acc += mod[p][lane] * prod[p][q][lane];
+  epilogue1(ep, dof, (fx >> q) & 1u, xo, (double)acc, ein);
+}
+
 template <typename T>
 void launch_apply_fine_node(const Grid& g, const T* E, const T* ke, const T* u,
                             const uint8_t* fixn, const Epi<T>& ep, hipStream_t s) {
+  if (!ep.want_dot && g.Nn <= kSplitNodes<T>) {
+    k_apply_fine_node8<T><<<div_up(g.Nn, 64), 512, 0, s>>>(g, E, ke, u, fixn, ep);
+    return;
+  }
   k_apply_fine_node<T><<<div_up(g.Nn, 256), 256, 0, s>>>(g, E, ke, u, fixn, ep);
   if (ep.want_dot && ep.dot_out) launch_finalize(ep.ws, div_up(g.Nn, 256), 1, ep.dot_out, s);
 }
