@@ -24,8 +24,8 @@
 // exact arithmetic; in FP64 it rounds differently from the dense product
 // (relative 1e-16 per entry).
 //
-// Work decomposition: one wave owns a tile of 16 elements in x (lane & 15)
-// by 4 element rows in y (lane >> 4) and marches along z over a chunk of
+// Work decomposition: one wave owns a tile of 16 elements in x by 4 element
+// rows in y, or 8 by 8 (sf_launch takes the one that needs fewer tiles), and marches along z over a chunk of
 // node planes, which it stages in its own LDS ring (no barrier, nothing
 // shared between waves).  Each lane computes one element per plane and owns
 // its (-x, -y, -z) node.  Along z the transform is split: a node face is
@@ -33,9 +33,9 @@
 // face of one element and the bottom face of the next), and on the output
 // side the top face's contribution is carried in the same (x, y) basis and
 // added to the next element's bottom face before one inverse transform per
-// plane.  x sums come from lane n - 1 by a DPP row shift, y sums from lane
-// - 16 by ds_bpermute.  One halo element on the low side of x and y is
-// recomputed, so the tile owns 15 x 3 nodes per plane; every node sums its
+// plane.  x sums come from lane n - 1 by a DPP row shift, y sums from the
+// lane of the row below by ds_bpermute.  One halo element on the low side of x and y is
+// recomputed, so the tile owns 15 x 3 (7 x 7) nodes per plane; every node sums its
 // eight element contributions in the same order whatever the chunk length.
 #include <algorithm>
 
@@ -49,9 +49,14 @@ namespace sgmg {
 namespace {
 
 constexpr int kSfWaves = 4;                  // waves per block
-constexpr int kSfRow = 17 * 24;              // 17 nodes x 3 doubles
-constexpr int kSfPlane = 5 * kSfRow;         // node rows 0 .. 4 of the tile
-constexpr int kSfWave = 3 * kSfPlane;        // ring of three node planes
+template <int LX>                            // elements in x per wave: 16 or 8
+struct SfTile {
+  static constexpr int LY = 64 / LX;         // element rows
+  static constexpr int Row = (LX + 1) * 24;  // LX + 1 nodes x 3 doubles
+  static constexpr int Plane = (LY + 1) * Row;
+  static constexpr int Wave = 3 * Plane;     // ring of three node planes
+  static constexpr int Rows = 64 / (LX + 1); // node rows per load (two loads)
+};
 
 struct SfCoef {
   double a;    // lam / 16: (x_u, y_v, z_w) sum
@@ -258,21 +263,23 @@ __device__ __forceinline__ void l1_element(const double (&F0)[3][2][2], const do
 // level-1 Galerkin operator on the coarse grid g (E: the eight child moduli
 // of each coarse element, zero for coarse elements the product does not
 // cover; nodes with skip[node] != 0 are left to another kernel).
-template <int MODE, bool L1>
+template <int MODE, bool L1, int LX>
 __device__ __forceinline__ void fine_sf64_body(Grid g, const double* __restrict__ E, SfCoef cf,
                                                const double* __restrict__ u,
                                                const uint8_t* __restrict__ fixn,
                                                const uint8_t* __restrict__ skip, Epi<double> ep,
                                                int zchunk, int ntx, int nty, int ntiles,
                                                int blk) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds_all[kSfWaves * kSfWave];
+  __shared__ __attribute__((aligned(16))) unsigned char lds_all[kSfWaves * SfTile<LX>::Wave];
+  constexpr int kSfRow = SfTile<LX>::Row, kSfPlane = SfTile<LX>::Plane, kRows = SfTile<LX>::Rows;
+  constexpr int LY = SfTile<LX>::LY;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  unsigned char* const lds = lds_all + wave * kSfWave;
+  unsigned char* const lds = lds_all + wave * SfTile<LX>::Wave;
   const int tile = blk * kSfWaves + wave;
   const int tx = tile % ntx, tt = tile / ntx, ty = tt % nty, tz = tt / nty;
-  const int gr = lane >> 4, n = lane & 15;
-  const int xs = tx * 15, ys = ty * 3, zs = tz * zchunk;
+  const int gr = lane / LX, n = lane % LX;
+  const int xs = tx * (LX - 1), ys = ty * (LY - 1), zs = tz * zchunk;
   const int ex = xs - 1 + n, ey = ys - 1 + gr;
   const int zend = tile < ntiles ? min(zs + zchunk, g.Nz) : zs - 1;
   const size_t nvec = (size_t)g.n * sizeof(double);
@@ -292,31 +299,31 @@ __device__ __forceinline__ void fine_sf64_body(Grid g, const double* __restrict_
   auto off2 = [](int a, int b) { return (int)((unsigned)a + (unsigned)b); };
   auto part = [](bool ok, int v) { return ok ? v : kPoison; };
 
-  // node planes: load i, lane l < 51 carries node xs - 1 + l % 17 of node
-  // row k = 3 i + l / 17 (rows 0 .. 4 of the tile)
-  const int um = lane % 17, uk = lane / 17;
+  // node planes: load i, lane l carries node xs - 1 + l % (LX + 1) of node row
+  // k = kRows i + l / (LX + 1) (rows 0 .. LY of the tile)
+  const int um = lane % (LX + 1), uk = lane / (LX + 1);
   int u_lane[2];
   bool u_on[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const int k = 3 * i + uk;
-    u_on[i] = lane < 51 && k <= 4;
+    const int k = kRows * i + uk;
+    u_on[i] = uk < kRows && k <= LY;
     u_lane[i] = part(u_on[i] && (unsigned)(xs - 1 + um) < (unsigned)g.Nx &&
                          (unsigned)(ys - 1 + k) < (unsigned)g.Ny,
                      24 * (xs - 1 + um + g.Nx * (ys - 1 + k)));
   }
   double uv[2][3];
-  auto load_u = [&](int P, bool need) {
+  auto load_u = [&](int P, bool need, double (&uv)[2][3]) {
     const int pp = part(need && (unsigned)P < (unsigned)g.Nz, 24 * g.Nx * g.Ny * P);
 #pragma unroll
     for (int i = 0; i < 2; ++i) bload3(ru, off2(u_lane[i], pp), uv[i]);
   };
-  auto store_u = [&](int P) {
+  auto store_u = [&](int P, const double (&uv)[2][3]) {
     unsigned char* const slot = lds + ((P + 3) % 3) * kSfPlane + uk * kSfRow + um * 24;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       if (u_on[i]) {
-        double* q = (double*)(slot + 3 * i * kSfRow);
+        double* q = (double*)(slot + kRows * i * kSfRow);
         q[0] = uv[i][0];
         q[1] = uv[i][1];
         q[2] = uv[i][2];
@@ -367,7 +374,7 @@ __device__ __forceinline__ void fine_sf64_body(Grid g, const double* __restrict_
   };
 
   double dot = 0.0;
-  const int up = 4 * ((lane + 48) & 63);          // lane - 16 (group gr - 1)
+  const int up = 4 * ((lane + 64 - LX) & 63);     // lane - LX (group gr - 1)
   // node face of this lane's element on plane P: nodes (n + dx, gr + dy)
   double xown[3];                                  // node (n, gr) of the face
   auto read_face = [&](int P, double (&F)[3][2][2]) {
@@ -395,19 +402,29 @@ __device__ __forceinline__ void fine_sf64_body(Grid g, const double* __restrict_
     for (int cx = 0; cx < 2; ++cx)
 #pragma unroll
       for (int cy = 0; cy < 2; ++cy) Pc[c][cx][cy] = 0.0;
-  load_u(zs - 1, true);
-  store_u(zs - 1);
-  load_u(zs, true);
-  store_u(zs);
-  load_u(zs + 1, zs + 1 <= zend);
-  load_e(zs - 1, true);
+  if constexpr (L1) {
+    load_u(zs - 1, true, uv);
+    store_u(zs - 1, uv);
+    load_u(zs, true, uv);
+    store_u(zs, uv);
+    load_u(zs + 1, zs + 1 <= zend, uv);
+    load_e(zs - 1, true);
+  } else {  // the first planes in flight together (the level-1 product has no registers left)
+    double ua[2][3], ub[2][3];
+    load_u(zs - 1, true, ua);
+    load_u(zs, true, ub);
+    load_e(zs - 1, true);
+    load_u(zs + 1, zs + 1 <= zend, uv);
+    store_u(zs - 1, ua);
+    store_u(zs, ub);
+  }
   read_face(zs - 1, F0);
   for (int ez = zs - 1; ez < zend; ++ez) {
-    store_u(ez + 2);                               // loaded during the previous plane
+    store_u(ez + 2, uv);                             // loaded during the previous plane
     double esc[NEv];
 #pragma unroll
     for (int q = 0; q < NEv; ++q) esc[q] = ev[q];
-    load_u(ez + 3, ez + 3 <= zend);
+    load_u(ez + 3, ez + 3 <= zend, uv);
     load_e(ez + 1, ez + 1 < zend);
     load_v(ez);
     double x[3] = {xown[0], xown[1], xown[2]};     // the owned node's input (plane ez)
@@ -434,7 +451,7 @@ __device__ __forceinline__ void fine_sf64_body(Grid g, const double* __restrict_
       face_bwd(P, w);
       const double x0 = w[0][0] + dpp_shr1(w[1][0]);   // dx = 1 of lane n - 1
       const double x1 = w[0][1] + dpp_shr1(w[1][1]);
-      y[c] = x0 + bpermute(up, x1);                    // dy = 1 of lane - 16
+      y[c] = x0 + bpermute(up, x1);                    // dy = 1 of lane - LX
     }
     const int o = off2(o_lane, part(ez >= zs && ez < zend && sv == 0, 24 * g.Nx * g.Ny * ez));
     const bool mine = (unsigned)o < (unsigned)kPoison;
@@ -471,11 +488,11 @@ __device__ __forceinline__ void fine_sf64_body(Grid g, const double* __restrict_
   }
 }
 
-template <int MODE>
+template <int MODE, int LX>
 __global__ __launch_bounds__(64 * kSfWaves) void k_apply_fine_sf64(
     Grid g, const double* __restrict__ E, SfCoef cf, const double* __restrict__ u,
     const uint8_t* __restrict__ fixn, Epi<double> ep, int zchunk, int ntx, int nty, int ntiles) {
-  fine_sf64_body<MODE, false>(g, E, cf, u, fixn, nullptr, ep, zchunk, ntx, nty, ntiles,
+  fine_sf64_body<MODE, false, LX>(g, E, cf, u, fixn, nullptr, ep, zchunk, ntx, nty, ntiles,
                               xcd_block(blockIdx.x, gridDim.x));
 }
 
@@ -507,7 +524,7 @@ __device__ inline void l1_list_row(const Grid& g, const double* __restrict__ Sd,
 }
 
 // Blocks [0, nlb): the listed rows; the rest: the element-product tiles.
-template <int MODE>
+template <int MODE, int LX>
 __global__ __launch_bounds__(64 * kSfWaves) void k_apply_l1_haar(
     Grid g, const double* __restrict__ E8, SfCoef cf, const double* __restrict__ u,
     const uint8_t* __restrict__ fixn, const uint8_t* __restrict__ skip, Epi<double> ep, int zchunk,
@@ -518,7 +535,7 @@ __global__ __launch_bounds__(64 * kSfWaves) void k_apply_l1_haar(
     return;
   }
   const int nt = gridDim.x - nlb;
-  fine_sf64_body<MODE, true>(g, E8, cf, u, fixn, skip, ep, zchunk, ntx, nty, ntiles,
+  fine_sf64_body<MODE, true, LX>(g, E8, cf, u, fixn, skip, ep, zchunk, ntx, nty, ntiles,
                              xcd_block(blockIdx.x - nlb, nt));
 }
 
@@ -541,18 +558,32 @@ __global__ __launch_bounds__(64 * kSfWaves) void k_bs_fine_sf64(
   ep.out = I.q;
   ep.want_dot = 1;
   ep.ws.partials = part;
-  fine_sf64_body<kStoreDot, false>(V.g, S.E64, sf_coef(S.lam, S.mu), I.p, V.fixn, nullptr, ep,
+  fine_sf64_body<kStoreDot, false, 16>(V.g, S.E64, sf_coef(S.lam, S.mu), I.p, V.fixn, nullptr, ep,
                                    zchunk, gm.x, gm.y, gm.z, e.y);
 }
 
-struct SfLaunch { int ntx, nty, ntiles, blocks; };
-SfLaunch sf_launch(const Grid& g, int zchunk) {
+struct SfLaunch { int lx, ntx, nty, ntiles, blocks; };
+SfLaunch sf_launch(const Grid& g, int zchunk, int lx) {
   SfLaunch m;
-  m.ntx = div_up(g.Nx, 15);
-  m.nty = div_up(g.Ny, 3);
+  m.lx = lx;
+  m.ntx = div_up(g.Nx, lx - 1);
+  m.nty = div_up(g.Ny, 64 / lx - 1);
   m.ntiles = m.ntx * m.nty * div_up(g.Nz, zchunk);
   m.blocks = div_up(m.ntiles, kSfWaves);
   return m;
+}
+// Tiles of 16 x 4 or 8 x 8 elements, whichever takes fewer for the grid: the
+// owned nodes are 15 x 3 (70 % of the lanes) or 7 x 7 (77 %), less what the
+// grid's edges leave empty (31 x 31 nodes: 33 tiles or 25).  Every node sums
+// its eight elements in the same order with both.  A wave computes a plane in
+// 1.75 us at level 1 (1040 FP64 instructions; 0.75 us at the fine level), and a
+// level-1 wave has a SIMD to itself, so the time goes in steps of blocks per
+// compute unit: level 1 of 80^3 took 10.3 us (3 planes per wave; with 2 the
+// blocks did not fit in one round, 15.6 us), now 8.8 us with 2; the fine product
+// of 80^3 13.4 -> 12.5 us, of 200 x 100 x 50 22.6 -> 20.3 us.
+SfLaunch sf_launch(const Grid& g, int zchunk) {
+  const SfLaunch a = sf_launch(g, zchunk, 16), b = sf_launch(g, zchunk, 8);
+  return b.ntiles < a.ntiles ? b : a;
 }
 
 }  // namespace
@@ -620,12 +651,18 @@ void launch_apply_l1_haar(const Grid& c, int zchunk, const double* E8, double la
   const SfCoef cf = l1_coef(lam, mu);
   const int nlb = div_up(3 * std::max(nlist, 0), 64 * kSfWaves);
   const dim3 grid(nlb + m.blocks), block(64 * kSfWaves);
-#define SGMG_L1(M)                                                                          \
-  k_apply_l1_haar<M><<<grid, block, 0, s>>>(c, E8, cf, u, fixn, skip, ep, zchunk, m.ntx, m.nty, \
-                                            m.ntiles, Sd, list, nlist, nlb)
-  if (ep.mode == EPI_STORE) SGMG_L1(EPI_STORE);
-  else if (ep.mode == EPI_RESID) SGMG_L1(EPI_RESID);
-  else SGMG_L1(EPI_SMOOTH);
+#define SGMG_L1(M, LX)                                                                          \
+  k_apply_l1_haar<M, LX><<<grid, block, 0, s>>>(c, E8, cf, u, fixn, skip, ep, zchunk, m.ntx, m.nty, \
+                                                m.ntiles, Sd, list, nlist, nlb)
+  if (m.lx == 16) {
+    if (ep.mode == EPI_STORE) SGMG_L1(EPI_STORE, 16);
+    else if (ep.mode == EPI_RESID) SGMG_L1(EPI_RESID, 16);
+    else SGMG_L1(EPI_SMOOTH, 16);
+  } else {
+    if (ep.mode == EPI_STORE) SGMG_L1(EPI_STORE, 8);
+    else if (ep.mode == EPI_RESID) SGMG_L1(EPI_RESID, 8);
+    else SGMG_L1(EPI_SMOOTH, 8);
+  }
 #undef SGMG_L1
 }
 
@@ -640,30 +677,34 @@ void bs_fine_sf64_store_dot(const BsArgs& a, const BsTable& t, const int4* geo, 
 }
 
 size_t apply_fine_sf64_blocks(const Grid& g, int zchunk) {
-  return (size_t)sf_launch(g, zchunk < 1 ? 1 : zchunk).blocks;
+  return (size_t)sf_launch(g, zchunk < 1 ? 1 : zchunk, 16).blocks;
 }
 
 void launch_apply_fine_sf64(const Grid& g, int zchunk, const double* E, double lam, double mu,
                             const double* u, const uint8_t* fixn, const Epi<double>& ep,
                             hipStream_t s) {
   if (zchunk < 1) zchunk = 1;
-  const SfLaunch m = sf_launch(g, zchunk);
+  const bool dot = ep.mode == EPI_STORE && ep.want_dot;
+  // the dot's partials are those of the 16 x 4 tiles (apply_fine_sf64_blocks)
+  const SfLaunch m = dot ? sf_launch(g, zchunk, 16) : sf_launch(g, zchunk);
   const SfCoef cf = sf_coef(lam, mu);
   const dim3 grid(m.blocks), block(64 * kSfWaves);
-  if (ep.mode == EPI_STORE && ep.want_dot)
-    k_apply_fine_sf64<kStoreDot><<<grid, block, 0, s>>>(g, E, cf, u, fixn, ep, zchunk, m.ntx,
-                                                        m.nty, m.ntiles);
-  else if (ep.mode == EPI_STORE)
-    k_apply_fine_sf64<EPI_STORE><<<grid, block, 0, s>>>(g, E, cf, u, fixn, ep, zchunk, m.ntx,
-                                                        m.nty, m.ntiles);
-  else if (ep.mode == EPI_RESID)
-    k_apply_fine_sf64<EPI_RESID><<<grid, block, 0, s>>>(g, E, cf, u, fixn, ep, zchunk, m.ntx,
-                                                        m.nty, m.ntiles);
-  else
-    k_apply_fine_sf64<EPI_SMOOTH><<<grid, block, 0, s>>>(g, E, cf, u, fixn, ep, zchunk, m.ntx,
-                                                         m.nty, m.ntiles);
-  if (ep.mode == EPI_STORE && ep.want_dot && ep.dot_out)
-    launch_finalize(ep.ws, m.blocks, 1, ep.dot_out, s);
+#define SGMG_SF(M, LX)                                                                     \
+  k_apply_fine_sf64<M, LX><<<grid, block, 0, s>>>(g, E, cf, u, fixn, ep, zchunk, m.ntx, m.nty, \
+                                                  m.ntiles)
+  if (dot) {
+    SGMG_SF(kStoreDot, 16);
+    if (ep.dot_out) launch_finalize(ep.ws, m.blocks, 1, ep.dot_out, s);
+  } else if (m.lx == 16) {
+    if (ep.mode == EPI_STORE) SGMG_SF(EPI_STORE, 16);
+    else if (ep.mode == EPI_RESID) SGMG_SF(EPI_RESID, 16);
+    else SGMG_SF(EPI_SMOOTH, 16);
+  } else {
+    if (ep.mode == EPI_STORE) SGMG_SF(EPI_STORE, 8);
+    else if (ep.mode == EPI_RESID) SGMG_SF(EPI_RESID, 8);
+    else SGMG_SF(EPI_SMOOTH, 8);
+  }
+#undef SGMG_SF
 }
 
 }  // namespace sgmg
