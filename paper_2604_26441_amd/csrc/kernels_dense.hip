@@ -80,9 +80,8 @@ void launch_dense_add_diag(double* A, int nf, int ld, const double* mean_diag_su
 // Every element sees the same operations in the same order as with one full
 // update per block, so the split changes no bit of the result.
 // Measured per two pivot blocks at n = 3630: panels 10 + 11 us, cross 25 us (the
-// pivot's chain), the pass over A 85 us (2 x 46 us of matrix-core work or 43 us
-// of copy rate; 841 tiles leave a quarter-full last round); whole inverse 7.5
-// -> 3.9 ms. One launch each for column copy, pivot, row panel and update of a
+// pivot's chain), the pass over A 76 us (46 us of matrix-core work beside 43 us
+// of copy rate); whole inverse 7.5 -> 3.55 ms. One launch each for column copy, pivot, row panel and update of a
 // single block took 131 us per block. n = 1944: 2.7 -> 1.15 ms, n = 1344: 1.67 ->
 // 0.75 ms, both bound by the chain of pivots (25 us each with its tile).
 //
@@ -96,7 +95,7 @@ void launch_dense_add_diag(double* A, int nf, int ld, const double* mean_diag_su
 // ((8 g + t / 2) * 64 + l) * 2 + t % 2.
 typedef double f64x4_gj __attribute__((ext_vector_type(4)));
 constexpr int kLdP = 68;       // LDS pitch (doubles): 8 rows x 4 k of a wave in distinct banks
-constexpr int kUpdThreads = 1024;
+
 
 // The row panel (blocks 0 .. nb - 1, J) and the column panel (blocks nb ..
 // 2 nb - 1, I) of pivot block K.  Q: its inverse, 64 x 64, zero past nbw
@@ -205,36 +204,40 @@ __device__ inline double lane_value(double v, int l) {
                           __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
+template <int NW>
 struct PivotLds {
   double P[kNB][kNB + 1];
-  double g[2][4][kNB];         // 1 / a_pp in lane p, -a_rp / a_pp elsewhere, by parity
+  double g[2][kNB / NW][kNB];  // 1 / a_pp in lane p, -a_rp / a_pp elsewhere, by parity
 };
 
 // Inverse of the 64 x 64 block S.P by in-place Gauss-Jordan (SPD: no
-// pivoting), sixteen waves: lane r of wave w keeps columns 4 w .. 4 w + 3 of
+// pivoting), NW waves: lane r of wave w keeps the CW = 64 / NW columns CW w .. of
 // row r.  Pivot p:
 //   r == p : a_pc <- a_pc / a_pp (c != p),  a_pp <- 1 / a_pp
 //   r != p : a_rc <- a_rc - (a_rp / a_pp) a_pc (c != p),  a_rp <- -a_rp / a_pp
-// The wave that owns four pivot columns runs their four steps alone (row p
+// The wave that owns CW pivot columns runs their CW steps alone (row p
 // reaches the lanes through scalar registers), publishes the multipliers,
-// and after one barrier the other waves apply the four steps to their own
+// and after one barrier the other waves apply these steps to their own
 // columns in the same order; the next owner goes on with its own steps while
 // the others still apply.  Bound: the owners' chain, a division and the
-// columns of one wave per pivot, which is why each wave has only four.
+// columns of one wave per pivot: 22 us with 16 waves and four columns each,
+// taken where nothing hides it.
 // Writes Q, zero past nbw.
-__device__ inline void gj_pivot(PivotLds& S, int nbw, double* __restrict__ Q, int* __restrict__ flag) {
+template <int NW>
+__device__ inline void gj_pivot(PivotLds<NW>& S, int nbw, double* __restrict__ Q, int* __restrict__ flag) {
   const int r = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int CW = kNB / NW;
   __syncthreads();
-  double v[4];
+  double v[CW];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) v[c] = S.P[r][4 * w + c];
+  for (int c = 0; c < CW; ++c) v[c] = S.P[r][CW * w + c];
   bool bad = false;
-  for (int b = 0; b < 16; ++b) {
+  for (int b = 0; b < NW; ++b) {
     const int buf = b & 1;
     if (w == b) {
 #pragma unroll
-      for (int sp = 0; sp < 4; ++sp) {
-        const int p = 4 * b + sp;
+      for (int sp = 0; sp < CW; ++sp) {
+        const int p = CW * b + sp;
         const double pv = lane_value(v[sp], p);
         bad |= !(pv > 0.0);
         const double inv = 1.0 / pv;
@@ -242,7 +245,7 @@ __device__ inline void gj_pivot(PivotLds& S, int nbw, double* __restrict__ Q, in
         const double g = v[sp] * inv;            // a_rp / a_pp
         const double f = me ? inv : -g;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < CW; ++c) {
           if (c == sp) continue;
           v[c] = __builtin_fma(f, lane_value(v[c], p), me ? 0.0 : v[c]);
         }
@@ -253,23 +256,23 @@ __device__ inline void gj_pivot(PivotLds& S, int nbw, double* __restrict__ Q, in
     __syncthreads();
     if (w != b) {
 #pragma unroll
-      for (int sp = 0; sp < 4; ++sp) {
-        const int p = 4 * b + sp;
+      for (int sp = 0; sp < CW; ++sp) {
+        const int p = CW * b + sp;
         const bool me = r == p;
         const double f = S.g[buf][sp][r];
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+        for (int c = 0; c < CW; ++c)
           v[c] = __builtin_fma(f, lane_value(v[c], p), me ? 0.0 : v[c]);
       }
     }
   }
   if (bad && r == 0) *flag = 1;
 #pragma unroll
-  for (int c = 0; c < 4; ++c) S.P[r][4 * w + c] = v[c];
+  for (int c = 0; c < CW; ++c) S.P[r][CW * w + c] = v[c];
   __syncthreads();
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int e = threadIdx.x + kUpdThreads * u, a = e / kNB, c = e % kNB;
+  for (int u = 0; u < kNB / NW; ++u) {
+    const int e = threadIdx.x + 64 * NW * u, a = e / kNB, c = e % kNB;
     Q[e] = a < nbw && c < nbw ? S.P[a][c] : 0.0;
   }
 }
@@ -338,27 +341,32 @@ __device__ inline void gj_tile(const double* __restrict__ A, int n, int ld, int 
       for (int i = 0; i < 4; ++i) out(i0 + 16 * q + 4 * i + lk, j0 + 16 * p + lr, v[q][p][i]);
 }
 
-// Update by the last `panels` panels (K, or K - 1 and K), a 128 x 128 tile per
-// block and 32 x 32 per wave.  cross: only row and column K + 1, blocks 1 ..
-// nj the row's tiles and nj + 1 .. 2 nj the column's; otherwise every tile
-// outside row and column K.  Block 0 forms and inverts pivot block K + 1 (left out of the tiles).
-__global__ __launch_bounds__(kUpdThreads) void k_gj_update(double* __restrict__ A, int n, int ld, int nb,
-                                                           int K, int panels, int cross,
-                                                           const double* __restrict__ CF,
-                                                           const double* __restrict__ RF,
-                                                           size_t panel_stride,
-                                                           double* __restrict__ Q,
-                                                           int* __restrict__ flag) {
-  __shared__ PivotLds S;
+// Update by the last `panels` panels (K, or K - 1 and K), 32 x 32 per wave.
+// cross: only row and column K + 1, blocks 1 .. nj the row's tiles and nj + 1 ..
+// 2 nj the column's; otherwise every tile outside row and column K.  Block 0
+// forms and inverts pivot block K + 1 (left out of the tiles).  NW = 16: tiles
+// of 128 x 128.  NW = 8: 128 x 64, so two blocks share a compute unit and one
+// loads while the other multiplies, and the last round of blocks is a smaller
+// part of the launch (see dense_spd_inverse).
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_gj_update(double* __restrict__ A, int n, int ld, int nb,
+                                                       int K, int panels, int cross,
+                                                       const double* __restrict__ CF,
+                                                       const double* __restrict__ RF,
+                                                       size_t panel_stride, double* __restrict__ Q,
+                                                       int* __restrict__ flag) {
+  constexpr int WC = NW / 4;                       // waves along the columns
+  __shared__ PivotLds<NW> S;
   const int w = threadIdx.x >> 6;
   if (blockIdx.x == 0) {
     if (K + 1 >= nb) return;
     const int k1 = (K + 1) * kNB;
-    gj_tile<1, 1>(A, n, ld, k1 + 16 * (w >> 2), k1 + 16 * (w & 3), panels, CF, RF, panel_stride,
-                  [&](int a, int b, double v) {
-                    S.P[a - k1][b - k1] = a < n && b < n ? v : (a == b ? 1.0 : 0.0);
-                  });
-    gj_pivot(S, min(kNB, n - k1), Q, flag);
+    for (int q = w; q < 16; q += NW)
+      gj_tile<1, 1>(A, n, ld, k1 + 16 * (q >> 2), k1 + 16 * (q & 3), panels, CF, RF, panel_stride,
+                    [&](int a, int b, double v) {
+                      S.P[a - k1][b - k1] = a < n && b < n ? v : (a == b ? 1.0 : 0.0);
+                    });
+    gj_pivot<NW>(S, min(kNB, n - k1), Q, flag);
     return;
   }
   const int nj = (nb + 1) / 2, t = blockIdx.x - 1, mid = (K + 1) / 2;
@@ -367,7 +375,8 @@ __global__ __launch_bounds__(kUpdThreads) void k_gj_update(double* __restrict__ 
     // each XCD's share is about one band of four tile rows, column by column:
     // its L2 keeps the band's C and streams R (all of both is 7.4 MB at n =
     // 3630, more than the 4 MB an XCD has)
-    const int u = xcd_block(t, nj * nj), band = u / (4 * nj), in = u - band * 4 * nj;
+    const int nc = NW == 16 ? nj : nb;             // tile columns
+    const int u = xcd_block(t, nj * nc), band = u / (4 * nc), in = u - band * 4 * nc;
     const int rows = min(4, nj - 4 * band);
     Ip = 4 * band + in % rows;
     Jp = in / rows;
@@ -376,7 +385,7 @@ __global__ __launch_bounds__(kUpdThreads) void k_gj_update(double* __restrict__ 
     Jp = t < nj ? t : mid;
     if (t >= nj && Ip == mid) return;              // among the row's tiles
   }
-  const int i0 = 128 * Ip + 32 * (w >> 2), j0 = 128 * Jp + 32 * (w & 3);
+  const int i0 = 128 * Ip + 32 * (w / WC), j0 = 32 * WC * Jp + 32 * (w % WC);
   const int I = i0 / kNB, J = j0 / kNB;
   if (I >= nb || J >= nb || I == K || J == K || (I == K + 1 && J == K + 1)) return;
   if (cross && I != K + 1 && J != K + 1) return;
@@ -400,17 +409,28 @@ int dense_spd_inverse(double* A, int n, int ld, double* scratch, int* d_flag, hi
     k_gj_panel<<<2 * nb, 256, 0, s>>>(A, n, ld, nb, K, Q, CF + m * ps, RF + m * ps);
   };
   auto update = [&](int K, int panels, int cross, int blocks) {
-    k_gj_update<<<1 + blocks, kUpdThreads, 0, s>>>(A, n, ld, nb, K, panels, cross, CF, RF, ps, Q, d_flag);
+    k_gj_update<16><<<1 + blocks, 1024, 0, s>>>(A, n, ld, nb, K, panels, cross, CF, RF, ps, Q, d_flag);
   };
-  update(-1, 0, 0, 0);                               // pivot block 0
+  auto cross = [&](int K, int panels, int blocks) { update(K, panels, 1, blocks); };
+  // Up to one tile of 128 x 128 per compute unit the launch lasts as long as
+  // its pivot, which sixteen waves invert fastest (n = 1944: 29 us, with eight
+  // 39 us); beyond that the tiles hide the pivot (n = 3630: 84 us with 128 x
+  // 128, 76 us with 128 x 64).
+  auto full = [&](int K, int panels) {
+    if (nj * nj <= 256)
+      update(K, panels, 0, nj * nj);
+    else
+      k_gj_update<8><<<1 + nj * nb, 512, 0, s>>>(A, n, ld, nb, K, panels, 0, CF, RF, ps, Q, d_flag);
+  };
+  cross(-1, 0, 0);                                   // pivot block 0
   for (int K = 0; K < nb; K += 2) {
     panel(K, 0);
     if (K + 1 < nb) {
-      update(K, 1, 1, 2 * nj);
+      cross(K, 1, 2 * nj);
       panel(K + 1, 1);
-      update(K + 1, 2, 0, nj * nj);
+      full(K + 1, 2);
     } else if (nb > 1) {
-      update(K, 1, 0, nj * nj);
+      full(K, 1);
     }
   }
   return 0;

@@ -34,6 +34,13 @@ def test_cycle_with_the_inverse_matches_the_oracle(dims):
     assert np.linalg.norm(z.cpu().numpy() - want) <= 2e-10 * np.linalg.norm(want)
 
 
+# 34 to 39 pivot blocks (the pass over the matrix with 128 x 64 tiles): an even
+# and an odd number, with and without a remainder
+@pytest.mark.parametrize("dims", [(22, 14, 16), (26, 14, 14), (24, 14, 14), (26, 13, 15)])
+def test_cycle_with_a_larger_inverse_matches_the_oracle(dims):
+    test_cycle_with_the_inverse_matches_the_oracle(dims)
+
+
 def test_non_positive_pivot_is_reported():
     import torch
     from paper_2604_26441_amd import simpgmg
