@@ -31,6 +31,7 @@ struct BSys {               // one system (its hierarchy's operators)
   int nL;
   const int* free_idx;
   const double* Ainv;      // rows ld_inv doubles apart
+  const double* Apack;     // its upper-triangle tiles
   int ld_inv;
 };
 
@@ -45,6 +46,7 @@ struct BItem {              // one (system, load case) solve and its work vector
   double* lx[8][2];
   double* lr[8];
   double* rc;
+  double* sym;              // staged solve: partial sums of the coarsest products
 };
 
 // Chebyshev (Saad 12.1) or damped-Jacobi coefficients of smoothing step k

@@ -31,7 +31,10 @@ struct BsArgs {
 };
 
 int bs_threads();
-int bs_coarse_rows();
+// Column tiles per entry of the coarsest products' table, and an item's doubles
+// of partial sums (BItem::sym).
+int bs_coarse_strip();
+size_t bs_coarse_partials(int nL);
 void bs_fine64_res(const BsArgs& a, const BsTable& t, const int* flags, double* part, hipStream_t s);
 void bs_fine64_store_dot(const BsArgs& a, const BsTable& t, const int* flags, double* part,
                          hipStream_t s);
@@ -49,10 +52,11 @@ void bs_smooth0(const BsArgs& a, const BsTable& t, const int* flags, int post, i
 void bs_resid0(const BsArgs& a, const BsTable& t, const int* flags, int cin, hipStream_t s);
 void bs_restrict(const BsArgs& a, const BsTable& t, const int* flags, int l, hipStream_t s);
 // Coarsest solves: the right-hand sides over the items' table tg, the products
-// over a table tm of (group, row block) entries, groups[g] = up to four items
-// of one system (-1 past the last).
-void bs_coarse(const BsArgs& a, const BsTable& tg, const BsTable& tm, const int4* groups,
-               const int* flags, hipStream_t s);
+// over a table tm of (group, row block << 16 | first column block) entries,
+// groups[g] = up to four items of one system (-1 past the last), and the sums
+// of their partials over the items' table ty (64 rows per block).
+void bs_coarse(const BsArgs& a, const BsTable& tg, const BsTable& tm, const BsTable& ty,
+               const int4* groups, const int* flags, hipStream_t s);
 void bs_prolong(const BsArgs& a, const BsTable& t, const int* flags, int l, int cfine, int ccoarse,
                 hipStream_t s);
 // Level 0 on the BF16X3 MFMA operator: the tile grid of a mesh for launch

@@ -58,6 +58,12 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
+// v of lane l (the same l in the whole wave), through scalar registers.
+__device__ inline double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
 // Sums v over the block (blockDim.x a multiple of 64, <= 1024).  Result valid
 // in thread 0.
 __device__ inline double block_sum(double v, double* lds /* >= 16 */) {

@@ -318,55 +318,124 @@ __global__ __launch_bounds__(kB) void k_bs_coarse_gather(const BSys* __restrict_
 }
 
 // x_c = Ainv r_c for the load cases of one system (group: up to four of its
-// items, -1 past the last): a block does kCoarseRows rows, each wave four of
-// them for all active items at once, coalesced along the rows, with
-// fixed-order wave sums.  Bound: reading the inverses, so a system's rows are
-// read once for its load cases, not once for each (84 items of 32 systems,
-// inverses of up to 121 MB: 148 -> 102 us per cycle on average, 867 MB at 4.7 TB/s
-// while all are active); an item's sums are the
-// same operations in the same order whichever items share the pass.
-constexpr int kCoarseRows = 16;
+// items, -1 past the last), from the upper-triangle tiles of the symmetric
+// inverse (64 x 64, row block by row block, zero past nL).  Bound: reading the
+// inverses, so every coefficient is read once for the rows and the columns it
+// stands for and for all load cases of its system.  A block does a strip of
+// kSymStrip tiles of row block I: a tile's column sums A_IJ^T x_I go out as
+// partials of row block J, the strip's row sums A_IJ x_J stay in registers
+// (lane = column) and are added across the lanes once, through the LDS.  The
+// sums of an item are the same operations in the same order whichever items
+// share the pass.  84 items of 32 systems, inverses of up to 121 MB, 867 MB in
+// all: reading the whole inverses took 148 us per cycle on average with a pass
+// per item, 102 us with one per group, now 67 + 7 us (120 us, 3.7 TB/s, while
+// all are active; x_I from the LDS instead of scalar registers: 165 us).
+constexpr int kSymStrip = 8;
+constexpr int kSymWaves = 8;
+constexpr int kSymRows = 64 / kSymWaves;     // of a tile, per wave
+
+struct SymLds {
+  double tile[64][65];
+  double red[2][kSymWaves][4][64];   // by parity: wave, load case, column
+};
+
+// Partials of an item: row sums of strip s of row block I at (I * strips + s) *
+// 64, then the column sums of tile t at t * 64.
+__device__ inline double* sym_cols(double* part, int nb) {
+  return part + (size_t)nb * ((nb + kSymStrip - 1) / kSymStrip) * 64;
+}
+__device__ inline int sym_tile(int I, int J, int nb) { return I * nb - I * (I - 1) / 2 + J - I; }
 
 template <int K>
-__device__ inline void coarse_rows(const BItem* __restrict__ items, const BSys& S,
-                                   const int (&id)[4], int i0) {
-  const int lane = threadIdx.x & 63, nL = S.nL;
+__device__ inline void coarse_strip(SymLds& L, const BItem* __restrict__ items, const BSys& S,
+                                    const int (&id)[4], int I, int J0) {
+  const int nL = S.nL, nb = (nL + 63) / 64, lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int J1 = min(J0 + kSymStrip, nb), strips = (nb + kSymStrip - 1) / kSymStrip;
   const double* rc[K];
+  double* part[K];
 #pragma unroll
-  for (int k = 0; k < K; ++k) rc[k] = items[id[k]].rc;
-  const double* row[4];
+  for (int c = 0; c < K; ++c) {
+    rc[c] = items[id[c]].rc;
+    part[c] = items[id[c]].sym;
+  }
+  const double* T = S.Apack + (size_t)sym_tile(I, J0, nb) * 4096 + 64 * kSymRows * w + lane;
+  double v[kSymRows], xJ[K], acc[kSymRows][K] = {};
 #pragma unroll
-  for (int r = 0; r < 4; ++r) row[r] = S.Ainv + (size_t)min(i0 + r, nL - 1) * S.ld_inv;
-  double s[4][K] = {};
-#pragma unroll 4
-  for (int j = lane; j < nL; j += 64) {
-    double x[K];
+  for (int k = 0; k < kSymRows; ++k) v[k] = T[64 * k];
 #pragma unroll
-    for (int k = 0; k < K; ++k) x[k] = rc[k][j];
+  for (int c = 0; c < K; ++c) xJ[c] = rc[c][min(64 * J0 + lane, nL - 1)];   // the tile is zero past nL
+  // x_I of the wave's rows in scalar registers (read from the LDS for every
+  // tile, they took as long as the tiles themselves)
+  double xI[kSymRows][K];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const double a = row[r][j];
+  for (int c = 0; c < K; ++c) {
+    const double x = 64 * I + lane < nL ? rc[c][64 * I + lane] : 0.0;
 #pragma unroll
-      for (int k = 0; k < K; ++k) s[r][k] += a * x[k];
+    for (int k = 0; k < kSymRows; ++k) xI[k][c] = lane_value(x, kSymRows * w + k);
+  }
+  auto waves_sum = [&](int buf, int c) {
+    double t = 0.0;
+#pragma unroll
+    for (int q = 0; q < kSymWaves; ++q) t += L.red[buf][q][c][lane];
+    return t;
+  };
+  for (int J = J0; J < J1; ++J) {
+    double vn[kSymRows], xn[K], pc[K] = {};
+    T += 4096;
+    if (J + 1 < J1) {
+#pragma unroll
+      for (int k = 0; k < kSymRows; ++k) vn[k] = T[64 * k];
+#pragma unroll
+      for (int c = 0; c < K; ++c) xn[c] = rc[c][min(64 * J + 64 + lane, nL - 1)];
     }
+#pragma unroll
+    for (int k = 0; k < kSymRows; ++k)
+#pragma unroll
+      for (int c = 0; c < K; ++c) pc[c] += v[k] * xI[k][c];
+    if (J != I) {                                  // uniform over the block
+#pragma unroll
+      for (int c = 0; c < K; ++c) L.red[J & 1][w][c][lane] = pc[c];
+    }
+#pragma unroll
+    for (int k = 0; k < kSymRows; ++k)
+#pragma unroll
+      for (int c = 0; c < K; ++c) acc[k][c] += v[k] * xJ[c];
+    if (J != I) {
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < K; ++c)
+        if (w == c) sym_cols(part[c], nb)[(size_t)sym_tile(I, J, nb) * 64 + lane] = waves_sum(J & 1, c);
+    }
+#pragma unroll
+    for (int k = 0; k < kSymRows; ++k) v[k] = vn[k];
+#pragma unroll
+    for (int c = 0; c < K; ++c) xJ[c] = xn[c];
   }
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    if (i0 + r >= nL) break;
-    const int dof = S.free_idx[i0 + r];
+  for (int c = 0; c < K; ++c) {
+    __syncthreads();
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const double v = wave_sum(s[r][k]);
-      if (lane == 0) items[id[k]].lx[S.L - 1][0][dof] = v;
-    }
+    for (int k = 0; k < kSymRows; ++k) L.tile[kSymRows * w + k][lane] = acc[k][c];
+    __syncthreads();
+    double t = 0.0;
+#pragma unroll
+    for (int q = 0; q < kSymRows; ++q) t += L.tile[lane][kSymRows * w + q];
+    L.red[0][w][c][lane] = t;
   }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < K; ++c)
+    if (w == c) part[c][((size_t)I * strips + (J0 - I) / kSymStrip) * 64 + lane] = waves_sum(0, c);
 }
 
-__global__ __launch_bounds__(kB) void k_bs_coarse_symv(const BSys* __restrict__ sys,
+// tab: (group, strip) with strip = row block * 65536 + first tile's column block
+__global__ __launch_bounds__(64 * kSymWaves, 4) void k_bs_coarse_symv(const BSys* __restrict__ sys,
                                                        const BItem* __restrict__ items,
                                                        const int2* __restrict__ tab,
                                                        const int4* __restrict__ groups,
                                                        const int* __restrict__ flags) {
+  __shared__ SymLds L;
   const int2 e = tab[blockIdx.x];
   const int4 g = groups[e.x];
   const int all[4] = {g.x, g.y, g.z, g.w};
@@ -381,12 +450,38 @@ __global__ __launch_bounds__(kB) void k_bs_coarse_symv(const BSys* __restrict__ 
     }
   if (K == 0) return;
   const BSys& S = sys[items[id[0]].sys];
-  const int i0 = e.y * kCoarseRows + 4 * (threadIdx.x >> 6);
-  if (i0 >= S.nL) return;
-  if (K == 1) coarse_rows<1>(items, S, id, i0);
-  else if (K == 2) coarse_rows<2>(items, S, id, i0);
-  else if (K == 3) coarse_rows<3>(items, S, id, i0);
-  else coarse_rows<4>(items, S, id, i0);
+  const int I = e.y >> 16, J0 = e.y & 65535;
+  if (K == 1) coarse_strip<1>(L, items, S, id, I, J0);
+  else if (K == 2) coarse_strip<2>(L, items, S, id, I, J0);
+  else if (K == 3) coarse_strip<3>(L, items, S, id, I, J0);
+  else coarse_strip<4>(L, items, S, id, I, J0);
+}
+
+// Row block I of an item: the row sums of its strips and the column sums of
+// the tiles above it, a wave every fourth, then the four waves in order.
+__global__ __launch_bounds__(kB) void k_bs_coarse_sum(const BSys* __restrict__ sys,
+                                                      const BItem* __restrict__ items,
+                                                      const int2* __restrict__ tab,
+                                                      const int* __restrict__ flags) {
+  __shared__ double red[4][64];
+  Slot sl;
+  if (!active_block(tab, flags, sl)) return;
+  const BItem& it = items[sl.item];
+  const BSys& S = sys[it.sys];
+  const int nL = S.nL, nb = (nL + 63) / 64, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int I = sl.lb, strips = (nb + kSymStrip - 1) / kSymStrip;
+  const int mine = (nb - I + kSymStrip - 1) / kSymStrip;
+  const double* const cols = sym_cols(it.sym, nb);
+  double t = 0.0;
+#pragma unroll 2
+  for (int s = w; s < mine; s += 4) t += it.sym[((size_t)I * strips + s) * 64 + lane];
+#pragma unroll 4
+  for (int J = w; J < I; J += 4) t += cols[(size_t)sym_tile(J, I, nb) * 64 + lane];
+  red[w][lane] = t;
+  __syncthreads();
+  const int i = 64 * I + lane;
+  if (w == 0 && i < nL)
+    it.lx[S.L - 1][0][S.free_idx[i]] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
 }
 
 // Prolongation and correction of level l from level l + 1.  ccoarse: buffer
@@ -458,10 +553,11 @@ void bs_resid0(const BsArgs& a, const BsTable& t, const int* flags, int cin, hip
 void bs_restrict(const BsArgs& a, const BsTable& t, const int* flags, int l, hipStream_t s) {
   if (t.n) k_bs_restrict<<<t.n, kB, 0, s>>>(a.sys, a.items, t.blk, flags, l);
 }
-void bs_coarse(const BsArgs& a, const BsTable& tg, const BsTable& tm, const int4* groups, const int* flags,
-               hipStream_t s) {
+void bs_coarse(const BsArgs& a, const BsTable& tg, const BsTable& tm, const BsTable& ty,
+               const int4* groups, const int* flags, hipStream_t s) {
   if (tg.n) k_bs_coarse_gather<<<tg.n, kB, 0, s>>>(a.sys, a.items, tg.blk, flags);
-  if (tm.n) k_bs_coarse_symv<<<tm.n, kB, 0, s>>>(a.sys, a.items, tm.blk, groups, flags);
+  if (tm.n) k_bs_coarse_symv<<<tm.n, 64 * kSymWaves, 0, s>>>(a.sys, a.items, tm.blk, groups, flags);
+  if (ty.n) k_bs_coarse_sum<<<ty.n, kB, 0, s>>>(a.sys, a.items, ty.blk, flags);
 }
 void bs_prolong(const BsArgs& a, const BsTable& t, const int* flags, int l, int cfine, int ccoarse,
                 hipStream_t s) {
@@ -469,7 +565,11 @@ void bs_prolong(const BsArgs& a, const BsTable& t, const int* flags, int l, int 
 }
 
 int bs_threads() { return kB; }
-int bs_coarse_rows() { return kCoarseRows; }
+int bs_coarse_strip() { return kSymStrip; }
+size_t bs_coarse_partials(int nL) {
+  const size_t nb = div_up(nL, 64);
+  return 64 * (nb * div_up((int)nb, kSymStrip) + nb * (nb + 1) / 2);
+}
 
 // ---------------------------------------------------------------------------
 // Device-side iteration control (the one-launch solve).  The tests are those

@@ -199,11 +199,6 @@ __global__ __launch_bounds__(256) void k_gj_panel(double* __restrict__ A, int n,
   }
 }
 
-__device__ inline double lane_value(double v, int l) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
-                          __builtin_amdgcn_readlane(__double2loint(v), l));
-}
-
 template <int NW>
 struct PivotLds {
   double P[kNB][kNB + 1];

@@ -2070,7 +2070,7 @@ struct sgmg_batch {
   struct Staged {
     bool ready = false;
     void* dmem = nullptr;
-    BsTable tv, ts[8], tr[8], tcg, tcm;
+    BsTable tv, ts[8], tr[8], tcg, tcm, tcy;
     const int4* groups = nullptr;  // items of one system that share a pass over its inverse
     BsTable tsc[8];                // levels >= 1: row-split stencil blocks
     BsTable tss[8];                // levels >= 1: LDS-staged stencil blocks
@@ -2181,6 +2181,7 @@ BSys make_bsys(const sgmg_hierarchy* h) {
   S.nL = h->nL;
   S.free_idx = h->free_idx;
   S.Ainv = h->Ainv;
+  S.Apack = h->Apack;
   S.ld_inv = dense_ld(h->nL);
   return S;
 }
@@ -2297,7 +2298,7 @@ void bs_vcycle(const sgmg_batch::Staged& st, const BsArgs& a, const int* flags, 
     bs_restrict(a, st.tr[l], flags, l, s);
     cur &= ~(1u << (l + 1));
   }
-  bs_coarse(a, st.tcg, st.tcm, st.groups, flags, s);
+  bs_coarse(a, st.tcg, st.tcm, st.tcy, st.groups, flags, s);
   for (int l = st.Lmax - 2; l >= 0; --l) {
     const int steps = l == 0 ? st.steps0 : st.stepsL;
     bs_prolong(a, st.ts[l], flags, l, cb(l), cb(l + 1), s);
@@ -2574,8 +2575,8 @@ int bs_prepare(sgmg_batch* b, int n, hipStream_t s) {
     hts.push_back(make([&](const BSys& S) { return S.L - 1 > l ? div_up(3 * S.lev[l + 1].g.Nn, TB) : 0; }));
   }
   hts.push_back(make([&](const BSys& S) { return div_up(S.nL, TB); }));               // tcg
-  // groups of up to four items of one system, in execution order, and the row
-  // blocks of each group
+  // groups of up to four items of one system, in execution order, and the
+  // strips of tiles of each group
   std::vector<int4> groups;
   {
     HT t;
@@ -2588,14 +2589,17 @@ int bs_prepare(sgmg_batch* b, int n, hipStream_t s) {
       if (it == open.end() || groups[it->second].w >= 0) {
         open[sys] = (int)groups.size();
         groups.push_back(int4{i, -1, -1, -1});
-        const int c = div_up(hsys[sys].nL, bs_coarse_rows());
-        for (int j = 0; j < c; ++j) t.blk.push_back(int2{(int)groups.size() - 1, j});
+        const int c = div_up(hsys[sys].nL, 64);
+        for (int I = 0; I < c; ++I)
+          for (int J = I; J < c; J += bs_coarse_strip())
+            t.blk.push_back(int2{(int)groups.size() - 1, (I << 16) | J});
       } else {
         int4& g = groups[it->second];
         (g.y < 0 ? g.y : g.z < 0 ? g.z : g.w) = i;
       }
     }
     hts.push_back(t);                                                                  // tcm
+    hts.push_back(make([&](const BSys& S) { return div_up(S.nL, 64); }));               // tcy
   }
   for (int l = 1; l < st.Lmax - 1; ++l) {                                                // tsc, tss
     hts.push_back(make([&](const BSys& S) { return S.L - 1 > l ? bs_stencil_blocks(S.lev[l].g) : 0; }));
@@ -2630,8 +2634,10 @@ int bs_prepare(sgmg_batch* b, int n, hipStream_t s) {
   const size_t scal_b = (size_t)n * kBsScalars * sizeof(double);
   const size_t flag_b = 2 * (size_t)n * sizeof(int);
   const size_t grp_b = groups.size() * sizeof(int4);
+  size_t sym_b = 0;                                  // partial sums of the coarsest products
+  for (int i = 0; i < n; ++i) sym_b += bs_coarse_partials(hsys[b->h_items[i].sys].nL) * sizeof(double);
   char* m = nullptr;
-  if (hipMalloc((void**)&m, bytes + part_b + scal_b + flag_b + grp_b + 1024) != hipSuccess) {
+  if (hipMalloc((void**)&m, bytes + part_b + scal_b + flag_b + grp_b + sym_b + 2048) != hipSuccess) {
     set_error("staged batch allocation failed");
     return SGMG_ENOMEM;
   }
@@ -2662,6 +2668,12 @@ int bs_prepare(sgmg_batch* b, int n, hipStream_t s) {
   at += (flag_b + 255) & ~(size_t)255;
   st.groups = (const int4*)(m + at);
   SGMG_HIP(hipMemcpyAsync(m + at, groups.data(), grp_b, hipMemcpyHostToDevice, s));
+  at += (grp_b + 255) & ~(size_t)255;
+  for (int i = 0; i < n; ++i) {
+    b->h_items[i].sym = (double*)(m + at);
+    at += bs_coarse_partials(hsys[b->h_items[i].sys].nL) * sizeof(double);
+  }
+  SGMG_HIP(hipMemcpyAsync(b->d_items, b->h_items.data(), n * sizeof(BItem), hipMemcpyHostToDevice, s));
   int k = 0;
   st.tv = dts[k++];
   for (int l = 0; l < st.Lmax - 1; ++l) {
@@ -2670,6 +2682,7 @@ int bs_prepare(sgmg_batch* b, int n, hipStream_t s) {
   }
   st.tcg = dts[k++];
   st.tcm = dts[k++];
+  st.tcy = dts[k++];
   for (int l = 1; l < st.Lmax - 1; ++l) {
     st.tsc[l] = dts[k++];
     st.tss[l] = dts[k++];
