@@ -83,6 +83,9 @@ void bs_fine_mfma64_store_dot(const BsArgs& a, const BsTable& t, const int4* geo
                               int rows, int zchunk, double* part, hipStream_t s);
 void bs_fine_sf64_store_dot(const BsArgs& a, const BsTable& t, const int4* geo, const int* flags,
                             int zchunk, double* part, hipStream_t s);
+// r = f - K u on the same tiles, with the (f.f, r.r) block partials.
+void bs_fine_sf64_res(const BsArgs& a, const BsTable& t, const int4* geo, const int* flags, int zchunk,
+                      double* part, hipStream_t s);
 
 // Device-side iteration control of the one-launch solve: per item the
 // status (-1 while iterating, else the sgmg_status), the iteration count, |f|,

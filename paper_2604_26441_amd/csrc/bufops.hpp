@@ -43,6 +43,7 @@ __device__ inline void bload3(__amdgpu_buffer_rsrc_t r, int off, double* v) {
 // FP64 vector ep.dot64 (the cycle's last step and the PCG's r.z in one pass).
 constexpr int kStoreDot = 3;
 constexpr int kSmoothDot = 4;
+constexpr int kResidDots = 5;   // EPI_RESID with the sums b.b and out.out
 
 __device__ inline void bstore3(__amdgpu_buffer_rsrc_t r, int off, float a, float b, float c) {
   typedef unsigned u32x3 __attribute__((ext_vector_type(3)));

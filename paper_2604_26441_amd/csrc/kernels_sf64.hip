@@ -288,7 +288,8 @@ __device__ __forceinline__ void fine_sf64_body(Grid g, const double* __restrict_
   const __amdgpu_buffer_rsrc_t re = make_rsrc(E, (size_t)g.nel * kEs);
   const __amdgpu_buffer_rsrc_t rfix = make_rsrc(fixn, (size_t)g.Nn);
   const __amdgpu_buffer_rsrc_t rskip = make_rsrc(skip, L1 ? (size_t)g.Nn : 0);
-  const __amdgpu_buffer_rsrc_t rb = make_rsrc(ep.b, MODE == EPI_RESID || MODE == EPI_SMOOTH ? nvec : 0);
+  constexpr bool kHasB = MODE == EPI_RESID || MODE == EPI_SMOOTH || MODE == kResidDots;
+  const __amdgpu_buffer_rsrc_t rb = make_rsrc(ep.b, kHasB ? nvec : 0);
   const __amdgpu_buffer_rsrc_t rdi = make_rsrc(ep.dinv, MODE == EPI_SMOOTH ? nvec : 0);
   const __amdgpu_buffer_rsrc_t rd = make_rsrc(ep.d, MODE == EPI_SMOOTH ? nvec : 0);
   const __amdgpu_buffer_rsrc_t rout = make_rsrc(ep.out, ep.out ? nvec : 0);   // NULL: stores dropped
@@ -355,7 +356,7 @@ __device__ __forceinline__ void fine_sf64_body(Grid g, const double* __restrict_
   const bool own_xy = n >= 1 && gr >= 1 && ex < g.Nx && ey < g.Ny;
   const int o_lane = part(own_xy, 24 * (ex + g.Nx * ey));
   const int f_lane = part(own_xy, ex + g.Nx * ey);
-  constexpr int NV = MODE == EPI_SMOOTH ? 3 : MODE == EPI_RESID ? 1 : 0;
+  constexpr int NV = MODE == EPI_SMOOTH ? 3 : kHasB ? 1 : 0;
   double vv[NV > 0 ? NV : 1][3];
   unsigned fv = 0, sv = 0;
   auto load_v = [&](int ez) {
@@ -368,12 +369,12 @@ __device__ __forceinline__ void fine_sf64_body(Grid g, const double* __restrict_
       bload3(rb, o, vv[0]);
       bload3(rdi, o, vv[1]);
       bload3(rd, ep.c1 != 0.0 ? o : kNoOffset, vv[2]);
-    } else if (MODE == EPI_RESID) {
+    } else if (kHasB) {
       bload3(rb, o, vv[0]);
     }
   };
 
-  double dot = 0.0;
+  double dot = 0.0, dot2 = 0.0;
   const int up = 4 * ((lane + 64 - LX) & 63);     // lane - LX (group gr - 1)
   // node face of this lane's element on plane P: nodes (n + dx, gr + dy)
   double xown[3];                                  // node (n, gr) of the face
@@ -463,8 +464,12 @@ __device__ __forceinline__ void fine_sf64_body(Grid g, const double* __restrict_
       if (MODE == EPI_STORE || MODE == kStoreDot) {
         out[c] = fixed ? 0.0 : y[c];
         if (MODE == kStoreDot && mine) dot += xo * out[c];
-      } else if (MODE == EPI_RESID) {
+      } else if (MODE == EPI_RESID || MODE == kResidDots) {
         out[c] = fixed ? 0.0 : vv[0][c] - y[c];
+        if (MODE == kResidDots && mine) {
+          dot += vv[0][c] * vv[0][c];
+          dot2 += out[c] * out[c];
+        }
       } else {
         const double r = vv[0][c] - y[c];
         dd[c] = fixed ? 0.0 : ep.c1 * vv[2][c] + ep.c2 * vv[1][c] * r;
@@ -485,6 +490,13 @@ __device__ __forceinline__ void fine_sf64_body(Grid g, const double* __restrict_
   if (MODE == kStoreDot) {
     const double vd[1] = {dot};
     grid_sum<1>(vd, ep.ws);
+  } else if (MODE == kResidDots) {               // (b.b, r.r) of each block
+    __shared__ double lds[2][16];
+    const double bb = block_sum(dot, lds[0]), rr = block_sum(dot2, lds[1]);
+    if (threadIdx.x == 0) {
+      ep.ws.partials[2 * (size_t)blockIdx.x] = bb;
+      ep.ws.partials[2 * (size_t)blockIdx.x + 1] = rr;
+    }
   }
 }
 
@@ -539,10 +551,12 @@ __global__ __launch_bounds__(64 * kSfWaves) void k_apply_l1_haar(
                              xcd_block(blockIdx.x - nlb, nt));
 }
 
-// Stage-batched outer q = K p with the p.q block partials: block b is entry
+// Stage-batched outer products of the items: q = K p with the p.q block
+// partials, or (RES) r = f - K u with those of (f.f, r.r).  Block b is entry
 // tab[b] = (item, block of the item's tile grid); geo[item] holds that grid
 // (ntx, nty, ntiles) for zchunk planes (the tiles of the MFMA operator with 4
 // rows).
+template <bool RES>
 __global__ __launch_bounds__(64 * kSfWaves) void k_bs_fine_sf64(
     const BSys* __restrict__ sys, const BItem* __restrict__ items, const int2* __restrict__ tab,
     const int4* __restrict__ geo, const int* __restrict__ flags, double* __restrict__ part,
@@ -554,12 +568,14 @@ __global__ __launch_bounds__(64 * kSfWaves) void k_bs_fine_sf64(
   const BLevel& V = S.lev[0];
   const int4 gm = geo[e.x];
   Epi<double> ep{};
-  ep.mode = EPI_STORE;
-  ep.out = I.q;
+  ep.mode = RES ? EPI_RESID : EPI_STORE;
+  ep.b = RES ? I.f : nullptr;
+  ep.out = RES ? I.r : I.q;
   ep.want_dot = 1;
   ep.ws.partials = part;
-  fine_sf64_body<kStoreDot, false, 16>(V.g, S.E64, sf_coef(S.lam, S.mu), I.p, V.fixn, nullptr, ep,
-                                   zchunk, gm.x, gm.y, gm.z, e.y);
+  fine_sf64_body<RES ? kResidDots : kStoreDot, false, 16>(V.g, S.E64, sf_coef(S.lam, S.mu),
+                                                          RES ? I.u : I.p, V.fixn, nullptr, ep,
+                                                          zchunk, gm.x, gm.y, gm.z, e.y);
 }
 
 struct SfLaunch { int lx, ntx, nty, ntiles, blocks; };
@@ -673,7 +689,13 @@ bool sf64_size_ok(const Grid& g) {
 void bs_fine_sf64_store_dot(const BsArgs& a, const BsTable& t, const int4* geo, const int* flags,
                             int zchunk, double* part, hipStream_t s) {
   if (t.n == 0) return;
-  k_bs_fine_sf64<<<t.n, 64 * kSfWaves, 0, s>>>(a.sys, a.items, t.blk, geo, flags, part, zchunk);
+  k_bs_fine_sf64<false><<<t.n, 64 * kSfWaves, 0, s>>>(a.sys, a.items, t.blk, geo, flags, part, zchunk);
+}
+
+void bs_fine_sf64_res(const BsArgs& a, const BsTable& t, const int4* geo, const int* flags, int zchunk,
+                      double* part, hipStream_t s) {
+  if (t.n == 0) return;
+  k_bs_fine_sf64<true><<<t.n, 64 * kSfWaves, 0, s>>>(a.sys, a.items, t.blk, geo, flags, part, zchunk);
 }
 
 size_t apply_fine_sf64_blocks(const Grid& g, int zchunk) {
