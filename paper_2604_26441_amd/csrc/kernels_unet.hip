@@ -147,12 +147,19 @@ __device__ inline void conv_zero(ConvAcc<COT> (&acc)[kCTY]) {
     for (int c = 0; c < COT; ++c) acc[r].hi[c] = acc[r].lo[c] = cf32x4{0.f, 0.f, 0.f, 0.f};
 }
 
-template <int COT>
+// SEQ: all three terms into one sum, smallest first (lo stays zero).
+template <int COT, bool SEQ = false>
 __device__ inline void mfma3(const uint4 (&a)[COT], const cbf16x8 b0, const cbf16x8 b1,
                              const cbf16x8 b2, ConvAcc<COT>& acc) {
 #pragma unroll
   for (int c = 0; c < COT; ++c) {
     const cbf16x8 av = __builtin_bit_cast(cbf16x8, a[c]);
+    if constexpr (SEQ) {
+      acc.hi[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b2, acc.hi[c], 0, 0, 0);
+      acc.hi[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b1, acc.hi[c], 0, 0, 0);
+      acc.hi[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b0, acc.hi[c], 0, 0, 0);
+      continue;
+    }
     acc.lo[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b2, acc.lo[c], 0, 0, 0);
     acc.hi[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b0, acc.hi[c], 0, 0, 0);
     acc.lo[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b1, acc.lo[c], 0, 0, 0);
@@ -237,9 +244,14 @@ __device__ inline void conv_store(const ConvAcc<COT> (&acc)[kCTY], const ConvOut
 // LDS read (8 cycles of the CU) outweighs the MFMA (16 cycles on each of four
 // SIMDs).  Measured, layers 1-4 on a 1 x 104^3 grid: 62, 35, 28, 47 us with every
 // stage's loads waited for -> 54, 32, 23, 33 us.
-template <int COT>
-__global__ __launch_bounds__(256) void k_conv3_mfma(const float* __restrict__ x, int Ci, int Co,
-                                                    int Cop, int D, int H, int W, int tx, int ty,
+// SEQ: the training pass's forward.  A ReLU's mask is a step function of the
+// value before it, so a mask that flips with the rounding moves the gradient by
+// 1e-5 and more (about one pass in fifteen); its sums keep one fixed order of the
+// terms, and the decoder's layers (up = 1: x stored at half resolution) the order
+// of this kernel.
+template <int COT, bool SEQ>
+__global__ __launch_bounds__(256) void k_conv3_mfma(const float* __restrict__ x, int up, int Ci,
+                                                    int Co, int Cop, int D, int H, int W, int tx, int ty,
                                                     const uint4* __restrict__ wp, ConvOut out) {
   constexpr int kPer = (kCHV + 255) / 256;
   __shared__ uint4 lds[3][kCHV];
@@ -250,8 +262,8 @@ __global__ __launch_bounds__(256) void k_conv3_mfma(const float* __restrict__ x,
   const int n = blockIdx.y, ct0 = blockIdx.z * COT;
   const int bx = tile % tx, by = (tile / tx) % ty, bz = tile / (tx * ty);
   const int x0 = bx * kCTX, y0 = by * kCTY, z0 = bz * kCTZ;
-  const size_t HW = (size_t)H * W, DHW = D * HW;
-  const float* xn = x + (size_t)n * Ci * DHW;
+  const size_t HWi = (size_t)(H >> up) * (W >> up), DHWi = (D >> up) * HWi;
+  const float* xn = x + (size_t)n * Ci * DHWi;
   const int nchunk = (Ci + 7) >> 3;
 
   unsigned voff[kPer];                       // this thread's halo voxels
@@ -262,13 +274,13 @@ __global__ __launch_bounds__(256) void k_conv3_mfma(const float* __restrict__ x,
     const int gx = x0 - 1 + v % kCHX, gy = y0 - 1 + (v / kCHX) % kCHY, gz = z0 - 1 + v / (kCHX * kCHY);
     vin[u] = v < kCHV && (unsigned)gx < (unsigned)W && (unsigned)gy < (unsigned)H &&
              (unsigned)gz < (unsigned)D;
-    voff[u] = vin[u] ? (unsigned)(gz * HW + (size_t)gy * W + gx) : 0u;
+    voff[u] = vin[u] ? (unsigned)((gz >> up) * HWi + (size_t)(gy >> up) * (W >> up) + (gx >> up)) : 0u;
   }
   float stage[kPer][8];
   auto load = [&](int ch) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const float* xc = xn + (size_t)min(8 * ch + j, Ci - 1) * DHW;
+      const float* xc = xn + (size_t)min(8 * ch + j, Ci - 1) * DHWi;
 #pragma unroll
       for (int u = 0; u < kPer; ++u) stage[u][j] = xc[voff[u]];
     }
@@ -292,8 +304,9 @@ __global__ __launch_bounds__(256) void k_conv3_mfma(const float* __restrict__ x,
 #pragma unroll
       for (int r = 0; r < kCTY; ++r) {
         const int v = base + r * kCHX;
-        mfma3<COT>(a, __builtin_bit_cast(cbf16x8, lds[0][v]), __builtin_bit_cast(cbf16x8, lds[1][v]),
-                   __builtin_bit_cast(cbf16x8, lds[2][v]), acc[r]);
+        mfma3<COT, SEQ>(a, __builtin_bit_cast(cbf16x8, lds[0][v]),
+                        __builtin_bit_cast(cbf16x8, lds[1][v]),
+                        __builtin_bit_cast(cbf16x8, lds[2][v]), acc[r]);
       }
     };
     // one channel tile: all of the chunk's weights are loaded before the
@@ -491,16 +504,38 @@ void launch_conv3_mfma(const float* x, int up, int N, int Ci, int Co, int D, int
   while (!up && cot < 4 && ntile % (2 * cot) == 0) cot *= 2;
   while (cot > 1 && tiles * N * (ntile / cot) < kConvBlocks) cot /= 2;
   dim3 grid((unsigned)tiles, N, ntile / cot);
-#define SGMG_CONV3(KERNEL) KERNEL<<<grid, 256, 0, s>>>(x, Ci, Co, Cop, D, H, W, tx, ty, wp, o)
   if (up) {
-    if (hw) SGMG_CONV3(k_conv3_up<true>);
-    else SGMG_CONV3(k_conv3_up<false>);
+    if (hw) k_conv3_up<true><<<grid, 256, 0, s>>>(x, Ci, Co, Cop, D, H, W, tx, ty, wp, o);
+    else k_conv3_up<false><<<grid, 256, 0, s>>>(x, Ci, Co, Cop, D, H, W, tx, ty, wp, o);
     return;
   }
+#define SGMG_CONV3(COT, SEQ) \
+  k_conv3_mfma<COT, SEQ><<<grid, 256, 0, s>>>(x, 0, Ci, Co, Cop, D, H, W, tx, ty, wp, o)
   switch (cot) {
-    case 4: SGMG_CONV3(k_conv3_mfma<4>); break;
-    case 2: SGMG_CONV3(k_conv3_mfma<2>); break;
-    default: SGMG_CONV3(k_conv3_mfma<1>); break;
+    case 4: SGMG_CONV3(4, false); break;
+    case 2: SGMG_CONV3(2, false); break;
+    default: SGMG_CONV3(1, false); break;
+  }
+#undef SGMG_CONV3
+}
+
+void launch_conv3_train(const float* x, int up, int N, int Ci, int Co, int D, int H, int W,
+                        const uint4* wp, const float* b, int relu, float* rpre, const float* add,
+                        float* y, hipStream_t s) {
+  const int Cop = (Co + kCOB - 1) / kCOB * kCOB, ntile = Cop / 16;
+  const int tx = div_up(W, kCTX), ty = div_up(H, kCTY), tz = div_up(D, kCTZ);
+  const long tiles = (long)tx * ty * tz;
+  const ConvOut o{b, relu, rpre, add, y, nullptr, nullptr, nullptr};
+  int cot = 1;                               // as above
+  while (cot < 4 && ntile % (2 * cot) == 0) cot *= 2;
+  while (cot > 1 && tiles * N * (ntile / cot) < kConvBlocks) cot /= 2;
+  const dim3 grid((unsigned)tiles, N, ntile / cot);
+#define SGMG_CONV3(COT, SEQ) \
+  k_conv3_mfma<COT, SEQ><<<grid, 256, 0, s>>>(x, up, Ci, Co, Cop, D, H, W, tx, ty, wp, o)
+  switch (cot) {
+    case 4: SGMG_CONV3(4, true); break;
+    case 2: SGMG_CONV3(2, true); break;
+    default: SGMG_CONV3(1, true); break;
   }
 #undef SGMG_CONV3
 }

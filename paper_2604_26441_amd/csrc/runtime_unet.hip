@@ -26,6 +26,7 @@ struct ULayer {
   size_t nw;                  // ci * k3 * cop
   float *w, *wq, *b, *gw, *gb, *mw, *vw, *mb, *vb, *wt;
   uint4 *wp = nullptr, *wpt = nullptr;   // packed matrix-core operands (3x3x3 layers)
+  uint4* wps = nullptr;                  // those of the training pass's forward (wp for the encoder)
 };
 
 }  // namespace
@@ -34,7 +35,8 @@ struct sgmg_unet {
   ULayer L[kNL];
   std::vector<void*> mem;
   int step = 0;
-  bool packed = false;        // wp holds the current BF16 weights
+  bool packed = false;        // wp holds the current BF16 weights,
+  bool packed_train = false;  // wps does
   // activation workspace for one (N, D, H, W)
   int aN = 0, aD = 0, aH = 0, aW = 0;
   std::vector<void*> act;
@@ -163,21 +165,25 @@ void upload_layer(const ULayer& L, const std::vector<float>& w_dev_layout, const
 
 // the 3x3x3 layers run on the matrix cores with packed weights, repacked
 // after every change of the BF16 weights
-void pack_weights(sgmg_unet* u, hipStream_t s) {
-  if (u->packed) return;
+void pack_weights(sgmg_unet* u, bool infer, hipStream_t s) {
+  bool& done = infer ? u->packed : u->packed_train;
+  if (done) return;
   for (int l = 0; l < kNL; ++l)
     if (u->L[l].k == 3)
-      launch_pack_conv3(u->L[l].wq, kUp[l], u->L[l].ci, u->L[l].co, u->L[l].wp, s);
-  u->packed = true;
+      launch_pack_conv3(u->L[l].wq, infer ? kUp[l] : 0, u->L[l].ci, u->L[l].co,
+                        infer ? u->L[l].wp : u->L[l].wps, s);
+  done = true;
 }
 
 // A decoder layer's x is its input at half resolution; the convolution reads
 // its nearest-neighbour upsampling, which is never stored.
-void conv(sgmg_unet* u, int l, const float* x, int N, int D, int H, int W, int relu, float* rpre,
-          const float* add, float* y, hipStream_t s) {
+void conv(sgmg_unet* u, bool infer, int l, const float* x, int N, int D, int H, int W, int relu,
+          float* rpre, const float* add, float* y, hipStream_t s) {
   const ULayer& L = u->L[l];
-  if (L.k == 3)
+  if (L.k == 3 && infer)
     launch_conv3_mfma(x, kUp[l], N, L.ci, L.co, D, H, W, L.wp, L.b, relu, rpre, add, y, s);
+  else if (L.k == 3)
+    launch_conv3_train(x, kUp[l], N, L.ci, L.co, D, H, W, L.wps, L.b, relu, rpre, add, y, s);
   else
     launch_conv_fwd(L.k, x, N, L.ci, L.co, D, H, W, L.wq, L.b, relu, rpre, add, y, s);
 }
@@ -189,24 +195,24 @@ void forward(sgmg_unet* u, int N, int D, int H, int W, const float* x, hipStream
              bool infer = false, float* out = nullptr) {
   const int D2 = D / 2, H2 = H / 2, W2 = W / 2, D3 = D / 4, H3 = H / 4, W3 = W / 4, D4 = D / 8,
             H4 = H / 8, W4 = W / 8;
-  pack_weights(u, s);
-  conv(u, 0, x, N, D, H, W, 1, nullptr, nullptr, u->r1, s);
+  pack_weights(u, infer, s);
+  conv(u, infer, 0, x, N, D, H, W, 1, nullptr, nullptr, u->r1, s);
   launch_pool(u->r1, N * 16, D, H, W, u->p1, s);
-  conv(u, 1, u->p1, N, D2, H2, W2, 1, nullptr, nullptr, u->r2, s);
+  conv(u, infer, 1, u->p1, N, D2, H2, W2, 1, nullptr, nullptr, u->r2, s);
   launch_pool(u->r2, N * 32, D2, H2, W2, u->p2, s);
-  conv(u, 2, u->p2, N, D3, H3, W3, 1, nullptr, nullptr, u->r3, s);
+  conv(u, infer, 2, u->p2, N, D3, H3, W3, 1, nullptr, nullptr, u->r3, s);
   launch_pool(u->r3, N * 64, D3, H3, W3, u->p3, s);
-  conv(u, 3, u->p3, N, D4, H4, W4, 1, nullptr, nullptr, u->r4, s);
-  conv(u, 4, u->r4, N, D3, H3, W3, 1, infer ? nullptr : u->r5, u->r3, u->d3, s);
-  conv(u, 5, u->d3, N, D2, H2, W2, 1, infer ? nullptr : u->r6, u->r2, u->d2, s);
+  conv(u, infer, 3, u->p3, N, D4, H4, W4, 1, nullptr, nullptr, u->r4, s);
+  conv(u, infer, 4, u->r4, N, D3, H3, W3, 1, infer ? nullptr : u->r5, u->r3, u->d3, s);
+  conv(u, infer, 5, u->d3, N, D2, H2, W2, 1, infer ? nullptr : u->r6, u->r2, u->d2, s);
   if (infer) {
     const ULayer& L = u->L[6];
     launch_conv3_mfma(u->d2, 1, N, L.ci, L.co, D, H, W, L.wp, L.b, 1, nullptr, u->r1, nullptr, s,
                       u->L[7].wq, u->L[7].b, out);
     return;
   }
-  conv(u, 6, u->d2, N, D, H, W, 1, u->r7, u->r1, u->d1, s);
-  conv(u, 7, u->d1, N, D, H, W, 0, nullptr, nullptr, u->y, s);
+  conv(u, infer, 6, u->d2, N, D, H, W, 1, u->r7, u->r1, u->d1, s);
+  conv(u, infer, 7, u->d1, N, D, H, W, 0, nullptr, nullptr, u->y, s);
 }
 
 // dx = data gradient of layer l: the convolution with the channels swapped
@@ -302,6 +308,8 @@ int sgmg_unet_create(uint64_t seed, sgmg_unet** out) {
       float* a = nullptr;
       rc = ualloc(u->mem, &a, 4 * conv3_packed_words(kUp[l], L.ci, L.co));
       L.wp = (uint4*)a;
+      if (!rc && kUp[l]) rc = ualloc(u->mem, &a, 4 * conv3_packed_words(0, L.ci, L.co));
+      L.wps = (uint4*)a;
       if (!rc) rc = ualloc(u->mem, &a, 4 * conv3_packed_words(0, L.co, L.ci));
       L.wpt = (uint4*)a;
     }
@@ -350,7 +358,7 @@ int sgmg_unet_set_params(sgmg_unet* u, const float* host, void* stream) {
     hipMemsetAsync(L.vb, 0, L.cop * sizeof(float), s);
   }
   u->step = 0;
-  u->packed = false;
+  u->packed = u->packed_train = false;
   if (hipStreamSynchronize(s) != hipSuccess) { set_err("sync failed"); return SGMG_EHIP; }
   return check();
 }
@@ -416,7 +424,7 @@ static int backward_and_step(sgmg_unet* u, int N, int D, int H, int W, const flo
       launch_adam(L.w, L.wq, L.gw, L.mw, L.vw, (long)L.nw, lr, 0.9f, 0.999f, 1e-8f, u->step, 1, s);
       launch_adam(L.b, nullptr, L.gb, L.mb, L.vb, L.co, lr, 0.9f, 0.999f, 1e-8f, u->step, 0, s);
     }
-    u->packed = false;
+    u->packed = u->packed_train = false;
   }
   return 0;
 }

@@ -57,6 +57,11 @@ void launch_conv3_mfma(const float* x, int up, int N, int Ci, int Co, int D, int
                        const uint4* wp, const float* b, int relu, float* rpre, const float* add,
                        float* y, hipStream_t s, const float* hw = nullptr,
                        const float* hb = nullptr, float* hy = nullptr);
+// The training pass's forward: one order of every sum, also with up = 1 (wp
+// packed with up 0).
+void launch_conv3_train(const float* x, int up, int N, int Ci, int Co, int D, int H, int W,
+                        const uint4* wp, const float* b, int relu, float* rpre, const float* add,
+                        float* y, hipStream_t s);
 void launch_weight_transpose(const float* w, int Ci, int Co, int K, float* wt, hipStream_t s);
 size_t conv_wgrad_part_floats(int N, int Ci, int Co, int D, int H, int W, int K);
 void launch_conv_wgrad(int K, const float* x, int up, const float* dy, int N, int Ci, int Co, int D,
