@@ -540,6 +540,43 @@ void launch_conv3_train(const float* x, int up, int N, int Ci, int Co, int D, in
 #undef SGMG_CONV3
 }
 
+// The same operands (up 0) for the data gradients, whose weights are w with the
+// channels swapped and the taps flipped, straight from w[(ci * 27 + tap) * Cop +
+// co]: all layers in one launch (a transposed copy and a pack per layer took
+// 12 launches of 4.6 us).
+__global__ void k_pack_conv3_flip(ConvPacks ps) {
+  int i = blockIdx.x * blockDim.x + threadIdx.x, l = 0;
+  while (l < ps.n && i >= ps.p[l].total) i -= ps.p[l++].total;
+  if (l == ps.n) return;
+  const ConvPacks::One& p = ps.p[l];
+  const int q = i & 3, ci = (i >> 2) % p.Cip, k = i / (4 * p.Cip);
+  const int t = 4 * (k % kCSteps) + q, c0 = 8 * (k / kCSteps);
+  unsigned v[4];
+#pragma unroll
+  for (int j = 0; j < 8; j += 2) {
+    float f[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int co = c0 + j + h;
+      f[h] = t < 27 && co < p.Co && ci < p.Ci ? p.w[((size_t)ci * 27 + 26 - t) * p.Cop + co] : 0.f;
+    }
+    v[j >> 1] = (__float_as_uint(f[0]) >> 16) | (__float_as_uint(f[1]) & 0xffff0000u);
+  }
+  p.wp[i] = uint4{v[0], v[1], v[2], v[3]};
+}
+
+void launch_pack_conv3_flip(ConvPacks ps, hipStream_t s) {
+  long total = 0;
+  for (int l = 0; l < ps.n; ++l) {
+    ConvPacks::One& p = ps.p[l];
+    p.Cop = (p.Co + kCOB - 1) / kCOB * kCOB;
+    p.Cip = (p.Ci + kCOB - 1) / kCOB * kCOB;
+    p.total = (int)conv3_packed_words(0, p.Co, p.Ci);
+    total += p.total;
+  }
+  k_pack_conv3_flip<<<div_up(total, 256), 256, 0, s>>>(ps);
+}
+
 // Weights for the data gradient: wt[(co * K3 + (K3 - 1 - t)) * Cip + ci] =
 // w[(ci * K3 + t) * Cop + co]  (channels swapped, taps flipped).
 __global__ void k_weight_transpose(const float* __restrict__ w, int Ci, int Co, int Cop, int K3,
@@ -607,7 +644,15 @@ __global__ void k_conv1_wgrad_sum(const float* __restrict__ part, int nchunks, i
   if (i >= Ci * nq * 8) return;
   const int j = i % 8, q = (i / 8) % nq, ci = i / (8 * nq);
   float s = 0.f;
-  for (int c = 0; c < nchunks; ++c) s += part[(((size_t)c * Ci + ci) * nq + q) * 8 + j];
+  for (int c0 = 0; c0 < nchunks; c0 += 16) {       // sixteen loads together, the adds in order
+    float v[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c)
+      v[c] = part[(((size_t)min(c0 + c, nchunks - 1) * Ci + ci) * nq + q) * 8 + j];
+#pragma unroll
+    for (int c = 0; c < 16; ++c)
+      if (c0 + c < nchunks) s += v[c];
+  }
   const int co = q * 4 + (j & 3);
   if (co >= Co) return;
   if (j < 4) dw[(size_t)ci * Cop + co] = s;
@@ -636,9 +681,15 @@ __global__ void k_conv1_wgrad_sum(const float* __restrict__ part, int nchunks, i
 // read a step ahead.
 // Measured, 8 samples of a 32^3 mesh (40^3 voxels), seven layers: 2565 us
 // (vector ALU, one input and four output channels per block, 31 neighbour
-// loads per voxel) -> 684 us, the sums 118 -> 42 us.
+// loads per voxel) -> 639 us, the sums 118 -> 42 us.
 constexpr int kWgPitch = 17;
 
+//
+// NC = 5 (at most five input channels): a column is (channel, x tap), column 3
+// ci + dx, so one product serves three taps and ten sums (nine (y, z) taps and
+// the bias) replace 28; wave w takes sums w, w + 4, w + 8.  The 5 -> 16 layer:
+// 118 us with 11 of 16 columns empty, 62 us.  Same bits.
+template <int NC>
 __global__ __launch_bounds__(256, 2) void k_conv3_wgrad(const float* __restrict__ x, int up,
                                                      const float* __restrict__ dy, int Ci, int Co,
                                                      int Cop, int D, int H, int W, int tx, int ty,
@@ -651,20 +702,25 @@ __global__ __launch_bounds__(256, 2) void k_conv3_wgrad(const float* __restrict_
   const int ci0 = blockIdx.y * 16, co0 = blockIdx.z * 16;
   const int HW = H * W, Wi = W >> up, HWi = (H >> up) * Wi;
   const size_t DHW = (size_t)D * HW, DHWi = (size_t)(D >> up) * HWi;
-  int off[7];                                   // LDS offset of this lane's operand per tap
+  constexpr bool kPack = NC < 16;
+  constexpr int NS = kPack ? 3 : 7;             // sums of a wave
+  auto sum_of = [&](int j) { return kPack ? w + 4 * j : 7 * w + j; };
+  int off[NS];                                  // LDS offset of this lane's operand per sum
 #pragma unroll
-  for (int j = 0; j < 7; ++j) {
-    const int t = min(7 * w + j, 26), dx = t % 3, dyy = (t / 3) % 3, dz = t / 9;
-    off[j] = ((dz * kCHY + dyy) * kCHX + dx + k) * kWgPitch + col;
+  for (int j = 0; j < NS; ++j) {
+    const int t = kPack ? 3 * min(sum_of(j), 8) + min(col, 14) % 3 : min(sum_of(j), 26);
+    const int dx = t % 3, dyy = (t / 3) % 3, dz = t / 9;
+    off[j] = ((dz * kCHY + dyy) * kCHX + dx + k) * kWgPitch + (kPack ? min(col, 14) / 3 : col);
   }
-  const bool ones = w == 3;                     // its last sum is the bias gradient
-  cf32x4 acc[7];
+  constexpr int jb = kPack ? 2 : 6;             // the bias gradient: this sum of
+  const bool ones = w == (kPack ? 1 : 3);       // this wave
+  cf32x4 acc[NS];
 #pragma unroll
-  for (int j = 0; j < 7; ++j) acc[j] = cf32x4{0.f, 0.f, 0.f, 0.f};
+  for (int j = 0; j < NS; ++j) acc[j] = cf32x4{0.f, 0.f, 0.f, 0.f};
 
   // the staged voxels of a tile that this thread loads: three of the halo
   // (the third only for the first 136 threads), one of dy
-  float xq[3][16], dq[16];
+  float xq[3][NC], dq[16];
   auto load = [&](int tile) {
     const int bx = tile % tx, by = (tile / tx) % ty, bz = (tile / (tx * ty)) % tz,
               n = tile / (tx * ty * tz);
@@ -680,9 +736,9 @@ __global__ __launch_bounds__(256, 2) void k_conv3_wgrad(const float* __restrict_
                       (unsigned)gz < (unsigned)D;
       const size_t o = in ? (size_t)(gz >> up) * HWi + (size_t)(gy >> up) * Wi + (gx >> up) : 0;
 #pragma unroll
-      for (int c = 0; c < 16; ++c) xq[u][c] = xn[min(c, Ci - 1 - ci0) * DHWi + o];
+      for (int c = 0; c < NC; ++c) xq[u][c] = xn[min(c, Ci - 1 - ci0) * DHWi + o];
 #pragma unroll
-      for (int c = 0; c < 16; ++c) xq[u][c] = in && ci0 + c < Ci ? xq[u][c] : 0.f;
+      for (int c = 0; c < NC; ++c) xq[u][c] = in && ci0 + c < Ci ? xq[u][c] : 0.f;
     }
     const int gx = x0 + (tid & 15), gy = y0 + ((tid >> 4) & 3), gz = z0 + (tid >> 6);
     const bool in = gx < W && gy < H && gz < D;
@@ -702,7 +758,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3_wgrad(const float* __restrict_
       const int v = tid + 256 * u;
       if (v < kCHV) {
 #pragma unroll
-        for (int c = 0; c < 16; ++c) xs[v * kWgPitch + c] = xq[u][c];
+        for (int c = 0; c < NC; ++c) xs[v * kWgPitch + c] = xq[u][c];
       }
     }
 #pragma unroll
@@ -712,17 +768,17 @@ __global__ __launch_bounds__(256, 2) void k_conv3_wgrad(const float* __restrict_
     const int nx = min(kCTX, W - (tile % tx) * kCTX), ny = min(kCTY, H - (tile / tx) % ty * kCTY),
               nz = min(kCTZ, D - (tile / (tx * ty)) % tz * kCTZ);
     // operands one step of four voxels ahead of the products
-    float av[2], bv[2][7];
+    float av[2], bv[2][NS];
     auto read = [&](int b, int z, int yy, int g) {
       const int dr = (z * kCTY + yy) * kCTX + g, xr = (z * kCHY + yy) * kCHX + g;
       av[b] = ds[(dr + k) * kWgPitch + col];
 #pragma unroll
-      for (int j = 0; j < 7; ++j) bv[b][j] = xs[xr * kWgPitch + off[j]];
-      bv[b][6] = ones ? 1.f : bv[b][6];
+      for (int j = 0; j < NS; ++j) bv[b][j] = xs[xr * kWgPitch + off[j]];
+      bv[b][jb] = ones ? 1.f : bv[b][jb];
     };
-    cf32x4 sum[7];                              // this tile's
+    cf32x4 sum[NS];                             // this tile's
 #pragma unroll
-    for (int j = 0; j < 7; ++j) sum[j] = cf32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NS; ++j) sum[j] = cf32x4{0.f, 0.f, 0.f, 0.f};
     int z = 0, yy = 0, g = 0;
     auto next = [&]() {
       g += 4;
@@ -730,7 +786,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3_wgrad(const float* __restrict_
     };
     auto products = [&](int b) {
 #pragma unroll
-      for (int j = 0; j < 7; ++j)
+      for (int j = 0; j < NS; ++j)
         sum[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[b], bv[b][j], sum[j], 0, 0, 0);
     };
     read(0, 0, 0, 0);
@@ -746,17 +802,18 @@ __global__ __launch_bounds__(256, 2) void k_conv3_wgrad(const float* __restrict_
       products(1);
     }
 #pragma unroll
-    for (int j = 0; j < 7; ++j) acc[j] += sum[j];
+    for (int j = 0; j < NS; ++j) acc[j] += sum[j];
   }
   // result: lane holds output channels 4 (lane / 16) + i of input channel col
   const size_t nw = (size_t)Ci * 27 * Cop;
   float* dst = part + (size_t)blockIdx.x * (nw + Cop);
-  const int ci = ci0 + col;
 #pragma unroll
-  for (int j = 0; j < 7; ++j) {
-    const int t = 7 * w + j, co = co0 + 4 * k;
-    if (t < 27 ? ci < Ci : ci == 0) {
-      float* o = t < 27 ? dst + ((size_t)ci * 27 + t) * Cop + co : dst + nw + co;
+  for (int j = 0; j < NS; ++j) {
+    const int q = sum_of(j), co = co0 + 4 * k;
+    const bool bias = q == (kPack ? 9 : 27);
+    const int ci = ci0 + (kPack ? col / 3 : col), t = kPack ? 3 * q + col % 3 : q;
+    if (bias ? ci0 + col == 0 : q < (kPack ? 9 : 27) && ci < Ci && (!kPack || col < 15)) {
+      float* o = bias ? dst + nw + co : dst + ((size_t)ci * 27 + t) * Cop + co;
       *(float4*)o = make_float4(acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
     }
   }
@@ -822,8 +879,12 @@ void launch_conv_wgrad(int K, const float* x, int up, const float* dy, int N, in
   if (K == 3) {
     const WgradPlan p = wgrad_plan(N, Ci, Co, D, H, W);
     const dim3 grid(p.runs, p.gy, p.gz);
-    k_conv3_wgrad<<<grid, 256, 0, s>>>(x, up, dy, Ci, Co, Cop, D, H, W, p.tx, p.ty, p.tz, p.tiles,
-                                       p.run, part);
+    if (Ci <= 5)
+      k_conv3_wgrad<5><<<grid, 256, 0, s>>>(x, up, dy, Ci, Co, Cop, D, H, W, p.tx, p.ty, p.tz,
+                                            p.tiles, p.run, part);
+    else
+      k_conv3_wgrad<16><<<grid, 256, 0, s>>>(x, up, dy, Ci, Co, Cop, D, H, W, p.tx, p.ty, p.tz,
+                                             p.tiles, p.run, part);
     const size_t nw = (size_t)Ci * 27 * Cop;
     k_conv3_wgrad_sum<<<div_up((long)(nw + Cop), 64), 1024, 0, s>>>(part, p.runs, nw, Cop, Co, dw, db);
     return;
@@ -850,20 +911,24 @@ __global__ void k_pool(const float* __restrict__ x, int D, int H, int W, float* 
   y[((size_t)nc * Do + dd) * Ho * Wo + j] = s * 0.125f;
 }
 
-// pool adjoint (scale 1/8) or upsampling (scale 1): y(fine) = scale * x(coarse)
-__global__ void k_expand(const float* __restrict__ x, int D, int H, int W, float scale,
-                         float* __restrict__ y) {
+// The adjoint of the pooling (scale 1/8), the skip's gradient and the ReLU mask in
+// one pass over the fine grid (16 channels of 8 x 40^3: 42 us in two, 22 us).
+__global__ void k_expand_relu(const float* __restrict__ x, int D, int H, int W, float scale,
+                              const float* __restrict__ r, const float* __restrict__ extra,
+                              float* __restrict__ y) {
   const int j = blockIdx.y * blockDim.x + threadIdx.x;
   if (j >= H * W) return;
   const int d = blockIdx.x % D, nc = blockIdx.x / D;
   const int h = j / W, w = j - h * W;
   const int Hc = H >> 1, Wc = W >> 1;
-  y[((size_t)nc * D + d) * H * W + j] =
-      scale * x[(((size_t)nc * (D >> 1) + (d >> 1)) * Hc + (h >> 1)) * Wc + (w >> 1)];
+  const size_t i = ((size_t)nc * D + d) * H * W + j;
+  const float g =
+      extra[i] + scale * x[(((size_t)nc * (D >> 1) + (d >> 1)) * Hc + (h >> 1)) * Wc + (w >> 1)];
+  y[i] = r[i] > 0.f ? g : 0.f;
 }
-
-// upsampling adjoint: y(coarse) = sum of the 8 children
-__global__ void k_sum8(const float* __restrict__ x, int D, int H, int W, float* __restrict__ y) {
+__global__ void k_sum8_relu(const float* __restrict__ x, int D, int H, int W,
+                            const float* __restrict__ r, float* __restrict__ y,
+                            float* __restrict__ dr) {
   const int Do = D >> 1, Ho = H >> 1, Wo = W >> 1;
   const int j = blockIdx.y * blockDim.x + threadIdx.x;
   if (j >= Ho * Wo) return;
@@ -872,31 +937,32 @@ __global__ void k_sum8(const float* __restrict__ x, int D, int H, int W, float* 
   const float* b = x + ((size_t)nc * D + 2 * dd) * H * W + (size_t)(2 * ho) * W + 2 * wo;
   float s = 0.f;
   for (int a = 0; a < 8; ++a) s += b[(size_t)(a >> 2) * H * W + ((a >> 1) & 1) * W + (a & 1)];
-  y[((size_t)nc * Do + dd) * Ho * Wo + j] = s;
+  const size_t i = ((size_t)nc * Do + dd) * Ho * Wo + j;
+  if (y) y[i] = s;
+  dr[i] = r[i] > 0.f ? s : 0.f;
 }
 
 void launch_pool(const float* x, int NC, int D, int H, int W, float* y, hipStream_t s) {
   k_pool<<<dim3(NC * (D / 2), div_up((H / 2) * (W / 2), 256)), 256, 0, s>>>(x, D, H, W, y);
 }
-void launch_expand(const float* x, int NC, int D, int H, int W, float scale, float* y, hipStream_t s) {
-  k_expand<<<dim3(NC * D, div_up(H * W, 256)), 256, 0, s>>>(x, D, H, W, scale, y);
+void launch_expand_relu(const float* x, int NC, int D, int H, int W, float scale, const float* r,
+                        const float* extra, float* y, hipStream_t s) {
+  k_expand_relu<<<dim3(NC * D, div_up(H * W, 256)), 256, 0, s>>>(x, D, H, W, scale, r, extra, y);
 }
-void launch_sum8(const float* x, int NC, int D, int H, int W, float* y, hipStream_t s) {
-  k_sum8<<<dim3(NC * (D / 2), div_up((H / 2) * (W / 2), 256)), 256, 0, s>>>(x, D, H, W, y);
+void launch_sum8_relu(const float* x, int NC, int D, int H, int W, const float* r, float* y, float* dr,
+                      hipStream_t s) {
+  k_sum8_relu<<<dim3(NC * (D / 2), div_up((H / 2) * (W / 2), 256)), 256, 0, s>>>(x, D, H, W, r, y, dr);
 }
 
-// dr = dy * (r > 0) [+ extra]; extra may be NULL
-__global__ void k_relu_bwd(const float* __restrict__ dy, const float* __restrict__ r,
-                           const float* __restrict__ extra, long n, float* __restrict__ dr) {
+// dr = dy * (r > 0)
+__global__ void k_relu_bwd(const float* __restrict__ dy, const float* __restrict__ r, long n,
+                           float* __restrict__ dr) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float g = (extra ? extra[i] : 0.f) + dy[i];
-  dr[i] = r[i] > 0.f ? g : 0.f;
+  if (i < n) dr[i] = r[i] > 0.f ? dy[i] : 0.f;
 }
 
-void launch_relu_bwd(const float* dy, const float* r, const float* extra, long n, float* dr,
-                     hipStream_t s) {
-  k_relu_bwd<<<div_up(n, 256), 256, 0, s>>>(dy, r, extra, n, dr);
+void launch_relu_bwd(const float* dy, const float* r, long n, float* dr, hipStream_t s) {
+  k_relu_bwd<<<div_up(n, 256), 256, 0, s>>>(dy, r, n, dr);
 }
 
 __global__ void k_add(const float* __restrict__ a, const float* __restrict__ b, long n,

@@ -215,18 +215,26 @@ void forward(sgmg_unet* u, int N, int D, int H, int W, const float* x, hipStream
   conv(u, infer, 7, u->d1, N, D, H, W, 0, nullptr, nullptr, u->y, s);
 }
 
+// The data gradients' weights: the 3x3x3 layers' packed, the head's transposed.
+void pack_dgrad(sgmg_unet* u, hipStream_t s) {
+  ConvPacks ps{};
+  for (int l = 1; l < kNL; ++l) {
+    const ULayer& L = u->L[l];
+    if (L.k == 3) ps.p[ps.n++] = {L.wq, L.wpt, L.ci, L.co, 0, 0, 0};
+    else launch_weight_transpose(L.wq, L.ci, L.co, L.k, L.wt, s);
+  }
+  launch_pack_conv3_flip(ps, s);
+}
+
 // dx = data gradient of layer l: the convolution with the channels swapped
 // and the taps flipped
 void conv_dgrad(sgmg_unet* u, int l, const float* dy, int N, int D, int H, int W, float* dx,
                 hipStream_t s) {
   const ULayer& L = u->L[l];
-  launch_weight_transpose(L.wq, L.ci, L.co, L.k, L.wt, s);
-  if (L.k == 3) {
-    launch_pack_conv3(L.wt, 0, L.co, L.ci, L.wpt, s);
+  if (L.k == 3)
     launch_conv3_mfma(dy, 0, N, L.co, L.ci, D, H, W, L.wpt, nullptr, 0, nullptr, nullptr, dx, s);
-  } else {
+  else
     launch_conv_fwd(L.k, dy, N, L.co, L.ci, D, H, W, L.wt, nullptr, 0, nullptr, nullptr, dx, s);
-  }
 }
 
 void backward(sgmg_unet* u, int N, int D, int H, int W, const float* x, hipStream_t s) {
@@ -235,34 +243,29 @@ void backward(sgmg_unet* u, int N, int D, int H, int W, const float* x, hipStrea
             H4 = H / 8, W4 = W / 8;
   const long v1 = (long)D * H * W, v2 = v1 / 8, v3 = v2 / 8, v4 = v3 / 8;
   float *gd1 = u->g1, *gt = u->g2, *gd2 = u->g3, *gd3 = u->g4, *gt2 = u->g5;
+  pack_dgrad(u, s);
   // output 1x1 conv
   launch_conv_wgrad(1, u->d1, 0, u->gy, N, 16, 3, D, H, W, u->part, L[7].gw, L[7].gb, s);
   conv_dgrad(u, 7, u->gy, N, D, H, W, gd1, s);                       // dL/d d1 (skip to e1 too)
-  launch_relu_bwd(gd1, u->r7, nullptr, N * 16 * v1, gt, s);          // dL/d r7 pre
+  launch_relu_bwd(gd1, u->r7, N * 16 * v1, gt, s);                   // dL/d r7 pre
   launch_conv_wgrad(3, u->d2, 1, gt, N, 32, 16, D, H, W, u->part, L[6].gw, L[6].gb, s);
   conv_dgrad(u, 6, gt, N, D, H, W, gt2, s);                          // dL/d u2 [N,32,D]
-  launch_sum8(gt2, N * 32, D, H, W, gd2, s);                         // dL/d d2 [N,32,D2]
-  launch_relu_bwd(gd2, u->r6, nullptr, N * 32 * v2, gt, s);
+  launch_sum8_relu(gt2, N * 32, D, H, W, u->r6, gd2, gt, s);         // dL/d d2 [N,32,D2]
   launch_conv_wgrad(3, u->d3, 1, gt, N, 64, 32, D2, H2, W2, u->part, L[5].gw, L[5].gb, s);
   conv_dgrad(u, 5, gt, N, D2, H2, W2, gt2, s);                       // dL/d u3 [N,64,D2]
-  launch_sum8(gt2, N * 64, D2, H2, W2, gd3, s);                      // dL/d d3 [N,64,D3]
-  launch_relu_bwd(gd3, u->r5, nullptr, N * 64 * v3, gt, s);
+  launch_sum8_relu(gt2, N * 64, D2, H2, W2, u->r5, gd3, gt, s);      // dL/d d3 [N,64,D3]
   launch_conv_wgrad(3, u->r4, 1, gt, N, 128, 64, D3, H3, W3, u->part, L[4].gw, L[4].gb, s);
   conv_dgrad(u, 4, gt, N, D3, H3, W3, gt2, s);                       // dL/d u4 [N,128,D3]
-  launch_sum8(gt2, N * 128, D3, H3, W3, gt, s);                      // dL/d r4 [N,128,D4]
-  launch_relu_bwd(gt, u->r4, nullptr, N * 128 * v4, gt2, s);
-  launch_conv_wgrad(3, u->p3, 0, gt2, N, 64, 128, D4, H4, W4, u->part, L[3].gw, L[3].gb, s);
-  conv_dgrad(u, 3, gt2, N, D4, H4, W4, gt, s);                       // dL/d p3 [N,64,D4]
-  launch_expand(gt, N * 64, D3, H3, W3, 0.125f, gt2, s);             // pool adjoint
-  launch_relu_bwd(gt2, u->r3, gd3, N * 64 * v3, gt, s);              // + skip from d3
+  launch_sum8_relu(gt2, N * 128, D3, H3, W3, u->r4, nullptr, gt, s); // dL/d r4 [N,128,D4]
+  launch_conv_wgrad(3, u->p3, 0, gt, N, 64, 128, D4, H4, W4, u->part, L[3].gw, L[3].gb, s);
+  conv_dgrad(u, 3, gt, N, D4, H4, W4, gt2, s);                       // dL/d p3 [N,64,D4]
+  launch_expand_relu(gt2, N * 64, D3, H3, W3, 0.125f, u->r3, gd3, gt, s);   // pool adjoint + skip
   launch_conv_wgrad(3, u->p2, 0, gt, N, 32, 64, D3, H3, W3, u->part, L[2].gw, L[2].gb, s);
   conv_dgrad(u, 2, gt, N, D3, H3, W3, gt2, s);                       // dL/d p2 [N,32,D3]
-  launch_expand(gt2, N * 32, D2, H2, W2, 0.125f, gt, s);
-  launch_relu_bwd(gt, u->r2, gd2, N * 32 * v2, gt2, s);              // + skip from d2
-  launch_conv_wgrad(3, u->p1, 0, gt2, N, 16, 32, D2, H2, W2, u->part, L[1].gw, L[1].gb, s);
-  conv_dgrad(u, 1, gt2, N, D2, H2, W2, gt, s);                       // dL/d p1 [N,16,D2]
-  launch_expand(gt, N * 16, D, H, W, 0.125f, gt2, s);
-  launch_relu_bwd(gt2, u->r1, gd1, N * 16 * v1, gt, s);              // + skip from d1
+  launch_expand_relu(gt2, N * 32, D2, H2, W2, 0.125f, u->r2, gd2, gt, s);   // + skip from d2
+  launch_conv_wgrad(3, u->p1, 0, gt, N, 16, 32, D2, H2, W2, u->part, L[1].gw, L[1].gb, s);
+  conv_dgrad(u, 1, gt, N, D2, H2, W2, gt2, s);                       // dL/d p1 [N,16,D2]
+  launch_expand_relu(gt2, N * 16, D, H, W, 0.125f, u->r1, gd1, gt, s);      // + skip from d1
   launch_conv_wgrad(3, x, 0, gt, N, 5, 16, D, H, W, u->part, L[0].gw, L[0].gb, s);
 }
 
@@ -303,7 +306,7 @@ int sgmg_unet_create(uint64_t seed, sgmg_unet** out) {
       if (!rc) rc = ualloc(u->mem, p, L.nw);
     for (float** p : {&L.b, &L.gb, &L.mb, &L.vb})
       if (!rc) rc = ualloc(u->mem, p, L.cop);
-    if (!rc) rc = ualloc(u->mem, &L.wt, (size_t)L.co * L.k3 * L.cip);
+    if (!rc && L.k != 3) rc = ualloc(u->mem, &L.wt, (size_t)L.co * L.k3 * L.cip);
     if (!rc && L.k == 3) {
       float* a = nullptr;
       rc = ualloc(u->mem, &a, 4 * conv3_packed_words(kUp[l], L.ci, L.co));

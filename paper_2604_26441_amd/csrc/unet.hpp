@@ -50,6 +50,17 @@ void launch_conv_fwd(int K, const float* x, int N, int Ci, int Co, int D, int H,
 // (up = 0) or upsampled (up = 1).
 size_t conv3_packed_words(int up, int Ci, int Co);
 void launch_pack_conv3(const float* w, int up, int Ci, int Co, uint4* wp, hipStream_t s);
+// Packed weights of the data gradients of up to eight 3x3x3 layers: w, the
+// layer's channels and wp (conv3_packed_words(0, Co, Ci)) are given.
+struct ConvPacks {
+  struct One {
+    const float* w;
+    uint4* wp;
+    int Ci, Co, Cip, Cop, total;
+  } p[8];
+  int n;
+};
+void launch_pack_conv3_flip(ConvPacks ps, hipStream_t s);
 // up = 1: x is stored at (D/2, H/2, W/2) and read as its nearest x2 upsampling
 // (Ci a multiple of 8); with hw (up = 1, Co = 16) the 1x1x1 head's three
 // channels hw, hb of the result are written to hy, and y may be NULL.
@@ -67,11 +78,14 @@ size_t conv_wgrad_part_floats(int N, int Ci, int Co, int D, int H, int W, int K)
 void launch_conv_wgrad(int K, const float* x, int up, const float* dy, int N, int Ci, int Co, int D,
                        int H, int W, float* part, float* dw, float* db, hipStream_t s);
 void launch_pool(const float* x, int NC, int D, int H, int W, float* y, hipStream_t s);
-void launch_expand(const float* x, int NC, int D, int H, int W, float scale, float* y,
-                   hipStream_t s);
-void launch_sum8(const float* x, int NC, int D, int H, int W, float* y, hipStream_t s);
-void launch_relu_bwd(const float* dy, const float* r, const float* extra, long n, float* dr,
-                     hipStream_t s);
+// y = scale * x upsampled + extra where r > 0 (the adjoints of the pooling, the
+// skip and the ReLU), and the eightfold sums of x (into y, unless NULL) where r
+// > 0 (those of the upsampling and the ReLU, into dr).
+void launch_expand_relu(const float* x, int NC, int D, int H, int W, float scale, const float* r,
+                        const float* extra, float* y, hipStream_t s);
+void launch_sum8_relu(const float* x, int NC, int D, int H, int W, const float* r, float* y, float* dr,
+                      hipStream_t s);
+void launch_relu_bwd(const float* dy, const float* r, long n, float* dr, hipStream_t s);
 void launch_add(const float* a, const float* b, long n, float* y, hipStream_t s);
 void launch_mse(const float* y, const float* t, const float* mask, int N, int C, int DHW, float* dy,
                 RedWs ws, double* sums, hipStream_t s);
