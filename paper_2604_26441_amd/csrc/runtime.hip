@@ -82,6 +82,9 @@ struct sgmg_hierarchy {
   // vector ALU 45 %, the matrix cores 30 %
   int store_rows[2] = {4, 4};
   int store_zchunk[2] = {4, 4};
+  // planes of the FP64 tiles where they also form p.q (rows 1): that kernel keeps
+  // the 16 x 4 tiles, so its chunk is timed by itself
+  int dot_zchunk = 4;
   uint16_t* atab = nullptr;  // MFMA A-operand table (BF16 bits)
   double* atab64 = nullptr;  // FP64 MFMA A-operand table
   // level 1 without its stored stencil (FP64 level 1 above the coarsest):
@@ -293,7 +296,8 @@ int apply_level<double>(const sgmg_hierarchy* h, int l, sgmg_prec prec, const do
     return SGMG_EINVAL;
   }
   if (l == 0 && h->mfma_rows[2] == 1 && sf64_size_ok(L.g)) {
-    launch_apply_fine_sf64(L.g, h->mfma_zchunk[2], h->E64, h->kt.lam, h->kt.mu, x, L.fixn, ep, s);
+    launch_apply_fine_sf64(L.g, ep.want_dot ? h->dot_zchunk : h->mfma_zchunk[2], h->E64, h->kt.lam,
+                           h->kt.mu, x, L.fixn, ep, s);
   } else if (l == 0 && h->mfma_rows[2] > 1 && mfma64_size_ok(L.g)) {
     launch_apply_fine_mfma64(L.g, h->mfma_rows[2], h->mfma_zchunk[2], h->E64, h->atab64, x, L.fixn,
                              ep, s);
@@ -352,7 +356,7 @@ int apply_level<float>(const sgmg_hierarchy* h, int l, sgmg_prec prec, const flo
 int k64_dot_partials(const sgmg_hierarchy* h) {
   const Level& L = h->lev[0];
   if (h->mfma_rows[2] == 1 && sf64_size_ok(L.g))
-    return (int)apply_fine_sf64_blocks(L.g, h->mfma_zchunk[2]);
+    return (int)apply_fine_sf64_blocks(L.g, h->dot_zchunk);
   if (h->mfma_rows[2] > 1 && mfma64_size_ok(L.g))
     return (int)apply_fine_mfma_blocks(L.g, h->mfma_rows[2] == 4 ? 4 : 8,
                                        h->mfma_zchunk[2] < 1 ? 1 : h->mfma_zchunk[2]);
@@ -763,7 +767,10 @@ int sgmg_setup_hierarchy(const sgmg_options* opts, const double* rho_or_E, const
                                 q == 2 ? std::make_pair(1, 4) : std::make_pair(4, 4));
     h->mfma_rows[q] = sh.first;
     h->mfma_zchunk[q] = sh.second;
-    if (q == 2) break;
+    if (q == 2) {
+      h->dot_zchunk = tuned_shape(opts->nx, opts->ny, opts->nz, 264, sh).second;
+      break;
+    }
     const auto st = tuned_shape(opts->nx, opts->ny, opts->nz, q ? 203 : 201, sh);
     h->store_rows[q] = st.first;
     h->store_zchunk[q] = st.second;
@@ -1630,6 +1637,8 @@ int sgmg_set_launch_shape(sgmg_hierarchy* h, int variant, int rows, int planes) 
   if (variant < 2) {
     h->store_rows[variant] = rows;
     h->store_zchunk[variant] = planes;
+  } else {
+    h->dot_zchunk = planes;
   }
   for (auto& row : h->iter_graph)        // captured graphs hold the old launch shape
     for (auto& g : row)
@@ -1867,7 +1876,35 @@ int sgmg_autotune(sgmg_hierarchy* h, int* shape_out, void* stream) {
     h->mfma_zchunk[q] = best_z;
     if (shape_out) { shape_out[2 * q] = best_r; shape_out[2 * q + 1] = best_z; }
     keep(key);
-    if (q == 2) break;
+    if (q == 2) {
+      if (best_r != 1) break;
+      best_ms = 1e30f;                            // the same tiles with p.q
+      for (int iz = 0; iz < n_z && !rc; ++iz) {
+        const int z = z_c[iz];
+        if (z > L0.g.Nz && z != z_c[0]) continue;
+        auto launch = [&]() {
+          launch_apply_fine_sf64(L0.g, z, h->E64, h->kt.lam, h->kt.mu, u64, L0.fixn,
+                                 epi_store_partials<double>(y64, h->ws), s);
+        };
+        for (int w = 0; w < 3; ++w) launch();
+        hipEventRecord(e0, s);
+        for (int r = 0; r < 20; ++r) launch();
+        hipEventRecord(e1, s);
+        if ((rc = check_launch())) break;
+        if (hipEventSynchronize(e1) != hipSuccess) {
+          rc = SGMG_EHIP;
+          set_error("autotune sync failed");
+          break;
+        }
+        float ms = 0.f;
+        hipEventElapsedTime(&ms, e0, e1);
+        if (ms < best_ms) { best_ms = ms; best_z = z; }
+      }
+      if (rc) break;
+      h->dot_zchunk = best_z;
+      keep(264);
+      break;
+    }
     best_ms = 1e30f;
     tune_tiles(true);
     if (rc) break;
