@@ -260,11 +260,11 @@ int sgmg_lanczos(sgmg_hierarchy* h, int precond, int m, const double* g, double 
  * keeps the fastest in h and in a process-wide cache keyed by (nx, ny, nz,
  * variant) that later setups of the same mesh read.  shape_out (host, 6
  * ints, may be NULL) receives (rows, planes) for BF16, BF16X3 (smoothing
- * steps), then FP64; for FP64 the vector-ALU node kernel is a candidate too, reported as (0, 0),
- * and so are the vector-ALU sum-factorised tiles with 2 .. 32 planes,
- * reported as (1, planes) ((1, 4) is the FP64 choice of an untuned mesh; the
- * PCG's product with its dot has a planes of its own, not reported).  When
- * the hierarchy holds the level-1 element products (stencil_form 0 or 3,
+ * steps), then FP64; for FP64 the vector-ALU node kernel is a candidate too,
+ * reported as (0, 0), and so are the vector-ALU sum-factorised tiles with 2 ..
+ * 32 planes, reported as (1, planes) ((1, 4) is the FP64 choice of an untuned
+ * mesh; the PCG's product with its dot has planes of its own, not reported).
+ * When the hierarchy holds the level-1 element products (stencil_form 0 or 3,
  * FP64 level 1 above the coarsest) it also times level 1 from the stored
  * stencil against the products with 1 to 6 and 8 planes and keeps the faster
  * (with stencil_form 3 the products stay); that choice is kept in the same
@@ -332,21 +332,23 @@ int sgmg_pcg_solve_batch(sgmg_batch* b, int nitems, const int* item_sys, const d
 /* The same items solved stage by stage: every stage of the outer PCG (Sec.
  * 3.6) and of the V-cycle (Eq. vcycle) is one launch over all items, with as
  * many workgroups per item as its level has work (so the whole device works
- * on each stage, whatever the item sizes).  Two captured graphs are replayed
- * from a host loop: a prologue (r = f - K u in FP64, V-cycle, p = z, r.z)
- * and one PCG iteration (q = K p, alpha, x and r, V-cycle, beta, p); per-item
- * flags copied in before each replay select the items that take part.  After
- * every iteration the host reads each item's scalars; an item whose
- * recursive residual passes rtol runs the prologue, which is its FP64
- * true-residual check and, if that fails, its restart (beta = 0).  Same
+ * on each stage, whatever the item sizes).  Three captured graphs are
+ * replayed from a host loop: a prologue (r = f - K u in FP64, V-cycle, p = z,
+ * r.z), one PCG iteration (q = K p, alpha, x and r, V-cycle, beta, p) and the
+ * residual alone; per-item flags copied in before each replay select the
+ * items that take part.  After every iteration the host reads each item's
+ * scalars; an item whose recursive residual passes rtol runs the residual
+ * graph, its FP64 true-residual check, and if that fails the prologue, its
+ * restart (beta = 0).  The coarsest products read each coefficient of a
+ * system's symmetric inverse once for up to four of its load cases.  Same
  * algorithm and acceptance as sgmg_pcg_solve with Fletcher-Reeves beta.
  * Level operators: level 0 inside the V-cycle on the BF16X3 MFMA operator
  * when every item's system has fine_prec BF16X3 (else the FP32 vector-ALU
  * node operator), the Galerkin levels on the FP64 stored stencils, the
- * outer q = K p on the FP64 MFMA operator; the two MFMA launch shapes and the
- * stencil form of each Galerkin level are timed on the item set at its first
- * call and the fastest kept.  Reductions
- * per item in a fixed order.  All systems must share the smoothing step
+ * outer q = K p on the FP64 MFMA operator or the sum/difference-basis one (then
+ * the residuals as well); the two launch shapes and the stencil form of each
+ * Galerkin level are timed on the item set at its first call and the fastest
+ * kept.  Reductions per item in a fixed order.  All systems must share the smoothing step
  * counts.  Work vectors, tables and graphs are built on the first call for
  * an item set.  *total_ms: wall time of the whole solve on the stream.
  * Synchronises once per iteration. */
@@ -549,7 +551,9 @@ int sgmg_simp_sensitivity(sgmg_simp* s, const sgmg_hierarchy* h, const double* u
                           double* compliance, double* dc, double* dv, void* stream);
 /* One OC update of rho (device, in place) from the last sensitivities; the
  * outputs (host, optional) are the multiplier, the physical volume at it and
- * the largest density change.  Reads back one scalar per halving. */
+ * the largest density change.  The bisection runs on the device, six halvings
+ * per pass over the elements (one with projection), and its result is read
+ * back once per 84 halvings. */
 int sgmg_simp_oc_update(sgmg_simp* s, double* rho, double* lambda, double* volume,
                         double* max_change, void* stream);
 /* One SIMP iteration: physical field, sgmg_update_moduli (which re-estimates

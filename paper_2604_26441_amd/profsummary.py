@@ -166,7 +166,7 @@ def counters(path):
         print(f"| `{name}` | {nd} | " + " | ".join(f"{v:.1f}" for v in vals) + " |")
 
 
-def last_solve(c, marker="k_apply_fine_sf64<3>"):
+def last_solve(c, marker="k_apply_fine_sf64<3"):
     rows = list(c.execute("select name, start, end from kernels order by start"))
     starts = [i for i, r in enumerate(rows) if "k_pcg_init" in r[0]]
     if not starts:
@@ -201,7 +201,7 @@ def last_solve(c, marker="k_apply_fine_sf64<3>"):
     kp = [i for i, r in enumerate(seg) if marker in r[0]]
     if len(kp) > 1:
         its = [sum(e - s for _, s, e in seg[a:b]) / 1e3 for a, b in zip(kp, kp[1:])]
-        print(f"\nKernel time per PCG iteration (from one `{_short(marker)}` dispatch to the next): "
+        print(f"\nKernel time per PCG iteration (from one `{_short(seg[kp[0]][0])}` dispatch to the next): "
               + ", ".join(f"{x:.1f}" for x in its) + f" us; mean {sum(its) / len(its):.1f} us. "
               f"Before the first: {sum(e - s for _, s, e in seg[:kp[0]]) / 1e3:.1f} us; "
               f"from the last to the end: {sum(e - s for _, s, e in seg[kp[-1]:]) / 1e3:.1f} us.")
