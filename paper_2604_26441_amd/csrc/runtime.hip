@@ -2130,7 +2130,6 @@ struct sgmg_batch {
     int* h_flags = nullptr;        // pinned mirror
     double* h_scal = nullptr;      // pinned mirror
     int Lmax = 0, steps0 = 0, stepsL = 0;
-    hipGraphExec_t g_pro = nullptr, g_it = nullptr, g_chk = nullptr;
     // level 0 on the BF16X3 MFMA operator: launch shape, (item, block)
     // table and per-item tile grids
     bool mfma0 = false;
@@ -2167,9 +2166,6 @@ void batch_drop_graph(sgmg_batch* b) {
 
 void batch_free_staged(sgmg_batch* b) {
   auto& st = b->st;
-  if (st.g_pro) hipGraphExecDestroy(st.g_pro);
-  if (st.g_it) hipGraphExecDestroy(st.g_it);
-  if (st.g_chk) hipGraphExecDestroy(st.g_chk);
   if (st.g_first) hipGraphExecDestroy(st.g_first);
   if (st.g_more) hipGraphExecDestroy(st.g_more);
   if (st.lmem) hipFree(st.lmem);
@@ -2416,11 +2412,6 @@ int bs_capture_fn(sgmg_batch* b, F&& body, hipGraphExec_t* out) {
   hipGraphDestroy(g);
   if (e2 != hipSuccess) { *out = nullptr; set_error("staged batch graph instantiate failed"); return SGMG_EHIP; }
   return 0;
-}
-
-int bs_capture(sgmg_batch* b, void (*body)(const sgmg_batch*, const BsArgs&, int, hipStream_t),
-               int n, hipGraphExec_t* out) {
-  return bs_capture_fn(b, [&](const BsArgs& a, hipStream_t s) { body(b, a, n, s); }, out);
 }
 
 // steps PCG iterations under device-side control: after each iteration the
@@ -2804,9 +2795,6 @@ int bs_prepare(sgmg_batch* b, int n, hipStream_t s) {
     st.k64rows = k64_shapes[bc][0];
     st.k64z = k64_shapes[bc][1];
   }
-  TRY(bs_capture(b, bs_prologue, n, &st.g_pro));
-  TRY(bs_capture(b, bs_iteration, n, &st.g_it));
-  TRY(bs_capture(b, bs_residual, n, &st.g_chk));
   st.ready = true;
   return 0;
 }
@@ -3005,10 +2993,20 @@ int sgmg_pcg_solve_batch_staged(sgmg_batch* b, int nitems, const int* item_sys,
   SGMG_HIP(hipEventCreate(&e0));
   SGMG_HIP(hipEventCreate(&e1));
   SGMG_HIP(hipEventRecord(e0, s));
-  // one graph replay with the given prologue / iteration flags, then the scalars
-  auto run = [&](hipGraphExec_t g) -> int {
-    SGMG_HIP(hipMemcpyAsync(st.flags, hf, 2 * (size_t)n * sizeof(int), hipMemcpyHostToDevice, s));
-    SGMG_HIP(hipGraphLaunch(g, s));
+  // one pass over the items with the given prologue / iteration flags, then the
+  // scalars.  The host waits for every pass, so what counts is how soon its first
+  // kernel starts: launched one by one it starts at once and the host keeps ahead
+  // of the rest (no kernel takes less than its launch), a graph starts later.
+  // Flags that are on the device already are not copied again.
+  std::vector<int> sent(2 * (size_t)n, -1);
+  const BsArgs args{b->d_sys, b->d_items};
+  auto run = [&](void (*body)(const sgmg_batch*, const BsArgs&, int, hipStream_t)) -> int {
+    if (!std::equal(sent.begin(), sent.end(), hf)) {
+      sent.assign(hf, hf + 2 * (size_t)n);
+      SGMG_HIP(hipMemcpyAsync(st.flags, hf, 2 * (size_t)n * sizeof(int), hipMemcpyHostToDevice, s));
+    }
+    body(b, args, n, s);
+    TRY(check_launch());
     SGMG_HIP(hipMemcpyAsync(hs, st.scal, (size_t)n * kBsScalars * sizeof(double), hipMemcpyDeviceToHost, s));
     SGMG_HIP(hipStreamSynchronize(s));
     return 0;
@@ -3016,7 +3014,7 @@ int sgmg_pcg_solve_batch_staged(sgmg_batch* b, int nitems, const int* item_sys,
   auto sc = [&](int i, int k) { return hs[(size_t)i * kBsScalars + k]; };
   // prologue for every item: true residual from x0, first V-cycle
   for (int i = 0; i < n; ++i) { hf[i] = 1; hf[n + i] = 0; }
-  TRY(run(st.g_pro));
+  TRY(run(bs_prologue));
   for (int i = 0; i < n; ++i) {
     nf[i] = std::sqrt(sc(i, kBsFF));
     if (nf[i] == 0.0) {
@@ -3043,7 +3041,7 @@ int sgmg_pcg_solve_batch_staged(sgmg_batch* b, int nitems, const int* item_sys,
       nact += hf[n + i];
     }
     if (!nact) break;
-    TRY(run(st.g_it));
+    TRY(run(bs_iteration));
     int ncheck = 0;
     for (int i = 0; i < n; ++i) {
       hf[n + i] = 0;
@@ -3063,7 +3061,7 @@ int sgmg_pcg_solve_batch_staged(sgmg_batch* b, int nitems, const int* item_sys,
     if (ncheck) {
       // the true residual alone first: most checked items are done with it,
       // and a V-cycle of a few items costs as many launches as one of all
-      TRY(run(st.g_chk));
+      TRY(run(bs_residual));
       int nagain = 0;
       for (int i = 0; i < n; ++i) {
         if (!hf[i]) continue;
@@ -3074,7 +3072,7 @@ int sgmg_pcg_solve_batch_staged(sgmg_batch* b, int nitems, const int* item_sys,
       }
       // the prologue restarts the recurrence from it (beta = 0) for the items
       // that continue
-      if (nagain) TRY(run(st.g_pro));
+      if (nagain) TRY(run(bs_prologue));
       for (int i = 0; i < n; ++i) {
         if (!hf[i]) continue;
         const double rz = sc(i, kBsRZ);
@@ -3093,7 +3091,7 @@ int sgmg_pcg_solve_batch_staged(sgmg_batch* b, int nitems, const int* item_sys,
     nleft += hf[i];
   }
   if (nleft) {
-    TRY(run(st.g_chk));
+    TRY(run(bs_residual));
     for (int i = 0; i < n; ++i)
       if (hf[i]) rel_true[i] = std::sqrt(sc(i, kBsRR)) / (nf[i] > 0.0 ? nf[i] : 1.0);
   }
