@@ -334,13 +334,13 @@ int sgmg_pcg_solve_batch(sgmg_batch* b, int nitems, const int* item_sys, const d
 /* The same items solved stage by stage: every stage of the outer PCG (Sec.
  * 3.6) and of the V-cycle (Eq. vcycle) is one launch over all items, with as
  * many workgroups per item as its level has work (so the whole device works
- * on each stage, whatever the item sizes).  Three captured graphs are
- * replayed from a host loop: a prologue (r = f - K u in FP64, V-cycle, p = z,
+ * on each stage, whatever the item sizes).  A host loop launches three
+ * kinds of pass: a prologue (r = f - K u in FP64, V-cycle, p = z,
  * r.z), one PCG iteration (q = K p, alpha, x and r, V-cycle, beta, p) and the
- * residual alone; per-item flags copied in before each replay select the
- * items that take part.  After every iteration the host reads each item's
+ * residual alone; per-item flags, sent before a pass whose items are others,
+ * select the items that take part.  After every iteration the host reads each item's
  * scalars; an item whose recursive residual passes rtol runs the residual
- * graph, its FP64 true-residual check, and if that fails the prologue, its
+ * pass, its FP64 true-residual check, and if that fails the prologue, its
  * restart (beta = 0).  The coarsest products read each coefficient of a
  * system's symmetric inverse once for up to four of its load cases.  Same
  * algorithm and acceptance as sgmg_pcg_solve with Fletcher-Reeves beta.
@@ -351,9 +351,9 @@ int sgmg_pcg_solve_batch(sgmg_batch* b, int nitems, const int* item_sys, const d
  * the residuals as well); the two launch shapes and the stencil form of each
  * Galerkin level are timed on the item set at its first call and the fastest
  * kept.  Reductions per item in a fixed order.  All systems must share the smoothing step
- * counts.  Work vectors, tables and graphs are built on the first call for
+ * counts.  Work vectors and tables are built on the first call for
  * an item set.  *total_ms: wall time of the whole solve on the stream.
- * Synchronises once per iteration. */
+ * Waits once per iteration. */
 int sgmg_pcg_solve_batch_staged(sgmg_batch* b, int nitems, const int* item_sys,
                                 const double* const* f, double* const* u, double rtol, int maxit,
                                 sgmg_solve_info* infos, double* total_ms, void* stream);

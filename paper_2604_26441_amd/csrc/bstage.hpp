@@ -38,6 +38,9 @@ size_t bs_coarse_partials(int nL);
 void bs_fine64_res(const BsArgs& a, const BsTable& t, const int* flags, double* part, hipStream_t s);
 void bs_fine64_store_dot(const BsArgs& a, const BsTable& t, const int* flags, double* part,
                          hipStream_t s);
+void bs_flags(const int* host, int* flags, int m, hipStream_t s);
+void bs_publish(const double* scal, int m, double* host, double* host_seq, double seq,
+                hipStream_t s);
 void bs_finalize(const BsTable& t, int nitems, int nv, const double* part, const int* flags,
                  int what, double* scal, hipStream_t s);
 void bs_update_xr(const BsArgs& a, const BsTable& t, const int* flags, const double* scal,

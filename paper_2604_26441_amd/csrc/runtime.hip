@@ -1156,6 +1156,28 @@ static bool lookahead_ok(const std::vector<double>& hist, double rtol) {
   return hist[m - 1] * q * 0.25 >= rtol;
 }
 
+// Waits until a kernel on s has written target (or more) to the coherent host
+// address at, and checks now and then that the stream still has work, so that a
+// failed launch cannot leave the host spinning.
+static int wait_count(const volatile double* at, double target, hipStream_t s, const char* what) {
+  for (unsigned k = 1; *at < target; ++k) {
+    if ((k & 4095) == 0) {
+      const hipError_t q = hipStreamQuery(s);
+      if (q == hipSuccess && *at < target) {
+        set_error(std::string(what) + " did not arrive");
+        return SGMG_EHIP;
+      }
+      if (q != hipSuccess && q != hipErrorNotReady) {
+        set_error(std::string(what) + ": " + hipGetErrorString(q));
+        return SGMG_EHIP;
+      }
+    }
+    __builtin_ia32_pause();
+  }
+  std::atomic_thread_fence(std::memory_order_acquire);
+  return 0;
+}
+
 // Whether an iteration is replayed from a graph.  Consecutive graphs are 8.3 us
 // apart on the device, consecutive launches not at all, so a graph pays only
 // where the host could not queue the launches in time.  An iteration takes about
@@ -1228,9 +1250,7 @@ int sgmg_pcg_solve(sgmg_hierarchy* h, int precond, const double* f, double* u, d
   // The iteration of slot parity q writes its scalars to h_it + q SC_COUNT
   // from its last kernel, then the hierarchy's iteration count to
   // h_it[2 SC_COUNT].  The host waits for the count that the launch will
-  // write (no event between iteration graphs); while waiting it checks now
-  // and then that the stream still has work, so a failed launch cannot leave
-  // it spinning.
+  // write (no event between iterations).
   auto par = [](int sl) { return sl == SC_RZ0 ? 0 : 1; };
   double seq_next = 0.0;             // count the next iteration launch writes
   double seq_of[2] = {0.0, 0.0};     // count awaited per parity
@@ -1242,23 +1262,7 @@ int sgmg_pcg_solve(sgmg_hierarchy* h, int precond, const double* f, double* u, d
     return 0;
   };
   auto wait_iter = [&](int sl) -> int {
-    const double target = seq_of[par(sl)];
-    for (unsigned k = 1; *seq_host < target; ++k) {
-      if ((k & 4095) == 0) {
-        const hipError_t q = hipStreamQuery(s);
-        if (q == hipSuccess && *seq_host < target) {
-          set_error("PCG iteration scalars did not arrive");
-          return SGMG_EHIP;
-        }
-        if (q != hipSuccess && q != hipErrorNotReady) {
-          set_error(std::string("PCG iteration: ") + hipGetErrorString(q));
-          return SGMG_EHIP;
-        }
-      }
-      __builtin_ia32_pause();
-    }
-    std::atomic_thread_fence(std::memory_order_acquire);
-    return 0;
+    return wait_count(seq_host, seq_of[par(sl)], s, "PCG iteration scalars");
   };
   // Guarded BF16 (Sec. 3.5, 3.6): on a failed step, a non-positive or
   // non-finite r.z, or too little progress over guard_window iterations, the
@@ -2127,8 +2131,11 @@ struct sgmg_batch {
     double* part = nullptr;
     double* scal = nullptr;
     int* flags = nullptr;          // [0, n): prologue, [n, 2n): iteration
-    int* h_flags = nullptr;        // pinned mirror
-    double* h_scal = nullptr;      // pinned mirror
+    int* h_flags = nullptr;        // coherent, device-mapped: the flags, then the
+    double* h_scal = nullptr;      // scalars and the number of the pass they are of
+    const int* d_hflags = nullptr; // device addresses of the two
+    double* d_hscal = nullptr;
+    double seq = 0.0;              // passes queued so far
     int Lmax = 0, steps0 = 0, stepsL = 0;
     // level 0 on the BF16X3 MFMA operator: launch shape, (item, block)
     // table and per-item tile grids
@@ -2381,8 +2388,9 @@ void bs_prologue(const sgmg_batch* b, const BsArgs& a, int n, hipStream_t s) {
   bs_finalize(st.tv, n, 1, st.part, fl, 4, st.scal, s);
 }
 
-// One PCG iteration (flags [n, 2n)): q = K p, alpha, x and r, V-cycle, beta, p.
-void bs_iteration(const sgmg_batch* b, const BsArgs& a, int n, hipStream_t s) {
+// One PCG iteration (flags [n, 2n)) without its p: q = K p, alpha, x and r,
+// V-cycle, beta.
+void bs_iteration_scalars(const sgmg_batch* b, const BsArgs& a, int n, hipStream_t s) {
   const auto& st = b->st;
   const int* fl = st.flags + n;
   if (st.mfma64) {
@@ -2397,7 +2405,10 @@ void bs_iteration(const sgmg_batch* b, const BsArgs& a, int n, hipStream_t s) {
   bs_vcycle(st, a, fl, s);
   bs_dot_rz(a, st.tv, fl, 0, st.part, s);
   bs_finalize(st.tv, n, 1, st.part, fl, 3, st.scal, s);
-  bs_update_p(a, st.tv, fl, st.scal, s);
+}
+
+void bs_iteration_p(const sgmg_batch* b, const BsArgs& a, int n, hipStream_t s) {
+  bs_update_p(a, b->st.tv, b->st.flags + n, b->st.scal, s);
 }
 
 template <class F>
@@ -2424,7 +2435,8 @@ void bs_loop_steps(const sgmg_batch* b, const BsArgs& a, int n, int steps, doubl
                    hipStream_t s) {
   const auto& st = b->st;
   for (int k = 0; k < steps; ++k) {
-    bs_iteration(b, a, n, s);
+    bs_iteration_scalars(b, a, n, s);
+    bs_iteration_p(b, a, n, s);
     bs_decide_iter(n, st.scal, st.flags, st.lp, k & 1, rtol, maxit, s);
     bs_prologue(b, a, n, s);
     bs_decide_check(n, st.scal, st.flags, st.lp, k & 1, rtol, maxit, s);
@@ -2735,8 +2747,11 @@ int bs_prepare(sgmg_batch* b, int n, hipStream_t s) {
   BsTable k64t[kK64];
   if (mf64)
     for (int c = 0; c < kK64; ++c) k64t[c] = dts[k++];
-  if (hipHostMalloc((void**)&st.h_flags, flag_b, hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc((void**)&st.h_scal, scal_b, hipHostMallocDefault) != hipSuccess) {
+  const unsigned mapped = hipHostMallocMapped | hipHostMallocCoherent;
+  if (hipHostMalloc((void**)&st.h_flags, flag_b, mapped) != hipSuccess ||
+      hipHostMalloc((void**)&st.h_scal, scal_b + sizeof(double), mapped) != hipSuccess ||
+      hipHostGetDevicePointer((void**)&st.d_hflags, st.h_flags, 0) != hipSuccess ||
+      hipHostGetDevicePointer((void**)&st.d_hscal, st.h_scal, 0) != hipSuccess) {
     set_error("staged batch host allocation failed");
     return SGMG_ENOMEM;
   }
@@ -2999,22 +3014,28 @@ int sgmg_pcg_solve_batch_staged(sgmg_batch* b, int nitems, const int* item_sys,
   // of the rest (no kernel takes less than its launch), a graph starts later.
   // Flags that are on the device already are not copied again.
   std::vector<int> sent(2 * (size_t)n, -1);
+  const int nscal = n * kBsScalars;
+  volatile double* seq_host = hs + nscal;
+  *seq_host = st.seq;
   const BsArgs args{b->d_sys, b->d_items};
-  auto run = [&](void (*body)(const sgmg_batch*, const BsArgs&, int, hipStream_t)) -> int {
+  // What needs none of the host's decisions (after) runs while the host reads.
+  using Pass = void (*)(const sgmg_batch*, const BsArgs&, int, hipStream_t);
+  auto run = [&](Pass body, Pass after) -> int {
     if (!std::equal(sent.begin(), sent.end(), hf)) {
       sent.assign(hf, hf + 2 * (size_t)n);
-      SGMG_HIP(hipMemcpyAsync(st.flags, hf, 2 * (size_t)n * sizeof(int), hipMemcpyHostToDevice, s));
+      bs_flags(st.d_hflags, st.flags, 2 * n, s);
     }
+    st.seq += 1.0;
     body(b, args, n, s);
+    bs_publish(st.scal, nscal, st.d_hscal, st.d_hscal + nscal, st.seq, s);
+    if (after) after(b, args, n, s);
     TRY(check_launch());
-    SGMG_HIP(hipMemcpyAsync(hs, st.scal, (size_t)n * kBsScalars * sizeof(double), hipMemcpyDeviceToHost, s));
-    SGMG_HIP(hipStreamSynchronize(s));
-    return 0;
+    return wait_count(seq_host, st.seq, s, "staged batch scalars");
   };
   auto sc = [&](int i, int k) { return hs[(size_t)i * kBsScalars + k]; };
   // prologue for every item: true residual from x0, first V-cycle
   for (int i = 0; i < n; ++i) { hf[i] = 1; hf[n + i] = 0; }
-  TRY(run(bs_prologue));
+  TRY(run(bs_prologue, nullptr));
   for (int i = 0; i < n; ++i) {
     nf[i] = std::sqrt(sc(i, kBsFF));
     if (nf[i] == 0.0) {
@@ -3041,7 +3062,7 @@ int sgmg_pcg_solve_batch_staged(sgmg_batch* b, int nitems, const int* item_sys,
       nact += hf[n + i];
     }
     if (!nact) break;
-    TRY(run(bs_iteration));
+    TRY(run(bs_iteration_scalars, bs_iteration_p));
     int ncheck = 0;
     for (int i = 0; i < n; ++i) {
       hf[n + i] = 0;
@@ -3061,7 +3082,7 @@ int sgmg_pcg_solve_batch_staged(sgmg_batch* b, int nitems, const int* item_sys,
     if (ncheck) {
       // the true residual alone first: most checked items are done with it,
       // and a V-cycle of a few items costs as many launches as one of all
-      TRY(run(bs_residual));
+      TRY(run(bs_residual, nullptr));
       int nagain = 0;
       for (int i = 0; i < n; ++i) {
         if (!hf[i]) continue;
@@ -3072,7 +3093,7 @@ int sgmg_pcg_solve_batch_staged(sgmg_batch* b, int nitems, const int* item_sys,
       }
       // the prologue restarts the recurrence from it (beta = 0) for the items
       // that continue
-      if (nagain) TRY(run(bs_prologue));
+      if (nagain) TRY(run(bs_prologue, nullptr));
       for (int i = 0; i < n; ++i) {
         if (!hf[i]) continue;
         const double rz = sc(i, kBsRZ);
@@ -3091,7 +3112,7 @@ int sgmg_pcg_solve_batch_staged(sgmg_batch* b, int nitems, const int* item_sys,
     nleft += hf[i];
   }
   if (nleft) {
-    TRY(run(bs_residual));
+    TRY(run(bs_residual, nullptr));
     for (int i = 0; i < n; ++i)
       if (hf[i]) rel_true[i] = std::sqrt(sc(i, kBsRR)) / (nf[i] > 0.0 ? nf[i] : 1.0);
   }
