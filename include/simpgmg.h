@@ -108,9 +108,7 @@ typedef struct {
   const double* lambda_override; /* host array of n_levels-1 raw estimates, or NULL  */
   int use_graphs;            /* 1: each PCG iteration (K.p, updates, V-cycle) is
                                 replayed from a HIP graph captured once per
-                                hierarchy, where that is no slower (below
-                                100,000 DOFs, an iterative coarsest solve, the
-                                W-cycle); 0: always direct launches (same results) */
+                                hierarchy; 0: direct launches (same results)      */
   int cycle_gamma;           /* cycle index: 1 V-cycle (default), 2 W-cycle (Sec. 4
                                 E6(c)): every level whose coarser level is not the
                                 coarsest approximates its coarse residual equation

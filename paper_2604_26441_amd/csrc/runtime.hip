@@ -1178,20 +1178,8 @@ static int wait_count(const volatile double* at, double target, hipStream_t s, c
   return 0;
 }
 
-// Whether an iteration is replayed from a graph.  Consecutive graphs are 8.3 us
-// apart on the device, consecutive launches not at all, so a graph pays only
-// where the host could not queue the launches in time.  An iteration takes about
-// 23 launches, at most 55 us of host time; from 100,000 DOFs on the device needs
-// 70 us or more for it, below that the two are level (measured, graph -> direct:
-// 24^3 947 -> 945 us per solve, 40 x 24 x 36 in FP64 1552 -> 1509, 40^3 1554 ->
-// 1505, 64^3 6635 -> 6377, 80^3 5276 -> 5112).  The iterative coarsest solve and
-// the W-cycle make many more launches of short kernels and stay in the graph.
-static bool graphed(const sgmg_hierarchy* h) {
-  return h->o.use_graphs && (h->lev[0].g.n < 100000 || h->coarse_iter || h->o.cycle_gamma > 1);
-}
-
 static int run_body(sgmg_hierarchy* h, int precond, int slot, hipStream_t s) {
-  if (!graphed(h)) return pcg_body(h, precond, slot, s);
+  if (!h->o.use_graphs) return pcg_body(h, precond, slot, s);
   const int par = slot == SC_RZ0 ? 0 : 1;
   TRY(ensure_graph(h, precond, par, s));
   SGMG_HIP(hipGraphLaunch(h->iter_graph[precond][par], s));
@@ -1199,16 +1187,16 @@ static int run_body(sgmg_hierarchy* h, int precond, int slot, hipStream_t s) {
 }
 
 static int run_prologue(sgmg_hierarchy* h, int precond, hipStream_t s) {
-  if (!graphed(h)) return pcg_prologue_body(h, precond, s);
+  if (!h->o.use_graphs) return pcg_prologue_body(h, precond, s);
   TRY(ensure_graph(h, precond, 2, s));
   SGMG_HIP(hipGraphLaunch(h->iter_graph[precond][2], s));
   return 0;
 }
 
-// The V-cycle-preconditioned iteration graphs are part of the hierarchy (where
-// it uses them): captured at setup and after every re-assembly, so a solve only launches.
+// The V-cycle-preconditioned iteration graphs are part of the hierarchy:
+// captured at setup and after every re-assembly, so a solve only launches.
 static int capture_vcycle_graphs(sgmg_hierarchy* h, hipStream_t s) {
-  if (!graphed(h)) return 0;
+  if (!h->o.use_graphs) return 0;
   TRY(ensure_graph(h, 2, 0, s));
   TRY(ensure_graph(h, 2, 1, s));
   return ensure_graph(h, 2, 2, s);
