@@ -62,7 +62,7 @@ void build_mfma_atab(const KeTables& kt, uint16_t* out /* 2 * 64 * 8 */);
 void launch_l1_masked_nodes(const Grid& fine, const Grid& coarse, const uint8_t* ffix, uint8_t* flag,
                             int* list, hipStream_t s);
 void launch_galerkin_l1(const Grid& fine, const Grid& coarse, const double* E, const uint8_t* flag,
-                        const int* list, const double* gtab, const double* ke,
+                        const int* list, int listed, const double* gtab, const double* ke,
                         const uint8_t* ffix, const uint8_t* cfix, double* S, hipStream_t s);
 void launch_galerkin_stencil(const Grid& fine, const Grid& coarse, const double* Sf,
                              const uint8_t* cfix, double* Sc, hipStream_t s);

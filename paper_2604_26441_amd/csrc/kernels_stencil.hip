@@ -232,19 +232,134 @@ __global__ __launch_bounds__(64) void k_galerkin_l1_masked(
   }
 }
 
+__device__ inline bool elem_has_fixed(const Grid& f, const uint8_t* ffix, int ex, int ey, int ez) {
+  unsigned any = 0;
+#pragma unroll
+  for (int a = 0; a < 8; ++a)
+    any |= ffix[(ex + (a & 1)) + f.Nx * ((ey + ((a >> 1) & 1)) + f.Ny * (ez + (a >> 2)))];
+  return any != 0;
+}
+
+// The same products, all nodes in one kernel with a thread per 3 x 3 block: the
+// loops visit only the coarse elements that hold both nodes and the children
+// that exist, and a thread forms the nine entries of a masked child together.
+// Bound: the chain of loads and short products of the slowest lane of a wave.
+__global__ __launch_bounds__(256) void k_galerkin_l1_blocks(
+    Grid f, Grid c, const double* __restrict__ E, const uint8_t* __restrict__ flag,
+    const double* __restrict__ gtab, const double* __restrict__ ke,
+    const uint8_t* __restrict__ ffix, const uint8_t* __restrict__ cfix, double* __restrict__ S) {
+  const int I = blockIdx.x * 256 + threadIdx.x;
+  const int o = blockIdx.y;
+  if (I >= c.Nn) return;
+  const int ox = o % 3 - 1, oy = (o / 3) % 3 - 1, oz = o / 9 - 1;
+  const int Ix = I % c.Nx, t = I / c.Nx, Iy = t % c.Ny, Iz = t / c.Ny;
+  const int Jx = Ix + ox, Jy = Iy + oy, Jz = Iz + oz;
+  const bool near_fixed = flag[I] != 0;
+  auto weight = [](int t, int end) {               // as pat_weight
+    return t == 1 ? 0.5 : (t == 0) == (end == 0) ? 1.0 : 0.0;
+  };
+  double acc[9];
+#pragma unroll
+  for (int q = 0; q < 9; ++q) acc[q] = 0.0;
+  const bool jok = (unsigned)Jx < (unsigned)c.Nx && (unsigned)Jy < (unsigned)c.Ny &&
+                   (unsigned)Jz < (unsigned)c.Nz;
+  if (jok) {
+    const int cx0 = max(max(Ix, Jx) - 1, 0), cx1 = min(min(Ix, Jx), c.nx - 1);
+    const int cy0 = max(max(Iy, Jy) - 1, 0), cy1 = min(min(Iy, Jy), c.ny - 1);
+    const int cz0 = max(max(Iz, Jz) - 1, 0), cz1 = min(min(Iz, Jz), c.nz - 1);
+    for (int cz = cz0; cz <= cz1; ++cz)
+      for (int cy = cy0; cy <= cy1; ++cy)
+        for (int cx = cx0; cx <= cx1; ++cx) {
+          const int aI = (Ix - cx) + 2 * (Iy - cy) + 4 * (Iz - cz);
+          const int aJ = (Jx - cx) + 2 * (Jy - cy) + 4 * (Jz - cz);
+          const int npx = (cx == c.nx - 1 && (f.nx & 1)) ? 3 : 2;
+          const int npy = (cy == c.ny - 1 && (f.ny & 1)) ? 3 : 2;
+          const int npz = (cz == c.nz - 1 && (f.nz & 1)) ? 3 : 2;
+          for (int pz = 0; pz < npz; ++pz)
+            for (int py = 0; py < npy; ++py)
+              for (int px = 0; px < npx; ++px) {
+                const int ex = 2 * cx + px, ey = 2 * cy + py, ez = 2 * cz + pz;
+                const double Ee = E[ex + f.nx * (ey + f.ny * ez)];
+                if (!near_fixed || !elem_has_fixed(f, ffix, ex, ey, ez)) {
+                  const double* G = gtab + (size_t)(px + 3 * py + 9 * pz) * 576;
+#pragma unroll
+                  for (int d = 0; d < 3; ++d)
+#pragma unroll
+                    for (int e = 0; e < 3; ++e)
+                      acc[3 * d + e] += Ee * G[(3 * aI + d) * 24 + 3 * aJ + e];
+                  continue;
+                }
+                for (int al = 0; al < 8; ++al) {
+                  const double wa = weight(px + (al & 1), aI & 1) *
+                                    weight(py + ((al >> 1) & 1), (aI >> 1) & 1) *
+                                    weight(pz + (al >> 2), aI >> 2);
+                  if (wa == 0.0) continue;
+                  const unsigned fa = ffix[(ex + (al & 1)) + f.Nx * ((ey + ((al >> 1) & 1)) +
+                                                                      f.Ny * (ez + (al >> 2)))];
+                  for (int be = 0; be < 8; ++be) {
+                    const double wb = weight(px + (be & 1), aJ & 1) *
+                                      weight(py + ((be >> 1) & 1), (aJ >> 1) & 1) *
+                                      weight(pz + (be >> 2), aJ >> 2);
+                    if (wb == 0.0) continue;
+                    const unsigned fb = ffix[(ex + (be & 1)) + f.Nx * ((ey + ((be >> 1) & 1)) +
+                                                                        f.Ny * (ez + (be >> 2)))];
+                    for (int d = 0; d < 3; ++d) {
+                      if ((fa >> d) & 1u) continue;
+                      for (int e = 0; e < 3; ++e) {
+                        if ((fb >> e) & 1u) continue;
+                        acc[3 * d + e] += Ee * wa * wb * ke[(3 * al + d) * 24 + 3 * be + e];
+                      }
+                    }
+                  }
+                }
+              }
+        }
+  }
+  const unsigned fI = cfix[I];
+  const unsigned fJ = jok ? cfix[Jx + c.Nx * (Jy + c.Ny * Jz)] : 7u;
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+      const bool z = ((fI >> d) & 1u) || ((fJ >> e) & 1u);
+      S[(size_t)(o * 9 + 3 * d + e) * c.Nn + I] = z ? 0.0 : acc[3 * d + e];
+    }
+}
+
+// Which form (the bits are the same).  A listed node costs 53 ns (the nine
+// entries of a block load the same moduli and masks nine times), 145 ns with an
+// odd axis (27 possible children per element instead of 8), and 2048 of them at
+// least 90 or 170 us; the blocks' form costs a few times less per such node and
+// more per other node.  Measured, blocks / listed, us:
+//   even: 80^3 clamped face 553 / 241, 29 % listed 1320 / 1160, all 1085 / 3655;
+//     160 x 100 x 50, 27 % 1945 / 1745, 70 % 2150 / 4240; 48^3, 31 % 663 / 359,
+//     71 % 801 / 697; 64^3, 30 % 900 / 714, 70 % 913 / 1476
+//   odd: 17^3 face 285 / 215, 85 % 955 / 292; 33^3 face 242 / 330, 27 % 578 / 371,
+//     88 % 966 / 985; 61 x 45 x 53 face 275 / 335, 24 % 664 / 1000; 64 x 64 x 63
+//     face 292 / 581, 86 % 890 / 4820; 79 x 81 x 77 face 570 / 668, all 1490 / 9260
+// so with an odd axis only a mesh whose coarse nodes are one round is listed.
+static bool l1_listed_form(const Grid& fine, const Grid& coarse, int listed) {
+  if ((fine.nx | fine.ny | fine.nz) & 1) return coarse.Nn <= 2048;
+  return listed <= std::max(coarse.Nn / 3, 12000);
+}
+
 void launch_galerkin_l1(const Grid& fine, const Grid& coarse, const double* E, const uint8_t* flag,
-                        const int* list, const double* gtab, const double* ke,
+                        const int* list, int listed, const double* gtab, const double* ke,
                         const uint8_t* ffix, const uint8_t* cfix, double* S, hipStream_t s) {
   const dim3 grid(div_up(coarse.Nn, 256), 27);
-  // the list's length is known on the device: enough blocks for a face of
-  // nodes, more nodes take more rounds
-  const dim3 gm(std::min(div_up(coarse.Nn, 64), 32u), 243);
+  if (!l1_listed_form(fine, coarse, listed)) {
+    k_galerkin_l1_blocks<<<grid, 256, 0, s>>>(fine, coarse, E, flag, gtab, ke, ffix, cfix, S);
+    return;
+  }
+  const dim3 gm(std::min(div_up(listed, 64), 32u), 243);
   if ((fine.nx | fine.ny | fine.nz) & 1) {
     k_galerkin_l1<true><<<grid, 256, 0, s>>>(fine, coarse, E, flag, gtab, cfix, S);
-    k_galerkin_l1_masked<true><<<gm, 64, 0, s>>>(fine, coarse, E, list, gtab, ke, ffix, cfix, S);
+    if (listed > 0)
+      k_galerkin_l1_masked<true><<<gm, 64, 0, s>>>(fine, coarse, E, list, gtab, ke, ffix, cfix, S);
   } else {
     k_galerkin_l1<false><<<grid, 256, 0, s>>>(fine, coarse, E, flag, gtab, cfix, S);
-    k_galerkin_l1_masked<false><<<gm, 64, 0, s>>>(fine, coarse, E, list, gtab, ke, ffix, cfix, S);
+    if (listed > 0)
+      k_galerkin_l1_masked<false><<<gm, 64, 0, s>>>(fine, coarse, E, list, gtab, ke, ffix, cfix, S);
   }
 }
 

@@ -68,6 +68,7 @@ struct sgmg_hierarchy {
   double* gtab = nullptr;
   uint8_t* l1_mask = nullptr;  // coarse nodes next to a fixed DOF: flags
   int* l1_mlist = nullptr;     // and a list, its length first
+  int l1_nmask = 0;            // the length
   double* E64 = nullptr;
   float* E32 = nullptr;
   float* E32s = nullptr;     // E / s for the MFMA kernel
@@ -419,7 +420,8 @@ int assemble_operators(sgmg_hierarchy* h, const double* rho_or_E, hipStream_t s)
     Level& F = h->lev[l - 1];
     Level& C = h->lev[l];
     if (l == 1)
-      launch_galerkin_l1(F.g, C.g, h->E64, h->l1_mask, h->l1_mlist, h->gtab, h->ke64, F.fixn, C.fixn, C.S64, s);
+      launch_galerkin_l1(F.g, C.g, h->E64, h->l1_mask, h->l1_mlist, h->l1_nmask,
+                         h->gtab, h->ke64, F.fixn, C.fixn, C.S64, s);
     else
       launch_galerkin_stencil(F.g, C.g, F.S64, C.fixn, C.S64, s);
     launch_stencil_diag(C.g, C.S64, C.d64, s);
@@ -788,16 +790,20 @@ int sgmg_setup_hierarchy(const sgmg_options* opts, const double* rho_or_E, const
     set_error("mesh cannot be coarsened to the requested number of levels");
     return fail(SGMG_EINVAL);
   }
-  // masks on the device (one buffer), free counts on the host
+  // masks on the device (one buffer, followed by the list of the nodes next to
+  // a fixed DOF, whose first word is its length), free counts on the host
   DeviceArena arena;
   std::vector<uint8_t*> masks(grids.size());
   for (size_t l = 0; l < grids.size(); ++l) arena.add(&masks[l], grids[l].Nn);
-  const size_t mask_bytes = arena.bytes;
+  const size_t count_at = arena.bytes, mask_bytes = count_at + sizeof(int);
+  arena.add(&h->l1_mlist, (size_t)grids[1].Nn + 1);
+  arena.add(&h->l1_mask, grids[1].Nn);
   if ((rc = arena.commit(h))) return fail(rc);
   if (fixed_dof) launch_mask_from_dofs(fixed_dof, masks[0], g0.Nn, s);
   else launch_mask_cantilever(g0, masks[0], s);
   for (size_t l = 1; l < grids.size(); ++l)
     launch_mask_inject(grids[l - 1], grids[l], masks[l - 1], masks[l], s);
+  launch_l1_masked_nodes(g0, grids[1], masks[0], h->l1_mask, h->l1_mlist, s);
   if ((rc = check_launch())) return fail(rc);
   std::vector<uint8_t> hmask(mask_bytes);
   if (hipMemcpyAsync(hmask.data(), masks[0], mask_bytes, hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -805,6 +811,7 @@ int sgmg_setup_hierarchy(const sgmg_options* opts, const double* rho_or_E, const
     set_error("mask download failed");
     return fail(SGMG_EHIP);
   }
+  std::memcpy(&h->l1_nmask, hmask.data() + count_at, sizeof(int));
   std::vector<int> nfree(grids.size());
   for (size_t l = 0; l < grids.size(); ++l) {
     const uint8_t* m = hmask.data() + (masks[l] - masks[0]);
@@ -861,8 +868,6 @@ int sgmg_setup_hierarchy(const sgmg_options* opts, const double* rho_or_E, const
   arena.add(&h->E64, g0.nel);
   arena.add(&h->E32, g0.nel);
   arena.add(&h->E32s, g0.nel);
-  arena.add(&h->l1_mask, grids[1].Nn);
-  arena.add(&h->l1_mlist, (size_t)grids[1].Nn + 1);
   arena.add(&h->atab, 2 * 64 * 8);
   arena.add(&h->atab64, 2 * 6 * 64);
   // reductions, scalars, PCG vectors
@@ -918,7 +923,6 @@ int sgmg_setup_hierarchy(const sgmg_options* opts, const double* rho_or_E, const
   if ((rc = arena.commit(h))) return fail(rc);
   for (int l = 0; l < L; ++l)
     for (void* v : {h->lev[l].x[0], h->lev[l].x[1]}) hipMemsetAsync(v, 0, h->lev[l].g.n * es[l], s);
-  launch_l1_masked_nodes(g0, grids[1], masks[0], h->l1_mask, h->l1_mlist, s);
   hipMemsetAsync(h->ws.counter, 0, sizeof(unsigned), s);
   hipMemsetAsync(h->sc, 0, SC_COUNT * sizeof(double), s);
   std::vector<double> gt, at64(2 * 6 * 64);
