@@ -161,9 +161,10 @@ __device__ inline double oc_candidate(double rho, double ratio, double lam, doub
 // Without projection the physical volume is linear in the candidate,
 //   sum_e (F x)_e = sum_i c_i x_i,  c = F^T 1,
 // so one evaluation needs no filter, and one pass over the elements evaluates
-// the midpoints of every outcome of the next six halvings (63 multipliers): 13
-// passes instead of about 77.  Bound: launch latency, 7.5 + 5.6 us a pass.  With projection each halving is one
-// pass through the filter at one multiplier.
+// the midpoints of every outcome of the next six halvings (63 multipliers): about
+// 77 halvings take 13 passes (14 are queued before the first readback).  Bound:
+// launch latency, 7.5 + 5.6 us a pass.  With projection each halving is one pass
+// through the filter at one multiplier.
 constexpr int kOcTile = 1024;
 
 // Interval (l1, l2) of node k of the tree of coming halvings (root 0; children

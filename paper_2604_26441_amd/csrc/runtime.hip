@@ -3447,15 +3447,23 @@ int sgmg_simp_oc_update(sgmg_simp* s, double* rho, double* lambda, double* volum
   const int n = p.nx * p.ny * p.nz;
   const double target = p.volfrac * n;
   hipStream_t st = as_stream(stream);
-  // passes of kOcLevels halvings (one with projection), the update gated on
-  // the bisection's end, then one readback; a bisection that is not done by
-  // then goes on.  1e9 down to a relative width of 1e-9 takes about 60 halvings
-  // plus the multiplier's own magnitude.
+  // passes of kOcLevels halvings (one with projection), the update gated on the
+  // bisection's end, then one readback; a bisection that is not done by then goes
+  // on.  No more passes than oc_max_halvings allows, and at first, without
+  // projection, 84 halvings' worth: the 1e9 down to a relative width of 1e-9
+  // takes about 60 plus the multiplier's own magnitude, and an idle pass takes 5
+  // us.  With projection there are six times the passes, so as many as a
+  // multiplier of 1 needs for the asked width (16 x 8 x 8 and 60^3, us, always 84
+  // -> this: default limits 902 -> 828, 1554 -> 1455; a width of 1e-2 649 -> 510,
+  // 1013 -> 864; ten halvings 463 -> 180, 541 -> 301; one 466 -> 46, 527 -> 60).
   const int nb = oc_apply_blocks(n), levels = p.beta == 0.0 ? kOcLevels : 1;
   s->h_part.resize(nb);
   launch_oc_init(s->oc, st);
+  int chunk = 84, done = 0;
+  if (levels == 1) chunk = std::min(84, std::max(1, 1 + std::ilogb(0.5e9 / p.oc_tol)));
   do {
-    for (int k = 0; k < 84; k += levels)
+    const int todo = std::min(chunk, p.oc_max_halvings - done);
+    for (int k = 0; k < todo; k += levels)
       launch_oc_pass(p.nx, p.ny, p.nz, p.rmin, s->W, s->cvol, rho, s->ratio, p.move, p.beta, p.eta,
                      target, p.oc_tol, p.oc_max_halvings, s->oc, s->oc_part, st);
     launch_oc_apply(n, rho, s->ratio, s->oc, p.move, s->ws, st);
@@ -3464,6 +3472,8 @@ int sgmg_simp_oc_update(sgmg_simp* s, double* rho, double* lambda, double* volum
     SGMG_HIP(hipMemcpyAsync(s->h_part.data(), s->ws.partials, nb * sizeof(double),
                             hipMemcpyDeviceToHost, st));
     SGMG_HIP(hipStreamSynchronize(st));
+    done = s->h_oc->halvings;
+    chunk = 24;
   } while (s->h_oc->status == 0);
   if (s->h_oc->status == 2) { set_error("OC volume is not finite"); return SGMG_EINVAL; }
   const double lmid = s->h_oc->lmid, vol = s->h_oc->vol;
