@@ -1781,9 +1781,20 @@ int sgmg_autotune(sgmg_hierarchy* h, int* shape_out, void* stream) {
   hipEventCreate(&e0);
   hipEventCreate(&e1);
   const int rows_c[] = {4, 8};
-  const int z_c[] = {2, 3, 4, 6, 8, 16, 32, 12, 20, 24, 29, 37, 43};
-  const int n_z = 7, n_z_store = 13;   // a plain product's chunks are long, and how many of
-                                       // them fill the last wave of blocks matters more
+  const std::vector<int> z_c = {2, 3, 4, 6, 8, 16, 32};
+  // A plain product's chunks are long, so a short last chunk and a last round of
+  // blocks that is nearly empty cost more: the even splits of this mesh's planes
+  // into chunks of 9 to 48, a tenth apart or more, stand for the long ones (fastest
+  // BF16X3 shape, fixed lengths 12, 16, 20, 24, 29, 32, 37, 43 -> even splits:
+  // 180 x 90 x 150 30.2 -> 26.8 us, 96 x 96 x 192 24.4 -> 22.0, 160^3 40.7 -> 38.8,
+  // 120^3 24.4 -> 23.4; 256^3 and 220^3, whose splits those were, and up to 100^3
+  // the same).
+  std::vector<int> z_plain = {2, 3, 4, 6, 8};
+  for (int k = 1, last = 0; div_up(L0.g.Nz, k) > 8; ++k) {
+    const int z = div_up(L0.g.Nz, k);
+    if (z > 48 || (last && 10 * last < 11 * z)) continue;
+    z_plain.push_back(last = z);
+  }
   double* u64 = nullptr;
   double* y64 = nullptr;
   int rc = 0;
@@ -1817,8 +1828,7 @@ int sgmg_autotune(sgmg_hierarchy* h, int* shape_out, void* stream) {
       hipEventElapsedTime(&best_ms, e0, e1);
       best_r = best_z = 0;
       // vector-ALU sum-factorised tiles (rows 1)
-      for (int iz = 0; iz < n_z; ++iz) {
-        const int z = z_c[iz];
+      for (int z : z_c) {
         if (z > L0.g.Nz && z != z_c[0]) continue;
         for (int w = 0; w < 3; ++w)
           launch_apply_fine_sf64(L0.g, z, h->E64, h->kt.lam, h->kt.mu, u64, L0.fixn,
@@ -1843,9 +1853,11 @@ int sgmg_autotune(sgmg_hierarchy* h, int* shape_out, void* stream) {
     // plain: y = K u; otherwise (BF16, BF16X3) a Chebyshev smoothing step, the
     // epilogue of most V-cycle applications
     auto tune_tiles = [&](bool plain) {
+      // (more shapes, fewer launches of each)
+      const bool longer = plain && q < 2;
+      const int reps = longer ? 12 : 30;
       for (int rows : rows_c) {
-        for (int iz = 0; iz < (plain && q < 2 ? n_z_store : n_z); ++iz) {
-          const int z = z_c[iz];
+        for (int z : longer ? z_plain : z_c) {
           if (z > L0.g.Nz && z != z_c[0]) continue;
           auto launch = [&]() {
             if (q == 2)
@@ -1860,7 +1872,7 @@ int sgmg_autotune(sgmg_hierarchy* h, int* shape_out, void* stream) {
           };
           for (int w = 0; w < 3; ++w) launch();
           hipEventRecord(e0, s);
-          for (int r = 0; r < 30; ++r) launch();
+          for (int r = 0; r < reps; ++r) launch();
           hipEventRecord(e1, s);
           if ((rc = check_launch())) return;
           if (hipEventSynchronize(e1) != hipSuccess) {
@@ -1887,8 +1899,7 @@ int sgmg_autotune(sgmg_hierarchy* h, int* shape_out, void* stream) {
     if (q == 2) {
       if (best_r != 1) break;
       best_ms = 1e30f;                            // the same tiles with p.q
-      for (int iz = 0; iz < n_z && !rc; ++iz) {
-        const int z = z_c[iz];
+      for (int z : z_c) {
         if (z > L0.g.Nz && z != z_c[0]) continue;
         auto launch = [&]() {
           launch_apply_fine_sf64(L0.g, z, h->E64, h->kt.lam, h->kt.mu, u64, L0.fixn,
