@@ -255,15 +255,17 @@ int sgmg_lanczos(sgmg_hierarchy* h, int precond, int m, const double* g, double 
 /* Autotuner of the fine operators' launch shape: times each candidate
  * (element rows per wave tile: 4, 8; owned node planes per wave: 2, 3, 4,
  * 6, 8, 16, 32) on this hierarchy's mesh for the BF16, BF16X3 and FP64 kernels
- * (the BF16 family in the smoothing epilogue and once more, up to 43 planes,
- * as a plain product, which has a shape of its own; FP64 as a plain product),
+ * (the BF16 family in the smoothing epilogue and once more, with even splits of
+ * the mesh's planes up to 48, as a plain product, which has a shape of its own;
+ * FP64 as a plain product),
  * keeps the fastest in h and in a process-wide cache keyed by (nx, ny, nz,
  * variant) that later setups of the same mesh read.  shape_out (host, 6
  * ints, may be NULL) receives (rows, planes) for BF16, BF16X3 (smoothing
  * steps), then FP64; for FP64 the vector-ALU node kernel is a candidate too,
  * reported as (0, 0), and so are the vector-ALU sum-factorised tiles with 2 ..
  * 32 planes, reported as (1, planes) ((1, 4) is the FP64 choice of an untuned
- * mesh; the PCG's product with its dot has planes of its own, not reported).
+ * mesh; the PCG's product with its dot has a kernel and planes of its own, not
+ * reported).
  * When the hierarchy holds the level-1 element products (stencil_form 0 or 3,
  * FP64 level 1 above the coarsest) it also times level 1 from the stored
  * stencil against the products with 1 to 6 and 8 planes and keeps the faster

@@ -83,8 +83,11 @@ struct sgmg_hierarchy {
   // vector ALU 45 %, the matrix cores 30 %
   int store_rows[2] = {4, 4};
   int store_zchunk[2] = {4, 4};
-  // planes of the FP64 tiles where they also form p.q (rows 1): that kernel keeps
-  // the 16 x 4 tiles, so its chunk is timed by itself
+  // and for FP64 products that also form p.q, timed by themselves: the tiles keep
+  // 16 x 4 elements there, and the node kernel has no split by corners (which
+  // makes it the fastest plain product on small meshes, but not with p.q: a
+  // BF16X3 solve of 24^3 took 1197 us with it, 1128 with the tiles)
+  int dot_rows = 1;
   int dot_zchunk = 4;
   uint16_t* atab = nullptr;  // MFMA A-operand table (BF16 bits)
   double* atab64 = nullptr;  // FP64 MFMA A-operand table
@@ -152,7 +155,8 @@ namespace {
 constexpr size_t kMinPartials = 1 << 16;
 
 // Process-wide autotuning results: (nx, ny, nz, variant) -> MFMA launch shape
-// (rows, z-chunk); variant 1 = BF16, 3 = BF16X3, 64 = FP64.
+// (rows, z-chunk); variant 1 = BF16, 3 = BF16X3, 64 = FP64, 201 and 203 plain
+// products with BF16 and BF16X3, 264 FP64 with p.q.
 std::mutex g_tune_mu;
 std::map<std::tuple<int, int, int, int>, std::pair<int, int>> g_tune;
 
@@ -296,12 +300,12 @@ int apply_level<double>(const sgmg_hierarchy* h, int l, sgmg_prec prec, const do
     set_error("double vectors require SGMG_F64");
     return SGMG_EINVAL;
   }
-  if (l == 0 && h->mfma_rows[2] == 1 && sf64_size_ok(L.g)) {
-    launch_apply_fine_sf64(L.g, ep.want_dot ? h->dot_zchunk : h->mfma_zchunk[2], h->E64, h->kt.lam,
-                           h->kt.mu, x, L.fixn, ep, s);
-  } else if (l == 0 && h->mfma_rows[2] > 1 && mfma64_size_ok(L.g)) {
-    launch_apply_fine_mfma64(L.g, h->mfma_rows[2], h->mfma_zchunk[2], h->E64, h->atab64, x, L.fixn,
-                             ep, s);
+  const int rows = ep.want_dot ? h->dot_rows : h->mfma_rows[2];
+  const int zchunk = ep.want_dot ? h->dot_zchunk : h->mfma_zchunk[2];
+  if (l == 0 && rows == 1 && sf64_size_ok(L.g)) {
+    launch_apply_fine_sf64(L.g, zchunk, h->E64, h->kt.lam, h->kt.mu, x, L.fixn, ep, s);
+  } else if (l == 0 && rows > 1 && mfma64_size_ok(L.g)) {
+    launch_apply_fine_mfma64(L.g, rows, zchunk, h->E64, h->atab64, x, L.fixn, ep, s);
   } else if (l == 0) {
     launch_apply_fine_node<double>(L.g, h->E64, h->ke64, x, L.fixn, ep, s);
   } else if (l == 1 && h->l1_mf && !ep.want_dot) {
@@ -356,11 +360,10 @@ int apply_level<float>(const sgmg_hierarchy* h, int l, sgmg_prec prec, const flo
 // size: the MFMA tile grid or one block per 256 nodes).
 int k64_dot_partials(const sgmg_hierarchy* h) {
   const Level& L = h->lev[0];
-  if (h->mfma_rows[2] == 1 && sf64_size_ok(L.g))
+  if (h->dot_rows == 1 && sf64_size_ok(L.g))
     return (int)apply_fine_sf64_blocks(L.g, h->dot_zchunk);
-  if (h->mfma_rows[2] > 1 && mfma64_size_ok(L.g))
-    return (int)apply_fine_mfma_blocks(L.g, h->mfma_rows[2] == 4 ? 4 : 8,
-                                       h->mfma_zchunk[2] < 1 ? 1 : h->mfma_zchunk[2]);
+  if (h->dot_rows > 1 && mfma64_size_ok(L.g))
+    return (int)apply_fine_mfma_blocks(L.g, h->dot_rows == 4 ? 4 : 8, std::max(1, h->dot_zchunk));
   return div_up(L.g.Nn, 256);
 }
 
@@ -770,7 +773,9 @@ int sgmg_setup_hierarchy(const sgmg_options* opts, const double* rho_or_E, const
     h->mfma_rows[q] = sh.first;
     h->mfma_zchunk[q] = sh.second;
     if (q == 2) {
-      h->dot_zchunk = tuned_shape(opts->nx, opts->ny, opts->nz, 264, sh).second;
+      const auto dot = tuned_shape(opts->nx, opts->ny, opts->nz, 264, sh);
+      h->dot_rows = dot.first;
+      h->dot_zchunk = dot.second;
       break;
     }
     const auto st = tuned_shape(opts->nx, opts->ny, opts->nz, q ? 203 : 201, sh);
@@ -1646,6 +1651,7 @@ int sgmg_set_launch_shape(sgmg_hierarchy* h, int variant, int rows, int planes) 
     h->store_rows[variant] = rows;
     h->store_zchunk[variant] = planes;
   } else {
+    h->dot_rows = rows;
     h->dot_zchunk = planes;
   }
   for (auto& row : h->iter_graph)        // captured graphs hold the old launch shape
@@ -1896,30 +1902,41 @@ int sgmg_autotune(sgmg_hierarchy* h, int* shape_out, void* stream) {
     h->mfma_zchunk[q] = best_z;
     if (shape_out) { shape_out[2 * q] = best_r; shape_out[2 * q + 1] = best_z; }
     keep(key);
-    if (q == 2) {
-      if (best_r != 1) break;
-      best_ms = 1e30f;                            // the same tiles with p.q
-      for (int z : z_c) {
-        if (z > L0.g.Nz && z != z_c[0]) continue;
-        auto launch = [&]() {
-          launch_apply_fine_sf64(L0.g, z, h->E64, h->kt.lam, h->kt.mu, u64, L0.fixn,
-                                 epi_store_partials<double>(y64, h->ws), s);
-        };
+    if (q == 2) {                                 // the same with p.q
+      const int plain_r = best_r, plain_z = best_z;
+      best_ms = 1e30f;
+      auto time_dot = [&](int rows, int z, auto&& launch) {
         for (int w = 0; w < 3; ++w) launch();
         hipEventRecord(e0, s);
         for (int r = 0; r < 20; ++r) launch();
         hipEventRecord(e1, s);
-        if ((rc = check_launch())) break;
+        if ((rc = check_launch())) return;
         if (hipEventSynchronize(e1) != hipSuccess) {
           rc = SGMG_EHIP;
           set_error("autotune sync failed");
-          break;
+          return;
         }
         float ms = 0.f;
         hipEventElapsedTime(&ms, e0, e1);
-        if (ms < best_ms) { best_ms = ms; best_z = z; }
+        if (ms < best_ms) { best_ms = ms; best_r = rows; best_z = z; }
+      };
+      const Epi<double> ep = epi_store_partials<double>(y64, h->ws);
+      for (int z : z_c) {
+        if (rc || (z > L0.g.Nz && z != z_c[0])) continue;
+        time_dot(1, z, [&]() {
+          launch_apply_fine_sf64(L0.g, z, h->E64, h->kt.lam, h->kt.mu, u64, L0.fixn, ep, s);
+        });
       }
+      if (!rc && plain_r == 0)
+        time_dot(0, 0, [&]() {
+          launch_apply_fine_node<double>(L0.g, h->E64, h->ke64, u64, L0.fixn, ep, s);
+        });
+      if (!rc && plain_r > 1)
+        time_dot(plain_r, plain_z, [&]() {
+          launch_apply_fine_mfma64(L0.g, plain_r, plain_z, h->E64, h->atab64, u64, L0.fixn, ep, s);
+        });
       if (rc) break;
+      h->dot_rows = best_r;
       h->dot_zchunk = best_z;
       keep(264);
       break;
