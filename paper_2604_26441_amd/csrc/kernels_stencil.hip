@@ -1062,7 +1062,8 @@ __global__ __launch_bounds__(256) void k_cpcg_init(int n, const double* __restri
   }
 }
 
-// Block (b, d): row d of 64 nodes; wave pz sums 9 stencil offsets.  Offsets
+// Block (b, d): row d of 64 nodes (ROWS = 3: all three rows); a wave sums the 9
+// stencil offsets of plane pz for one row.  Offsets
 // outside the grid read the node itself (a valid address) and add nothing.
 // K p_k is accumulated as K z_k + beta_k (K p_{k-1}) (the same product up
 // to rounding), so the stencil and vector loads need no beta and are all in
@@ -1075,8 +1076,8 @@ __global__ __launch_bounds__(256) void k_cpcg_init(int n, const double* __restri
 // loaded coalesced into LDS once instead of 54 strided loads per thread.  26 x
 // 13 x 7 nodes: 8.8 us with neither, 7.9 us staged, now 6.5 us (an empty launch
 // takes about 2 us).
-template <bool STAGED>
-__global__ __launch_bounds__(192) void k_cpcg_apply(Grid g, const double* __restrict__ S,
+template <bool STAGED, int ROWS>
+__global__ __launch_bounds__(192 * ROWS) void k_cpcg_apply(Grid g, const double* __restrict__ S,
                                                     const uint8_t* __restrict__ fixn,
                                                     const double* __restrict__ z,
                                                     const double* __restrict__ pold,
@@ -1084,10 +1085,10 @@ __global__ __launch_bounds__(192) void k_cpcg_apply(Grid g, const double* __rest
                                                     const double* __restrict__ prz,
                                                     double* __restrict__ ppq,
                                                     const int* __restrict__ done, int k, int nbu) {
-  __shared__ double part[2][3][64];
+  __shared__ double part[2][3][ROWS][64];
   extern __shared__ double band[];               // [z, pold][oz][3 * cpcg_band]
-  const int lane = threadIdx.x & 63, pz = threadIdx.x >> 6;
-  const int d = blockIdx.y;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, pz = w / ROWS;
+  const int d = ROWS == 1 ? blockIdx.y : w % ROWS, dl = ROWS == 1 ? 0 : d;
   const int node0 = blockIdx.x * 64 + lane;
   const bool in = node0 < g.Nn;
   const int node = in ? node0 : g.Nn - 1;
@@ -1106,7 +1107,7 @@ __global__ __launch_bounds__(192) void k_cpcg_apply(Grid g, const double* __rest
   if (STAGED) {
     const int first = 3 * ((int)blockIdx.x * 64 - g.Nx - 1);
 #pragma unroll 4
-    for (int e = threadIdx.x; e < 3 * wb; e += 192) {
+    for (int e = threadIdx.x; e < 3 * wb; e += 192 * ROWS) {
       const int oz = e / wb;
       const int at = min(max(first + (e - oz * wb) + 3 * (oz - 1) * g.Nx * g.Ny, 0), g.n - 1);
       band[e] = z[at];
@@ -1150,8 +1151,8 @@ __global__ __launch_bounds__(192) void k_cpcg_apply(Grid g, const double* __rest
     az += (okm >> qq) & 1u ? vz : 0.0;
     ap += (okm >> qq) & 1u ? vp : 0.0;
   }
-  part[0][pz][lane] = az;
-  part[1][pz][lane] = ap;
+  part[0][pz][dl][lane] = az;
+  part[1][pz][dl][lane] = ap;
   for (int b = lane + 64; b < nbu; b += 64) {
     t1 += rz1[b];
     t0 += rz0[b];
@@ -1162,8 +1163,8 @@ __global__ __launch_bounds__(192) void k_cpcg_apply(Grid g, const double* __rest
   if (pz != 1) return;
   double dot = 0.0;
   if (in) {
-    const double kz = (part[0][0][lane] + part[0][1][lane]) + part[0][2][lane];
-    const double kp = (part[1][0][lane] + part[1][1][lane]) + part[1][2][lane];
+    const double kz = (part[0][0][dl][lane] + part[0][1][dl][lane]) + part[0][2][dl][lane];
+    const double kp = (part[1][0][dl][lane] + part[1][1][dl][lane]) + part[1][2][dl][lane];
     const double pown = __builtin_fma(beta, pold_own, zown);
     const double y = (fx >> d) & 1u ? 0.0 : __builtin_fma(beta, kp, kz);
     pnew[dof] = pown;
@@ -1231,14 +1232,21 @@ void launch_coarse_pcg(const Grid& g, const double* S, const double* dinv, const
   // coarsest grid that long is rare; it keeps the strided loads)
   const size_t bands = 2 * 9 * (size_t)cpcg_band(g) * sizeof(double);
   const bool staged = bands <= 48 * 1024;
+  // three rows per block where such blocks fill most of the chip's 256 compute
+  // units just once (one V-cycle with 60 steps, a row per block -> three:
+  // 9261 nodes, 145 blocks, 725 -> 729 us, 12167 804 -> 749, 15625 958 -> 844;
+  // 4913 616 -> 683; 17238, 270 blocks, 1470 -> 1605, 35937 1773 -> 2031)
+  const bool rows3 = nba > 150 && nba <= 256;
   for (int k = 0; k < iters; ++k) {
     const double* pold = k == 0 ? z : pp[(k + 1) & 1];
-    if (staged)
-      k_cpcg_apply<true><<<dim3(nba, 3), 192, bands, s>>>(g, S, fixn, z, pold, pp[k & 1], q, prz,
-                                                          ppq, done, k, nbu);
-    else
-      k_cpcg_apply<false><<<dim3(nba, 3), 192, 0, s>>>(g, S, fixn, z, pold, pp[k & 1], q, prz, ppq,
-                                                       done, k, nbu);
+#define SGMG_CPCG(STAGED, ROWS)                                                              \
+  k_cpcg_apply<STAGED, ROWS><<<dim3(nba, 3 / ROWS), 192 * ROWS, STAGED ? bands : 0, s>>>(    \
+      g, S, fixn, z, pold, pp[k & 1], q, prz, ppq, done, k, nbu)
+    if (staged && rows3) SGMG_CPCG(true, 3);
+    else if (staged) SGMG_CPCG(true, 1);
+    else if (rows3) SGMG_CPCG(false, 3);
+    else SGMG_CPCG(false, 1);
+#undef SGMG_CPCG
     k_cpcg_update<<<nbu, 256, 0, s>>>(g.n, dinv, x, r, z, pp[k & 1], q, prz, ppq, done, k, nba);
   }
 }
