@@ -25,8 +25,8 @@
 // (relative 1e-16 per entry).
 //
 // Work decomposition: one wave owns a tile of 16 elements in x by 4 element
-// rows in y, or 8 by 8 (sf_launch takes the one that needs fewer tiles), and marches along z over a chunk of
-// node planes, which it stages in its own LDS ring (no barrier, nothing
+// rows in y, or 8 by 8 (see sf_launch), and marches along z over a chunk of node
+// planes, which it stages in its own LDS ring (no barrier, nothing
 // shared between waves).  Each lane computes one element per plane and owns
 // its (-x, -y, -z) node.  Along z the transform is split: a node face is
 // transformed over (x, y) once and carried to the next plane (it is the top
@@ -588,18 +588,27 @@ SfLaunch sf_launch(const Grid& g, int zchunk, int lx) {
   m.blocks = div_up(m.ntiles, kSfWaves);
   return m;
 }
-// Tiles of 16 x 4 or 8 x 8 elements, whichever takes fewer for the grid: the
-// owned nodes are 15 x 3 (70 % of the lanes) or 7 x 7 (77 %), less what the
-// grid's edges leave empty (31 x 31 nodes: 33 tiles or 25).  Every node sums
-// its eight elements in the same order with both.  A wave computes a plane in
-// 1.75 us at level 1 (1040 FP64 instructions; 0.75 us at the fine level), and a
-// level-1 wave has a SIMD to itself, so the time goes in steps of blocks per
-// compute unit: level 1 of 80^3 took 10.3 us (3 planes per wave; with 2 the
-// blocks did not fit in one round, 15.6 us), now 8.8 us with 2; the fine product
-// of 80^3 13.4 -> 12.5 us, of 200 x 100 x 50 22.6 -> 20.3 us.
+// Tiles of 16 x 4 or 8 x 8 elements: the owned nodes are 15 x 3 (70 % of the
+// lanes) or 7 x 7 (77 %), less what the grid's edges leave empty (31 x 31 nodes:
+// 33 tiles or 25).  Every node sums its eight elements in the same order with
+// both.  A wave computes a plane in 1.75 us at level 1 (1040 FP64 instructions;
+// 0.75 us at the fine level), and a level-1 wave has a SIMD to itself, so the time
+// goes in steps of blocks per compute unit.
+// Level 1 takes the fewer tiles: 80^3 with 2 planes 15.9 us (16 x 4; with the
+// listed rows the blocks do not fit in one round) and 9.3; where they make no
+// difference the two are within 1.5 %.
 SfLaunch sf_launch(const Grid& g, int zchunk) {
   const SfLaunch a = sf_launch(g, zchunk, 16), b = sf_launch(g, zchunk, 8);
   return b.ntiles < a.ntiles ? b : a;
+}
+// The fine product takes 8 x 8 where they make fewer rounds of 256 blocks: 60^3
+// with 3 planes 9.8 -> 8.6 us (3 rounds, 2), 80^3 with 4 13.9 -> 12.5 (4, 3), 200 x
+// 100 x 50 with 6 21.9 -> 18.8 (5, 4).  In as many rounds an 8 x 8 tile is the
+// slower one, by 2 to 5 % (60^3 with 4 planes 9.2 and 9.4 us, 64^3 9.2 and 9.5, 72
+// x 73 x 73 11.4 and 11.9).
+SfLaunch sf_launch_fine(const Grid& g, int zchunk) {
+  const SfLaunch a = sf_launch(g, zchunk, 16), b = sf_launch(g, zchunk, 8);
+  return div_up(b.blocks, 256) < div_up(a.blocks, 256) ? b : a;
 }
 
 }  // namespace
@@ -708,7 +717,7 @@ void launch_apply_fine_sf64(const Grid& g, int zchunk, const double* E, double l
   if (zchunk < 1) zchunk = 1;
   const bool dot = ep.mode == EPI_STORE && ep.want_dot;
   // the dot's partials are those of the 16 x 4 tiles (apply_fine_sf64_blocks)
-  const SfLaunch m = dot ? sf_launch(g, zchunk, 16) : sf_launch(g, zchunk);
+  const SfLaunch m = dot ? sf_launch(g, zchunk, 16) : sf_launch_fine(g, zchunk);
   const SfCoef cf = sf_coef(lam, mu);
   const dim3 grid(m.blocks), block(64 * kSfWaves);
 #define SGMG_SF(M, LX)                                                                     \
