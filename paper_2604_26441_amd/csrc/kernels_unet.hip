@@ -490,12 +490,12 @@ void launch_pack_conv3(const float* w, int up, int Ci, int Co, uint4* wp, hipStr
 }
 
 void launch_conv3_mfma(const float* x, int up, int N, int Ci, int Co, int D, int H, int W,
-                       const uint4* wp, const float* b, int relu, float* rpre, const float* add,
-                       float* y, hipStream_t s, const float* hw, const float* hb, float* hy) {
+                       const uint4* wp, const float* b, int relu, const float* add, float* y,
+                       hipStream_t s, const float* hw, const float* hb, float* hy) {
   const int Cop = (Co + kCOB - 1) / kCOB * kCOB, ntile = Cop / 16;
   const int tx = div_up(W, kCTX), ty = div_up(H, kCTY), tz = div_up(D, kCTZ);
   const long tiles = (long)tx * ty * tz;
-  const ConvOut o{b, relu, rpre, add, y, hw, hb, hy};
+  const ConvOut o{b, relu, nullptr, add, y, hw, hb, hy};
   // channel tiles per block: the largest power of two dividing ntile (<= 4;
   // one for upsampled inputs, whose operands serve three products anyway: two
   // took 73 us instead of 58 for the 64 -> 32 layer of the 104^3 grid), halved

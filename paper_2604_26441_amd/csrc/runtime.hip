@@ -1187,6 +1187,12 @@ static int wait_count(const volatile double* at, double target, hipStream_t s, c
   return 0;
 }
 
+// An iteration is one graph launch.  Its 17 to 50 kernels launched one by one save
+// the 8 us between two graphs on the device but take the host 2.4 to 5 us each,
+// which is more than the device needs up to about 350,000 DOFs (32^3, 4 levels: 2200
+// us per solve from graphs, 2340 to 2530 launched; 64^3 3549 and 3374 to 3419), and
+// with several host threads doing so a process has ended with a segmentation
+// fault inside a launch.
 static int run_body(sgmg_hierarchy* h, int precond, int slot, hipStream_t s) {
   if (!h->o.use_graphs) return pcg_body(h, precond, slot, s);
   const int par = slot == SC_RZ0 ? 0 : 1;
@@ -2139,7 +2145,7 @@ struct sgmg_batch {
   int g_nitems = -1, g_maxit = -1, g_bs = -1;
   double g_rtol = -1.0;
   // stage-batched solve of the cached item set: stage tables, per-item
-  // partials, scalars and active flags, the prologue and iteration graphs
+  // partials, scalars and active flags
   struct Staged {
     bool ready = false;
     void* dmem = nullptr;
@@ -2151,8 +2157,8 @@ struct sgmg_batch {
     double* part = nullptr;
     double* scal = nullptr;
     int* flags = nullptr;          // [0, n): prologue, [n, 2n): iteration
-    int* h_flags = nullptr;        // coherent, device-mapped: the flags, then the
-    double* h_scal = nullptr;      // scalars and the number of the pass they are of
+    int* h_flags = nullptr;        // coherent, device-mapped: the flags; and, apart,
+    double* h_scal = nullptr;      // the scalars and the number of the pass they are of
     const int* d_hflags = nullptr; // device addresses of the two
     double* d_hscal = nullptr;
     double seq = 0.0;              // passes queued so far
@@ -2606,8 +2612,7 @@ int bs_tune_stencil(sgmg_batch* b, int n, hipStream_t s) {
   return 0;
 }
 
-// Stage tables, partials, scalars and flags of the cached item set, and the
-// two graphs.
+// Stage tables, partials, scalars and flags of the cached item set.
 int bs_prepare(sgmg_batch* b, int n, hipStream_t s) {
   auto& st = b->st;
   if (st.ready) return 0;

@@ -182,7 +182,7 @@ void conv(sgmg_unet* u, bool infer, int l, const float* x, int N, int D, int H, 
           float* rpre, const float* add, float* y, hipStream_t s) {
   const ULayer& L = u->L[l];
   if (L.k == 3 && infer)
-    launch_conv3_mfma(x, kUp[l], N, L.ci, L.co, D, H, W, L.wp, L.b, relu, rpre, add, y, s);
+    launch_conv3_mfma(x, kUp[l], N, L.ci, L.co, D, H, W, L.wp, L.b, relu, add, y, s);
   else if (L.k == 3)
     launch_conv3_train(x, kUp[l], N, L.ci, L.co, D, H, W, L.wps, L.b, relu, rpre, add, y, s);
   else
@@ -208,7 +208,7 @@ void forward(sgmg_unet* u, int N, int D, int H, int W, const float* x, hipStream
   conv(u, infer, 5, u->d3, N, D2, H2, W2, 1, infer ? nullptr : u->r6, u->r2, u->d2, s);
   if (infer) {
     const ULayer& L = u->L[6];
-    launch_conv3_mfma(u->d2, 1, N, L.ci, L.co, D, H, W, L.wp, L.b, 1, nullptr, u->r1, nullptr, s,
+    launch_conv3_mfma(u->d2, 1, N, L.ci, L.co, D, H, W, L.wp, L.b, 1, u->r1, nullptr, s,
                       u->L[7].wq, u->L[7].b, out);
     return;
   }
@@ -233,7 +233,7 @@ void conv_dgrad(sgmg_unet* u, int l, const float* dy, int N, int D, int H, int W
                 hipStream_t s) {
   const ULayer& L = u->L[l];
   if (L.k == 3)
-    launch_conv3_mfma(dy, 0, N, L.co, L.ci, D, H, W, L.wpt, nullptr, 0, nullptr, nullptr, dx, s);
+    launch_conv3_mfma(dy, 0, N, L.co, L.ci, D, H, W, L.wpt, nullptr, 0, nullptr, dx, s);
   else
     launch_conv_fwd(L.k, dy, N, L.co, L.ci, D, H, W, L.wt, nullptr, 0, nullptr, nullptr, dx, s);
 }

@@ -65,9 +65,9 @@ void launch_pack_conv3_flip(ConvPacks ps, hipStream_t s);
 // (Ci a multiple of 8); with hw (up = 1, Co = 16) the 1x1x1 head's three
 // channels hw, hb of the result are written to hy, and y may be NULL.
 void launch_conv3_mfma(const float* x, int up, int N, int Ci, int Co, int D, int H, int W,
-                       const uint4* wp, const float* b, int relu, float* rpre, const float* add,
-                       float* y, hipStream_t s, const float* hw = nullptr,
-                       const float* hb = nullptr, float* hy = nullptr);
+                       const uint4* wp, const float* b, int relu, const float* add, float* y,
+                       hipStream_t s, const float* hw = nullptr, const float* hb = nullptr,
+                       float* hy = nullptr);
 // The training pass's forward: one order of every sum, also with up = 1 (wp
 // packed with up 0).
 void launch_conv3_train(const float* x, int up, int N, int Ci, int Co, int D, int H, int W,
