@@ -386,8 +386,8 @@ int sgmg_pcg_solve_batch_graph(sgmg_batch* b, int nitems, const int* item_sys,
  * stream of its own: a worker takes whole systems, largest DOFs x load
  * cases first, and solves that system's items in item order with
  * sgmg_pcg_solve (the V-cycle preconditioner; the system's hierarchy, its
- * work vectors and its captured iteration graphs are used by one worker at
- * a time).  Each item's result is bitwise that of a lone sgmg_pcg_solve
+ * work vectors and its captured iteration graphs, which it uses here also
+ * with use_graphs 0, are used by one worker at a time).  Each item's result is bitwise that of a lone sgmg_pcg_solve
  * from the same u.  infos (host, nitems, may be NULL; a history buffer in
  * an entry is filled) and *total_ms (host wall time) as above.  The caller's
  * stream is synchronised before the workers start; all work has finished

@@ -3265,9 +3265,24 @@ int sgmg_pcg_solve_batch_concurrent(sgmg_batch* b, int nitems, const int* item_s
   SGMG_HIP(hipGetDevice(&dev));
   // Every system's iteration graphs are captured here, on the calling
   // thread, before any worker starts (sgmg_set_launch_shape drops them): the
-  // workers only launch graphs and never capture concurrently.
-  for (int k : order) TRY(capture_vcycle_graphs(b->hs[k], as_stream(stream)));
-  SGMG_HIP(hipStreamSynchronize(as_stream(stream)));   // the inputs are ready
+  // workers only launch graphs and never capture concurrently.  Systems set up
+  // without graphs replay them here too: thousands of single launches from several
+  // threads have ended a process with a segmentation fault inside one.
+  std::vector<int> graphs;
+  auto restore = [&]() {
+    for (size_t k = 0; k < graphs.size(); ++k) b->hs[order[k]]->o.use_graphs = graphs[k];
+  };
+  for (int k : order) {
+    graphs.push_back(b->hs[k]->o.use_graphs);
+    b->hs[k]->o.use_graphs = 1;
+    const int rc = capture_vcycle_graphs(b->hs[k], as_stream(stream));
+    if (rc) { restore(); return rc; }
+  }
+  if (hipStreamSynchronize(as_stream(stream)) != hipSuccess) {   // the inputs are ready
+    restore();
+    set_error("sync failed");
+    return SGMG_EHIP;
+  }
   std::atomic<int> next{0};
   std::atomic<int> failed{0};
   std::mutex mu;
@@ -3303,6 +3318,7 @@ int sgmg_pcg_solve_batch_concurrent(sgmg_batch* b, int nitems, const int* item_s
   const int nw = std::min<int>(nworkers, (int)order.size());
   for (int w = 0; w < nw; ++w) pool.emplace_back(worker);
   for (auto& t : pool) t.join();
+  restore();
   const double ms =
       std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
   if (total_ms) *total_ms = ms;

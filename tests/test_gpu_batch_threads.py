@@ -1,7 +1,7 @@
 """Concurrent batch solve with worker threads on systems on both sides of 100,000
 DOFs, two load cases each: the workers replay the systems' iteration graphs, so
 every item is bitwise the solve of its system by itself, by one worker or by
-three."""
+three, also where the systems were set up without graphs."""
 import numpy as np
 import pytest
 
@@ -13,10 +13,11 @@ pytestmark = pytest.mark.gpu
 DIMS = [(34, 32, 32), (16, 12, 12), (30, 34, 33), (33, 33, 30)]
 
 
-@pytest.mark.parametrize("workers", [1, 3])
-def test_items_are_the_single_solves(workers):
+@pytest.mark.parametrize("workers,use_graphs", [(1, 1), (3, 1), (3, 0)])
+def test_items_are_the_single_solves(workers, use_graphs):
     from paper_2604_26441_amd import simpgmg
-    opts = [simpgmg.default_options(*d, n_levels=3, fine_prec="bf16x3") for d in DIMS]
+    opts = [simpgmg.default_options(*d, n_levels=3, fine_prec="bf16x3", use_graphs=use_graphs)
+            for d in DIMS]
     rhos = [t64(workloads.grf_rho(d, 11 + k)) for k, d in enumerate(DIMS)]
     rng = np.random.default_rng(4)
     items = [s for s in range(len(DIMS)) for _ in range(2)]
