@@ -60,13 +60,15 @@ namespace {
 
 void set_err(const std::string& m) { sgmg::set_error(m); }
 
-int ualloc(std::vector<void*>& mem, float** p, size_t n) {
+// Zeroed on the stream that will use it: the null stream's clearing is not
+// ordered with other streams and may come after their first writes.
+int ualloc(std::vector<void*>& mem, float** p, size_t n, hipStream_t s) {
   void* v = nullptr;
   if (hipMalloc(&v, std::max<size_t>(n, 1) * sizeof(float)) != hipSuccess) {
     set_err("U-Net allocation failed");
     return SGMG_ENOMEM;
   }
-  hipMemset(v, 0, std::max<size_t>(n, 1) * sizeof(float));
+  hipMemsetAsync(v, 0, std::max<size_t>(n, 1) * sizeof(float), s);
   mem.push_back(v);
   *p = (float*)v;
   return 0;
@@ -107,7 +109,7 @@ void free_act(sgmg_unet* u) {
   u->aN = 0;
 }
 
-int ensure_act(sgmg_unet* u, int N, int D, int H, int W) {
+int ensure_act(sgmg_unet* u, int N, int D, int H, int W, hipStream_t s) {
   if (u->aN == N && u->aD == D && u->aH == H && u->aW == W) return 0;
   free_act(u);
   const size_t v1 = (size_t)D * H * W, v2 = v1 / 8, v3 = v2 / 8, v4 = v3 / 8;
@@ -130,11 +132,11 @@ int ensure_act(sgmg_unet* u, int N, int D, int H, int W) {
   // every activation/gradient buffer is sized for the largest tensor
   // (N x 32 x full resolution) so the backward pass can reuse them freely
   for (const Req& r : reqs)
-    if (ualloc(u->act, r.p, std::max(r.n, (size_t)N * 32 * v1))) return SGMG_ENOMEM;
-  void* s = nullptr;
-  if (hipMalloc(&s, 2 * sizeof(double)) != hipSuccess) return SGMG_ENOMEM;
-  u->act.push_back(s);
-  u->sums = (double*)s;
+    if (ualloc(u->act, r.p, std::max(r.n, (size_t)N * 32 * v1), s)) return SGMG_ENOMEM;
+  void* v = nullptr;
+  if (hipMalloc(&v, 2 * sizeof(double)) != hipSuccess) return SGMG_ENOMEM;
+  u->act.push_back(v);
+  u->sums = (double*)v;
   void* pp = nullptr;
   if (hipMalloc(&pp, 2 * 1024 * sizeof(double)) != hipSuccess) return SGMG_ENOMEM;
   u->act.push_back(pp);
@@ -304,17 +306,17 @@ int sgmg_unet_create(uint64_t seed, sgmg_unet** out) {
     L.nw = (size_t)L.ci * L.k3 * L.cop;
     int rc = 0;
     for (float** p : {&L.w, &L.wq, &L.gw, &L.mw, &L.vw})
-      if (!rc) rc = ualloc(u->mem, p, L.nw);
+      if (!rc) rc = ualloc(u->mem, p, L.nw, 0);
     for (float** p : {&L.b, &L.gb, &L.mb, &L.vb})
-      if (!rc) rc = ualloc(u->mem, p, L.cop);
-    if (!rc && L.k != 3) rc = ualloc(u->mem, &L.wt, (size_t)L.co * L.k3 * L.cip);
+      if (!rc) rc = ualloc(u->mem, p, L.cop, 0);
+    if (!rc && L.k != 3) rc = ualloc(u->mem, &L.wt, (size_t)L.co * L.k3 * L.cip, 0);
     if (!rc && L.k == 3) {
       float* a = nullptr;
-      rc = ualloc(u->mem, &a, 4 * conv3_packed_words(kUp[l], L.ci, L.co));
+      rc = ualloc(u->mem, &a, 4 * conv3_packed_words(kUp[l], L.ci, L.co), 0);
       L.wp = (uint4*)a;
-      if (!rc && kUp[l]) rc = ualloc(u->mem, &a, 4 * conv3_packed_words(0, L.ci, L.co));
+      if (!rc && kUp[l]) rc = ualloc(u->mem, &a, 4 * conv3_packed_words(0, L.ci, L.co), 0);
       L.wps = (uint4*)a;
-      if (!rc) rc = ualloc(u->mem, &a, 4 * conv3_packed_words(0, L.co, L.ci));
+      if (!rc) rc = ualloc(u->mem, &a, 4 * conv3_packed_words(0, L.co, L.ci), 0);
       L.wpt = (uint4*)a;
     }
     if (rc) { sgmg_unet_destroy(u); return rc; }
@@ -374,7 +376,7 @@ int sgmg_unet_set_params(sgmg_unet* u, const float* host, void* stream) {
 // 1120, 850 by layers; then 190, 680 by layers).
 static int copy_out(sgmg_unet* u, float* host, bool grads, bool quantized, hipStream_t s) {
   const size_t n = (size_t)sgmg_unet_num_params();
-  if (!u->flat && ualloc(u->mem, &u->flat, n)) return SGMG_ENOMEM;
+  if (!u->flat && ualloc(u->mem, &u->flat, n, s)) return SGMG_ENOMEM;
   if (u->copied && !u->h_flat &&
       hipHostMalloc((void**)&u->h_flat, n * sizeof(float), hipHostMallocDefault) != hipSuccess) {
     u->h_flat = nullptr;
@@ -412,8 +414,8 @@ int sgmg_unet_forward(sgmg_unet* u, int N, int D, int H, int W, const float* in,
   if (!u || !in || !out) { set_err("NULL argument"); return SGMG_EINVAL; }
   int rc = check_dims(N, D, H, W);
   if (rc) return rc;
-  if ((rc = ensure_act(u, N, D, H, W))) return rc;
   hipStream_t s = (hipStream_t)stream;
+  if ((rc = ensure_act(u, N, D, H, W, s))) return rc;
   forward(u, N, D, H, W, in, s, true, out);
   return check();
 }
@@ -444,7 +446,7 @@ static int loss_and_grad(sgmg_unet* u, int N, int D, int H, int W, const float* 
                          float* grads_host, hipStream_t s) {
   int rc = check_dims(N, D, H, W);
   if (rc) return rc;
-  if ((rc = ensure_act(u, N, D, H, W))) return rc;
+  if ((rc = ensure_act(u, N, D, H, W, s))) return rc;
   forward(u, N, D, H, W, in, s);
   RedWs ws{u->partials, nullptr};
   launch_mse(u->y, target, mask, N, 3, D * H * W, u->gy, ws, u->sums, s);
@@ -484,8 +486,8 @@ int sgmg_unet_energy_step(sgmg_unet* u, const sgmg_hierarchy* h, int N, int D, i
     set_err("padded volume smaller than the node grid");
     return SGMG_EINVAL;
   }
-  if ((rc = ensure_act(u, N, D, H, W)) || (rc = ensure_energy(u, N, fv.g))) return rc;
   hipStream_t s = (hipStream_t)stream;
+  if ((rc = ensure_act(u, N, D, H, W, s)) || (rc = ensure_energy(u, N, fv.g))) return rc;
   forward(u, N, D, H, W, in, s);
   launch_simp(rho_or_E, u->eE, u->eE32, N * fv.g.nel, fv.is_modulus, fv.E0, fv.Emin, fv.penal, s);
   EnergyBatch e;
